@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <memory>
 #include <mutex>
 #include <cmath>
 #include <climits>
@@ -14,6 +15,7 @@
 
 #include "helm.h"
 #include "helm_launch.h"
+#include "helm_nd.h"
 
 using namespace helm;
 
@@ -22,10 +24,11 @@ struct helm_factor_s {
     int np;
     int prec;
     double omega;
-    void* G;       // nz * np * np complex (16 B for FP64, 8 B for FP32)
+    void* G;       // nz * np * np complex (16 B for FP64, 8 B for FP32), or the fronts of nd
     double* m;     // device copy of the model
-    size_t bytes;
     size_t gbytes;    // size of G
+    std::shared_ptr<NdPlan> nd;   // nested-dissection factor: G holds its fronts (complex128); else null
+    bool grown = false;           // of which a tile inverse grew: plain solves are corrected once
     hipStream_t st;   // the stream it was made on (its memory is released there)
     // last use on every other stream a solve ran it on (an event each); at
     // release the factor's own stream waits for them, so the memory is not
@@ -368,6 +371,191 @@ int check_models(int count, const double* const* ms, const int64_t* ns, hipStrea
 }
 int check_model(const double* m, int64_t n, hipStream_t st) { return check_models(1, &m, &n, st); }
 
+// ------------------------------------------------ nested-dissection plans --
+// Panel-step launches of the block factorisation of one system.
+int block_steps(const helm_grid& g) {
+    const int k = twist_row(g.nz);
+    return (pad16(g.nx) + KB - 1) / KB * (k + 1);
+}
+// Grids whose block factorisation is at most this long keep it.
+constexpr int ND_MIN_STEPS = 96;
+constexpr int64_t ND_MAX_NODES = (int64_t)1 << 26;   // the plan's tables are indexed in 32 bits
+
+// The plans made so far, one per (device, nx, nz): a plan depends on nothing
+// else, is read-only once made, and is shared by the factors of that grid on
+// every thread and stream.  Plans no factor uses are kept for the next one,
+// up to PLAN_KEEP of them; the oldest of the others is given back when a new
+// plan is made (hipFree waits for work that may still read its tables).
+struct PlanCache {
+    static constexpr size_t PLAN_KEEP = 16;
+    struct Entry {
+        int dev, nx, nz;
+        int64_t elems;
+        std::shared_ptr<NdPlan> plan;   // null: described only
+    };
+    std::mutex mu;
+    std::vector<Entry> entries;   // oldest use first
+
+    Entry& find_locked(int dev, int nx, int nz) {
+        for (size_t q = 0; q < entries.size(); ++q)
+            if (entries[q].dev == dev && entries[q].nx == nx && entries[q].nz == nz) {
+                std::rotate(entries.begin() + q, entries.begin() + q + 1, entries.end());
+                return entries.back();
+            }
+        size_t idle = 0;
+        for (auto& e : entries) idle += e.plan.use_count() <= 1;
+        for (size_t q = 0; q < entries.size() && idle >= PLAN_KEEP; ++q)
+            if (entries[q].plan.use_count() <= 1) {
+                if (entries[q].plan) {
+                    (void)hipFree(entries[q].plan->mem);
+                    (void)hipFree(entries[q].plan->reserve);
+                }
+                entries.erase(entries.begin() + q);
+                break;
+            }
+        entries.push_back({dev, nx, nz, nd_factor_elems(nx, nz), nullptr});
+        return entries.back();
+    }
+    int get(int nx, int nz, int64_t max_elems, std::shared_ptr<NdPlan>* out);
+};
+PlanCache g_plans;
+constexpr size_t NOALLOC_BYTES = (size_t)256 << 20;   // fixed region of helm_solve_noalloc
+constexpr size_t ND_SLACK = (size_t)1 << 20;          // of it, for tables and alignment
+
+// The plan of a grid, or null where its factor would exceed max_elems.
+int PlanCache::get(int nx, int nz, int64_t max_elems, std::shared_ptr<NdPlan>* out) {
+    out->reset();
+    int dev = 0;
+    HIPCHECK(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lk(mu);
+    Entry& e = find_locked(dev, nx, nz);
+    if (e.elems > max_elems) return HELM_OK;
+    if (!e.plan) {
+        auto p = std::make_shared<NdPlan>();
+        if (!nd_build(nx, nz, p.get())) {
+            e.elems = INT64_MAX;
+            return HELM_OK;
+        }
+        p->dev = dev;
+        auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+        struct Part {
+            const void* src;
+            size_t bytes, at;
+        };
+        Part parts[] = {{p->fronts.data(), sizeof(NdFront) * p->fronts.size(), 0},
+                        {p->ring.data(), sizeof(int) * p->ring.size(), 0},
+                        {p->map.data(), sizeof(int) * p->map.size(), 0},
+                        {p->nodeof.data(), sizeof(int) * p->nodeof.size(), 0},
+                        {p->tabs.data(), sizeof(int) * p->tabs.size(), 0},
+                        {p->tiles.data(), sizeof(NdTile) * p->tiles.size(), 0},
+                        {p->subs.data(), sizeof(NdSub) * p->subs.size(), 0},
+                        {p->shapes.data(), sizeof(NdShape) * p->shapes.size(), 0}};
+        size_t need = 0;
+        for (auto& q : parts) {
+            q.at = need;
+            need += up(std::max<size_t>(q.bytes, 1));
+        }
+        std::vector<char> host(need);
+        for (auto& q : parts)
+            if (q.bytes) std::memcpy(host.data() + q.at, q.src, q.bytes);
+        if (hipMalloc(&p->mem, need) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(HELM_ENOMEM, "plan allocation of " + std::to_string(need) + " bytes failed");
+        }
+        if (p->col_bytes() + ND_SLACK > NOALLOC_BYTES) {
+            p->reserve_bytes = p->col_bytes() + ND_SLACK;
+            if (hipMalloc(&p->reserve, p->reserve_bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                (void)hipFree(p->mem);
+                return fail(HELM_ENOMEM, "plan allocation of " + std::to_string(p->reserve_bytes) + " bytes failed");
+            }
+        }
+        if (hipMemcpy(p->mem, host.data(), need, hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipFree(p->mem);
+            (void)hipFree(p->reserve);
+            return fail(HELM_EDEVICE, "plan upload failed");
+        }
+        char* m = (char*)p->mem;
+        p->d_fronts = (const NdFront*)(m + parts[0].at);
+        p->d_ring = (const int*)(m + parts[1].at);
+        p->d_map = (const int*)(m + parts[2].at);
+        p->d_nodeof = (const int*)(m + parts[3].at);
+        p->d_tabs = (const int*)(m + parts[4].at);
+        p->d_tiles = (const NdTile*)(m + parts[5].at);
+        p->d_subs = (const NdSub*)(m + parts[6].at);
+        p->d_shapes = (const NdShape*)(m + parts[7].at);
+        // only the levels and sizes are needed on the host from here on
+        p->fronts = std::vector<NdFront>();
+        p->ring = std::vector<int>();
+        p->map = std::vector<int>();
+        p->nodeof = std::vector<int>();
+        p->tabs = std::vector<int>();
+        p->tiles = std::vector<NdTile>();
+        p->subs = std::vector<NdSub>();
+        p->shapes = std::vector<NdShape>();
+        e.plan = std::move(p);
+    }
+    *out = e.plan;
+    return HELM_OK;
+}
+
+NdTabs nd_tabs(const NdPlan& p) {
+    return {p.d_fronts, p.d_ring, p.d_map, p.d_nodeof, p.d_tabs, p.d_tiles, p.d_subs, p.d_shapes};
+}
+
+// The plan for a system of this grid and precision, or null where the block
+// factorisation serves it.
+int nd_choose(const helm_grid& g, int prec, std::shared_ptr<NdPlan>* out) {
+    out->reset();
+    if (block_steps(g) <= ND_MIN_STEPS || N_of(g) > ND_MAX_NODES) return HELM_OK;
+    const int64_t np = pad16(g.nx);
+    return g_plans.get(g.nx, g.nz, np * np * g.nz * (int64_t)elem_bytes(prec) / 16, out);
+}
+
+// Factor at most ND_MAXS systems of one plan together.  zero[c] is set where
+// system c met an exactly zero pivot.
+int nd_factor_group(helm_factor_s* const* fs, int n, int pivot, hipStream_t st, int* zero) {
+    const NdPlan& P = *fs[0]->nd;
+    Scratch sc(st);
+    double2 *w0, *w1;
+    int* status;
+    NdSysTab* dtab;
+    int rc;
+    if ((rc = sc.get(&w0, sizeof(double2) * (size_t)P.work_elems[0] * n))) return rc;
+    if ((rc = sc.get(&w1, sizeof(double2) * (size_t)P.work_elems[1] * n))) return rc;
+    if ((rc = sc.get(&status, sizeof(int) * 4 * n))) return rc;
+    if ((rc = sc.get(&dtab, sizeof(NdSysTab)))) return rc;
+    launch_zero(status, sizeof(int) * 4 * n, st);
+    NdSysTab tab;
+    std::memset(&tab, 0, sizeof(tab));
+    for (int c = 0; c < n; ++c) {
+        NdSys& s = tab.s[c];
+        s.cf = coef_of(fs[c]);
+        s.fac = (double2*)fs[c]->G;
+        s.work[0] = w0 + (size_t)P.work_elems[0] * c;
+        s.work[1] = w1 + (size_t)P.work_elems[1] * c;
+        s.status = status + 4 * c;
+        s.pivot = pivot;
+    }
+    launch_nd_put_sys(tab, dtab, st);
+    const NdTabs t = nd_tabs(P);
+    KernelTimer::Pair pu;
+    const bool tu = g_timer.begin(0, st, &pu);
+    int64_t launches = 0;
+    for (auto& lv : P.levels) launches += launch_nd_level(t, lv, dtab, n, st);
+    if (tu) g_timer.end(pu, launches, st);
+    g_launches += 2 + launches;
+    HIPCHECK(hipGetLastError());
+    std::vector<int> hs(4 * n);
+    HIPCHECK(hipMemcpyAsync(hs.data(), status, sizeof(int) * hs.size(), hipMemcpyDeviceToHost, st));
+    HIPCHECK(hipStreamSynchronize(st));
+    for (int c = 0; c < n; ++c) {
+        zero[c] = hs[4 * c];
+        fs[c]->grown = hs[4 * c + 3] != 0;
+    }
+    return HELM_OK;
+}
+
 // ------------------------------------------------------------ factorisation --
 // Factor a group of at most MAXB / 2 systems of one precision in lockstep,
 // each as a top and (when nz >= 4) a bottom front: one initial launch, then
@@ -490,6 +678,9 @@ void destroy(helm_factor_s* f) {
     delete f;
 }
 
+// working memory of the fronts factored in one group
+constexpr size_t ND_WORK_BYTES = (size_t)8 << 30;
+
 int factor_many(int count, const helm_grid* grids, const double* const* m_devs, const double* omegas, int prec,
                 hipStream_t st, helm_factor_t* outs) {
     if (count <= 0 || !grids || !m_devs || !omegas || !outs) return fail(HELM_EINVAL, "bad batch arguments");
@@ -508,6 +699,15 @@ int factor_many(int count, const helm_grid* grids, const double* const* m_devs, 
     auto cleanup = [&]() {
         for (auto* f : fs) destroy(f);
     };
+    auto store = [&](helm_factor_s* f, size_t bytes) -> int {
+        f->gbytes = bytes;
+        if (g_cache.get(&f->G, bytes, st) == hipSuccess) return HELM_OK;
+        f->G = nullptr;
+        return fail(HELM_ENOMEM, "factor allocation of " + std::to_string(bytes) + " bytes failed");
+    };
+    auto block_bytes = [&](const helm_factor_s* f) {
+        return (size_t)f->np * f->np * (size_t)f->g.nz * elem_bytes(prec);
+    };
     for (int c = 0; c < count; ++c) {
         helm_factor_s* f = new helm_factor_s();
         fs[c] = f;
@@ -515,14 +715,12 @@ int factor_many(int count, const helm_grid* grids, const double* const* m_devs, 
         f->np = pad16(grids[c].nx);
         f->prec = prec;
         f->omega = omegas[c];
-        f->bytes = factor_bytes_of(grids[c], prec);
         f->st = st;
-        size_t gb = (size_t)f->np * f->np * (size_t)grids[c].nz * elem_bytes(prec);
-        f->gbytes = gb;
-        if (g_cache.get(&f->G, gb, st) != hipSuccess) {
-            f->G = nullptr;
+        int rc = nd_choose(grids[c], prec, &f->nd);
+        if (rc == HELM_OK) rc = store(f, f->nd ? sizeof(double2) * (size_t)f->nd->fac_elems : block_bytes(f));
+        if (rc) {
             cleanup();
-            return fail(HELM_ENOMEM, "factor allocation of " + std::to_string(gb) + " bytes failed");
+            return rc;
         }
         if (g_cache.get((void**)&f->m, sizeof(double) * N_of(grids[c]), st) != hipSuccess) {
             f->m = nullptr;
@@ -535,11 +733,41 @@ int factor_many(int count, const helm_grid* grids, const double* const* m_devs, 
             return fail(HELM_EDEVICE, "model copy failed");
         }
     }
-    for (int c0 = 0; c0 < count; c0 += MAXF) {
-        const int k = std::min(MAXF, count - c0);
+    // nested-dissection systems, those of one plan together
+    std::vector<char> done(count, 0);
+    for (int c = 0; c < count; ++c) {
+        if (!fs[c]->nd || done[c]) continue;
+        const size_t work = sizeof(double2) * (size_t)(fs[c]->nd->work_elems[0] + fs[c]->nd->work_elems[1]);
+        const int room = (int)std::max<size_t>(1, std::min<size_t>(ND_MAXS, ND_WORK_BYTES / std::max<size_t>(work, 1)));
+        std::vector<helm_factor_s*> grp;
+        for (int d = c; d < count && (int)grp.size() < room; ++d)
+            if (!done[d] && fs[d]->nd == fs[c]->nd) {
+                grp.push_back(fs[d]);
+                done[d] = 1;
+            }
+        std::vector<int> zero(grp.size(), 0);
+        int rc = nd_factor_group(grp.data(), (int)grp.size(), g_force_pivot, st, zero.data());
+        // a zero pivot inside a box: the block factorisation, whose blocks
+        // reach the absorbing boundary, takes the system
+        for (size_t q = 0; q < grp.size() && rc == HELM_OK; ++q)
+            if (zero[q]) {
+                g_cache.put(grp[q]->G, grp[q]->gbytes, st);
+                grp[q]->nd.reset();
+                rc = store(grp[q], block_bytes(grp[q]));
+            }
+        if (rc) {
+            cleanup();
+            return rc;
+        }
+    }
+    std::vector<helm_factor_s*> blk;
+    for (auto* f : fs)
+        if (!f->nd) blk.push_back(f);
+    for (size_t c0 = 0; c0 < blk.size(); c0 += MAXF) {
+        const int k = (int)std::min<size_t>(MAXF, blk.size() - c0);
         bool needs = false;
-        int rc = factor_group(fs.data() + c0, k, g_force_pivot, st, &needs);
-        if (rc == HELM_OK && needs) rc = factor_group(fs.data() + c0, k, 1, st, &needs);
+        int rc = factor_group(blk.data() + c0, k, g_force_pivot, st, &needs);
+        if (rc == HELM_OK && needs) rc = factor_group(blk.data() + c0, k, 1, st, &needs);
         if (rc) {
             cleanup();
             return rc;
@@ -688,7 +916,8 @@ int residual_norms(const helm_factor_s* f, int adjoint, const double* B, int64_t
 }
 
 // The same for several (factor, B, X) at once: every residual is launched,
-// then one synchronisation brings all norms back.  maxrel[c] per request.
+// then one copy brings all norms back (a copy per request held up the next
+// launch: 30 us of idle GPU each).  maxrel[c] per request.
 struct ResidualReq {
     const helm_factor_s* f;
     const double* B;
@@ -703,25 +932,25 @@ int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStr
     const int n = (int)rq.size();
     if (n == 0) return HELM_OK;
     Scratch sc(st);
-    std::vector<double*> norms(n);
+    double* norms;
     size_t tot = 0;
     for (auto& r : rq) tot += 2 * (size_t)r.S;
     std::vector<double> h(tot);
+    int rc = sc.get(&norms, sizeof(double) * tot);
+    if (rc) return rc;
     size_t off = 0;
     for (int c = 0; c < n; ++c) {
         const ResidualReq& r = rq[c];
         const int64_t N = N_of(r.f->g);
         const int nblk = (int)((N + 255) / 256);
         double* partial;
-        int rc = sc.get(&partial, sizeof(double) * 2 * (size_t)nblk * r.S);
-        if (rc) return rc;
-        if ((rc = sc.get(&norms[c], sizeof(double) * 2 * r.S))) return rc;
+        if ((rc = sc.get(&partial, sizeof(double) * 2 * (size_t)nblk * r.S))) return rc;
         launch_residual(coef_of(r.f), adjoint, r.B, r.ldb, r.X, r.ldx, r.R, N, r.R32, r.S, partial, nblk, st);
-        launch_norms_finish(partial, nblk, r.S, norms[c], st);
+        launch_norms_finish(partial, nblk, r.S, norms + off, st);
         g_launches += 2;
-        HIPCHECK(hipMemcpyAsync(h.data() + off, norms[c], sizeof(double) * 2 * r.S, hipMemcpyDeviceToHost, st));
         off += 2 * (size_t)r.S;
     }
+    HIPCHECK(hipMemcpyAsync(h.data(), norms, sizeof(double) * tot, hipMemcpyDeviceToHost, st));
     HIPCHECK(hipStreamSynchronize(st));
     off = 0;
     for (int c = 0; c < n; ++c) {
@@ -739,8 +968,158 @@ int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStr
 
 constexpr int MAX_IR = 10;
 
+// ------------------------------------------- nested-dissection solves --
+// X = A^{-1} B (or X += A^{-1}(B - A X)) for jobs of one plan, at most
+// ND_MAXS of them, in blocks of columns that fit the scratch memory.  Every
+// column is computed alone, so the blocking changes no result.
+constexpr size_t ND_SOLVE_BYTES = (size_t)8 << 30;
+
+int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipStream_t st) {
+    const NdPlan& P = *js[0]->f->nd;
+    const int n = (int)js.size();
+    const int64_t N = (int64_t)P.nx * P.nz;
+    int smax = 0;
+    int64_t stot = 0;
+    for (auto* jb : js) {
+        smax = std::max(smax, jb->S);
+        stot += jb->S;
+    }
+    const size_t room = g_arena ? g_arena->cap - al256(g_arena->used) - ND_SLACK / 2 : ND_SOLVE_BYTES;
+    int cols = smax;
+    if (P.col_bytes() * (size_t)stot > room) {
+        cols = (int)std::min<size_t>(smax, std::max<size_t>(1, room / (P.col_bytes() * n)));
+        if (cols > 16) cols = cols / 16 * 16;
+    }
+    Scratch sc(st);
+    NdJobTab tab;
+    std::memset(&tab, 0, sizeof(tab));
+    NdJobTab* dtab;
+    int rc;
+    if ((rc = sc.get(&dtab, sizeof(NdJobTab)))) return rc;
+    std::vector<double*> R(n, nullptr), part(n, nullptr);
+    const int nblk = (int)((N + 255) / 256);
+    for (int c = 0; c < n; ++c) {
+        NdJob& d = tab.j[c];
+        const size_t S = (size_t)std::min(js[c]->S, cols);
+        d.cf = coef_of(js[c]->f);
+        d.fac = (const double2*)js[c]->f->G;
+        d.ldx = js[c]->ld;
+        d.ldb = correct ? N : js[c]->ld;
+        if ((rc = sc.get(&d.a, sizeof(double2) * (size_t)std::max(P.nrow_up, 1) * S))) return rc;
+        if ((rc = sc.get(&d.y, sizeof(double2) * (size_t)std::max(P.nrow, 1) * S))) return rc;
+        for (int q = 0; q < 2; ++q)
+            if ((rc = sc.get(&d.u[q], sizeof(double2) * (size_t)std::max<int64_t>(P.urows[q], 1) * S))) return rc;
+        if (correct) {
+            if ((rc = sc.get(&R[c], sizeof(double2) * (size_t)N * S))) return rc;
+            if ((rc = sc.get(&part[c], sizeof(double) * 2 * (size_t)nblk * S))) return rc;
+        }
+        g_solves += js[c]->S;
+    }
+    const NdTabs t = nd_tabs(P);
+    const int L = (int)P.levels.size();
+    for (int c0 = 0; c0 < smax; c0 += cols) {
+        int wide = 0;
+        for (int c = 0; c < n; ++c) {
+            NdJob& d = tab.j[c];
+            d.S = std::max(0, std::min(cols, js[c]->S - c0));
+            d.B = (const double2*)js[c]->B + (size_t)c0 * js[c]->ld;
+            d.X = (double2*)js[c]->X + (size_t)c0 * js[c]->ld;
+            wide = std::max(wide, d.S);
+            if (correct && d.S > 0) {
+                launch_residual(d.cf, adjoint ? 1 : 0, (const double*)d.B, js[c]->ld, (const double*)d.X, js[c]->ld,
+                                R[c], N, nullptr, d.S, part[c], nblk, st);
+                g_launches += 1;
+                d.B = (const double2*)R[c];
+            }
+        }
+        launch_nd_put_jobs(tab, dtab, st);
+        if (P.nrow_up) launch_nd_in(t, dtab, n, P.nrow_up, wide, adjoint, st);
+        KernelTimer::Pair p;
+        const bool tm = g_timer.begin(2, st, &p);
+        launch_nd_sub_forward(t, P, dtab, n, wide, adjoint, st);
+        for (int q = P.upper; q < L; ++q) launch_nd_forward(t, P.levels[q], dtab, n, wide, st);
+        for (int q = L - 1; q >= P.upper; --q) launch_nd_backward(t, P.levels[q], dtab, n, wide, st);
+        launch_nd_sub_backward(t, P, dtab, n, wide, correct, adjoint, st);
+        if (tm) g_timer.end(p, 2 + 2 * (L - P.upper), st);
+        if (P.nrow_up) launch_nd_out(t, dtab, n, P.nrow_up, wide, correct, adjoint, st);
+        g_launches += 5 + 2 * (L - P.upper);
+    }
+    HIPCHECK(hipGetLastError());
+    return HELM_OK;
+}
+
+// Solve jobs whose factors are nested-dissection ones (complex128 in either
+// precision), to tol where one is given or the precision implies one.
+int nd_solve_jobs(std::vector<SolveJob*>& jobs, bool adjoint, double tol, hipStream_t st) {
+    const int n = (int)jobs.size();
+    const bool refined = jobs[0]->f->prec == HELM_FP32_IR;
+    if (refined && tol <= 0.0) tol = 1e-10;
+    auto sweep = [&](const std::vector<int>& idx, bool correct) -> int {
+        std::vector<char> done(n, 0);
+        for (int c : idx) {
+            if (done[c]) continue;
+            std::vector<SolveJob*> grp;
+            for (int d : idx)
+                if (!done[d] && jobs[d]->f->nd == jobs[c]->f->nd && (int)grp.size() < ND_MAXS) {
+                    grp.push_back(jobs[d]);
+                    done[d] = 1;
+                }
+            if (int rc = nd_sweep(grp, correct, adjoint, st)) return rc;
+        }
+        return HELM_OK;
+    };
+    std::vector<int> act(n), iters(n, 0);
+    for (int c = 0; c < n; ++c) act[c] = c;
+    if (int rc = sweep(act, false)) return rc;
+    std::vector<double> rels(n, -1.0);
+    int worst = HELM_OK;
+    if (!(tol > 0.0)) {
+        // no residual is measured: where the factor says digits were lost,
+        // one correction, queued without a wait
+        std::vector<int> grown;
+        for (int c = 0; c < n; ++c)
+            if (jobs[c]->f->grown) grown.push_back(c);
+        if (!grown.empty())
+            if (int rc = sweep(grown, true)) return rc;
+        for (int c : grown) iters[c] = 1;
+    } else {
+        for (;;) {
+            std::vector<ResidualReq> rq;
+            for (int c : act)
+                rq.push_back({jobs[c]->f, jobs[c]->B, jobs[c]->ld, jobs[c]->X, jobs[c]->ld, nullptr, nullptr, jobs[c]->S});
+            std::vector<double> rel(act.size());
+            if (int rc = residual_norms_batch(rq, adjoint ? 1 : 0, st, rel.data())) return rc;
+            std::vector<int> next;
+            for (size_t q = 0; q < act.size(); ++q) {
+                const int c = act[q];
+                rels[c] = rel[q];
+                // one correction too where a box near resonance cost digits:
+                // the plain solve is otherwise far below any tolerance used
+                const bool more = !(rel[q] <= tol) || (iters[c] == 0 && rel[q] > 0.01 * tol);
+                if (more && iters[c] < MAX_IR) next.push_back(c);
+            }
+            act = next;
+            if (act.empty()) break;
+            if (int rc = sweep(act, true)) return rc;
+            for (int c : act) ++iters[c];
+        }
+        for (int c = 0; c < n; ++c)
+            if (!(rels[c] <= tol))
+                worst = fail(HELM_ENOCONV, "refinement stopped at relative residual " + std::to_string(rels[c]) + " > " +
+                                               std::to_string(tol));
+    }
+    for (int c = 0; c < n; ++c)
+        if (helm_info* i = jobs[c]->info) {
+            i->ir_iters = iters[c];
+            i->max_relres = rels[c];
+            i->solves = (int64_t)jobs[c]->S * (1 + iters[c]);
+        }
+    return worst;
+}
+
 // Solve a group of jobs that share one precision.
 int solve_jobs_on(std::vector<SolveJob>& jobs, bool adjoint, double tol, hipStream_t st);
+int block_solve_jobs(std::vector<SolveJob>& jobs, bool adjoint, double tol, hipStream_t st);
 
 int solve_jobs(std::vector<SolveJob>& jobs, bool adjoint, double tol, hipStream_t st) {
     const int rc = solve_jobs_on(jobs, adjoint, tol, st);
@@ -749,9 +1128,8 @@ int solve_jobs(std::vector<SolveJob>& jobs, bool adjoint, double tol, hipStream_
 }
 
 int solve_jobs_on(std::vector<SolveJob>& jobs, bool adjoint, double tol, hipStream_t st) {
-    const int n = (int)jobs.size();
-    if (n == 0) return HELM_OK;
-    const bool fp32 = jobs[0].f->prec == HELM_FP32_IR;
+    std::vector<SolveJob*> nd;
+    std::vector<SolveJob> blk;
     for (auto& jb : jobs) {
         if (jb.info) {
             jb.info->ir_iters = 0;
@@ -760,7 +1138,20 @@ int solve_jobs_on(std::vector<SolveJob>& jobs, bool adjoint, double tol, hipStre
             jb.info->bad_row = -1;
             jb.info->solves = 0;
         }
+        if (jb.f->nd) nd.push_back(&jb);
+        else blk.push_back(jb);
     }
+    int rc = nd.empty() ? HELM_OK : nd_solve_jobs(nd, adjoint, tol, st);
+    // a refinement that fails leaves the other systems to be solved
+    if (rc != HELM_OK && rc != HELM_ENOCONV) return rc;
+    const int rb = block_solve_jobs(blk, adjoint, tol, st);
+    return rc ? rc : rb;
+}
+
+int block_solve_jobs(std::vector<SolveJob>& jobs, bool adjoint, double tol, hipStream_t st) {
+    const int n = (int)jobs.size();
+    if (n == 0) return HELM_OK;
+    const bool fp32 = jobs[0].f->prec == HELM_FP32_IR;
     std::vector<helm_factor_s*> fs(n);
     for (int c = 0; c < n; ++c) fs[c] = jobs[c].f;
     if (!fp32) {
@@ -1873,7 +2264,6 @@ int fwi_run(Fwi& P, double* x, const helm_lbfgs_opts& o, double* hist, helm_fwi_
 // The scratch of helm_solve_noalloc: a fixed device array.  Host code never
 // passes `scratch` itself (on the host it names a stand-in, not device
 // memory); it uses the address hipGetSymbolAddress gives on each device.
-constexpr size_t NOALLOC_BYTES = (size_t)256 << 20;
 static __device__ __align__(256) char scratch[NOALLOC_BYTES];
 
 namespace {
@@ -1995,6 +2385,7 @@ int helm_solve_noalloc(helm_factor_t f, const double* B_dev, double* X_dev, int3
     void* base = nullptr;
     if ((rc = noalloc_region(&base))) return rc;
     Arena arena{(char*)base, NOALLOC_BYTES, 0};
+    if (f->nd && f->nd->reserve) arena = Arena{(char*)f->nd->reserve, f->nd->reserve_bytes, 0};
     ArenaScope scope(&arena);
     std::vector<SolveJob> jobs{{f, B_dev, X_dev, S, ld, info}};
     // untracked (tracking would create an event): the caller keeps f alive

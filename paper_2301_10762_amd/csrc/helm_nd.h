@@ -1,0 +1,199 @@
+// Nested-dissection factorisation: the elimination tree of a grid (its plan)
+// and the tables the kernels read.  Host and device.
+#pragma once
+#include <memory>
+#include <vector>
+
+#include "helm_internal.h"
+
+namespace helm {
+
+// Nodes of a subtree that one workgroup sweeps: with 16 columns its vectors
+// take about 57 KB of LDS, so that two workgroups share a CU.
+constexpr int ND_SUB = 170;
+constexpr int ND_SUB_LEAVES = 16;   // 16-row tiles of its leaves, at most
+
+// One front of the elimination tree: the p pivots of a box's separator line
+// (or all nodes of a leaf box) and the b nodes of the ring around the box,
+// all of which belong to separators eliminated later.  Local indices
+// 0 .. p-1 are the pivots, p .. p+b-1 the ring; in the working memory the
+// pivots are padded to pp and the ring to fp - pp (multiples of 16), pivots
+// with an identity tail.
+//
+// A leaf keeps G, the inverse of its block of the operator, alone: a ring
+// node couples to one node of the leaf, so its R = G F is a scaled column of
+// G and its Schur complement a scaled part of G, taken where needed.
+struct NdFront {
+    int p, b, pp, fp;
+    int piv0;          // first pivot's row (separators; rows are numbered below)
+    int ring;          // the ring's rows: ring[ring .. ring + b)
+    int child[2];      // fronts of the two halves, or -1
+    int map[2];        // per local index (p + b of them): its place in the child's ring
+                       // (a leaf child: the leaf node it couples to), or -1
+    int npan;          // panels of KB pivots
+    int urow;          // first row of its ring contributions in the level's vector block
+    int curow[2];      // the halves' urow
+    int64_t fac;       // factor store: [G | R], p x (p + b), column-major (a leaf: G)
+    int64_t work;      // a wide front's working memory (nd_rows, nd_tslot)
+    int64_t s;         // Schur complement on the ring (b x b, row-major), valid for row <= column
+    int leaf;
+    int pad_;
+    int x0, z0, w, h;  // box
+};
+static_assert(sizeof(NdFront) % 8 == 0, "fronts are read as whole words");
+
+// a 64 x 64 tile of a front's pivot rows or (ti <= tj) of its ring, or a 16-row tile of
+// a front's sweep product; front: index within the level
+struct NdTile {
+    int front;
+    short ti, tj;
+};
+
+struct NdLevel {
+    int first, count;         // fronts
+    int parity;               // which of the two working regions and vector blocks it uses
+    bool leaf;                // the leaves
+    bool small;               // narrow fronts: one workgroup each
+    int npan;                 // panels of the front with most
+    int tile0, tiles;         // 64 x 64 tiles of the pivot rows (wide fronts)
+    int stile0, stiles;       // and of the rings' upper halves
+    // levels above the subtrees
+    int frow0, frows, frt;    // forward sweep: groups of frt 16-row tiles of the rings
+    int brow0, brows;         // backward sweep: 16-row tiles of the pivots
+    int urows;                // rows of ring contributions
+    int pmax, fmax;           // widest pivot block and front (padded)
+};
+
+// The bottom of the tree is swept by one workgroup per subtree and 16
+// columns, with its vectors in LDS.  Subtrees of one size with rings on the
+// same sides share a shape, whose tables use local rows: z rows are the
+// subtree's separator nodes (deepest level first) and then its ring, w rows
+// the nodes of its leaves.
+struct NdLeaf {               // a 16-row tile of a leaf
+    int p, wrow, fac, tile;   // nodes, first w row, place in the subtree's factor
+};
+struct NdFwd {                // a 16-row tile of a front's ring
+    int zp, p, b, u, fac, tile;   // first z row of the pivots, rows of u from `u`
+};
+struct NdBwd {                // a front
+    int zp, p, b, ring, fac;  // ring: its z rows, in the shape's ring table
+};
+struct NdStep {               // a level of a shape, deepest first
+    int fwd, nfwd, add, nadd, bwd, nbwd;
+};
+struct NdShape {
+    int w, h, nsep, nring, nw, nu;   // nu: most rows of u of a level
+    int nleaf, leaf;          // leaf tiles
+    int nstep, step;          // levels
+    int box;                  // per node of the box: row (z rows, then w rows) | i << 12 | j << 22
+    int zst;                  // per z row: i, j, and the w rows left, right, above, below it (-1: none), as shorts
+    int wst;                  // per w row: i, j, and the z rows left, right, above, below it
+    int tab0, ntab;           // all of the shape's tables
+    int pad_;
+};
+struct NdSub {
+    int shape, x0, z0;
+    int row;                  // row of its first separator node
+    int ring;                 // its ring's rows in the ring table
+    int urow;                 // its ring contributions' first row
+    int64_t fac;
+};
+
+// The plan of an nx x nz grid: host description and device tables (one
+// allocation, complete when the plan is handed out).  Shared by every factor
+// on the grid; it depends on nothing but nx and nz.  Separator nodes have
+// rows: those above the subtrees first.
+struct NdPlan {
+    int nx = 0, nz = 0, dev = 0;
+    std::vector<NdFront> fronts;     // leaves, then deepest level first
+    std::vector<NdLevel> levels;     // leaves, then in elimination order (the root last)
+    int upper = 0;                   // first level above the subtrees
+    std::vector<int> ring, map, nodeof;
+    std::vector<NdTile> tiles;
+    std::vector<NdSub> subs;
+    std::vector<NdShape> shapes;
+    std::vector<int> tabs;           // the shapes' tables (NdLeaf, NdFwd, NdBwd, NdStep and index tables)
+    int sub_rows = 0, sub_tab = 0;   // most z, w rows of a subtree in LDS, words of a shape's tables
+    int sub_parity = 0;
+    int nrow = 0, nrow_up = 0;       // separator nodes, those above the subtrees
+    int nsub = 0;
+    int64_t fac_elems = 0;           // complex128 values of a factor
+    int64_t work_elems[2] = {0, 0};  // working memory of even and odd levels, per system
+    int64_t urows[2] = {0, 0};       // ring-contribution rows of even and odd levels
+    void* mem = nullptr;             // device tables
+    void* reserve = nullptr;         // scratch of one column's solve (grids beyond the fixed region only)
+    size_t reserve_bytes = 0;
+    const NdFront* d_fronts = nullptr;
+    const int *d_ring = nullptr, *d_map = nullptr, *d_nodeof = nullptr, *d_tabs = nullptr;
+    const NdTile* d_tiles = nullptr;
+    const NdSub* d_subs = nullptr;
+    const NdShape* d_shapes = nullptr;
+    size_t col_bytes() const {       // sweep scratch per right-hand side, with a residual
+        return sizeof(double) * 2 * ((size_t)nx * nz + (size_t)(nrow_up + nrow + urows[0] + urows[1]));
+    }
+};
+
+// host description only (no device memory); false: the grid does not divide
+// into subtrees of the size the sweeps take
+bool nd_build(int nx, int nz, NdPlan* plan);
+// complex128 values a factor of this grid stores
+int64_t nd_factor_elems(int nx, int nz);
+
+// device tables of a plan as the kernels take them
+struct NdTabs {
+    const NdFront* fronts;
+    const int *ring, *map, *nodeof, *tabs;
+    const NdTile* tiles;
+    const NdSub* subs;
+    const NdShape* shapes;
+};
+
+constexpr int ND_MAXS = 16;   // systems per launch
+
+struct NdSys {        // one system being factored
+    Coef cf;
+    double2* fac;
+    double2* work[2];   // working memory of even and odd levels
+    int* status;        // [0] zero-pivot flag, [1] front, [2] row, [3] grown inverses
+    int pivot;          // 1: partial pivoting in every tile
+    int pad_;
+};
+struct NdSysTab {
+    NdSys s[ND_MAXS];
+};
+struct NdJob {        // one block of right-hand sides being solved
+    Coef cf;
+    const double2* fac;
+    const double2* B;   // right-hand sides, column-major (ldb)
+    double2* X;         // solutions, column-major (ldx)
+    int64_t ldb, ldx;
+    double2* a;         // rows above the subtrees, [row][S]: right-hand sides, then the solution
+    double2* y;         // every row: forward results
+    double2* u[2];      // ring contributions of even and odd levels
+    int S, pad_;
+};
+struct NdJobTab {
+    NdJob j[ND_MAXS];
+};
+static_assert(sizeof(NdSysTab) <= 4000 && sizeof(NdJobTab) <= 4000, "tables pass through a kernel argument");
+
+void launch_nd_put_sys(const NdSysTab& tab, NdSysTab* dst, hipStream_t st);
+void launch_nd_put_jobs(const NdJobTab& tab, NdJobTab* dst, hipStream_t st);
+// LDS a workgroup of k_nd_front may take, and whether a level's fronts fit it
+constexpr size_t ND_LDS = 160 * 1024 - 512;
+bool nd_narrow(int pmax, int fmax);
+// factorisation of one level; returns the number of launches
+int launch_nd_level(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, int n, hipStream_t st);
+// right-hand sides of the rows above the subtrees (conjugated when conj), and their solutions back: X = a, or X += a
+void launch_nd_in(const NdTabs& t, const NdJobTab* djobs, int n, int rows, int smax, bool conj, hipStream_t st);
+void launch_nd_out(const NdTabs& t, const NdJobTab* djobs, int n, int rows, int smax, bool add, bool conj,
+                   hipStream_t st);
+void launch_nd_forward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st);
+void launch_nd_backward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st);
+// the subtrees' sweeps: from B to ring contributions, and from the rings' solutions to X
+void launch_nd_sub_forward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool conj,
+                           hipStream_t st);
+void launch_nd_sub_backward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool add,
+                            bool conj, hipStream_t st);
+
+}  // namespace helm

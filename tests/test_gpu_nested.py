@@ -1,0 +1,87 @@
+"""GPU: nested-dissection factors and solves against the FP64 oracle.
+
+Grids just above the size where the block factorisation hands over (65 x 65),
+odd and long rectangles in both directions (ring sides missing on one, two
+and three sides; separators of 16k, 16k + 1 and 32k + 1 nodes; leaves of every
+shape), one and 19 right-hand sides, forward and adjoint, in both precisions.
+Solutions are held to 1e-9 per column, the bound of the other parity tests
+(their conditioning is the same); residuals to the tolerance asked for.  A
+batch, a forced partial pivoting in every tile, a plain complex128 solve and
+the allocation-free solve are checked on the same grids.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from tests.parity import assert_cols
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+GRIDS = [(65, 65), (67, 77), (130, 51), (41, 140), (401, 37), (97, 129)]
+
+
+@pytest.fixture(scope="module")
+def helm():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2301_10762_amd import helm as h
+    h.lib()
+    yield h
+    h.set_tile_pivoting(False)
+
+
+def _system(nx, nz, S, ppw=9.0):
+    rng = np.random.default_rng(nx * 1000 + nz + S)
+    h = 0.025
+    m = 1.0 / (1.5 + 3.0 * rng.random(nx * nz)) ** 2
+    B = rng.standard_normal((S, nx * nz)) + 1j * rng.standard_normal((S, nx * nz))
+    return m, 2 * np.pi * 1.5 / (ppw * h), B, h
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("nx,nz", GRIDS)
+def test_nested_matches_oracle(helm, nx, nz, precision):
+    for S in (1, 19):
+        print(f"{nx}x{nz}, {S} columns, {precision}", flush=True)
+        m, w, B, h = _system(nx, nz, S)
+        G, Bd = helm.Grid(nx, nz, h, 0.9 * h), torch.as_tensor(B, device="cuda")
+        Fo = oracle.Factor(oracle.Grid(nx, nz, h, 0.9 * h), m, w)
+        Xo, Lo = Fo.solve(B), Fo.adjoint_solve(B)
+        Fo.close()
+        F = helm.factor(G, m, w, precision)
+        X, info = F.solve(Bd, tol=1e-10)
+        L, ainfo = F.adjoint_solve(Bd, tol=1e-10)
+        assert info.max_relres <= 1e-10 and ainfo.max_relres <= 1e-10
+        assert_cols(X.cpu().numpy(), Xo, 1e-9, what="forward")
+        assert_cols(L.cpu().numpy(), Lo, 1e-9, what="adjoint")
+        Xn = torch.full_like(Bd, complex(np.nan, np.nan))
+        helm.solve_noalloc(F, Bd, Xn, tol=1e-10)
+        assert torch.equal(Xn, X)
+        Xp, _ = F.solve(Bd)
+        assert_cols(Xp.cpu().numpy(), Xo, 1e-9, what="no tolerance")
+        F.close()
+        # with a second frequency and another block of columns in the batch: bitwise the same
+        Fs = helm.factor_batch([G, G], [m, m], [w, 0.7 * w], precision)
+        Xb, _ = helm.solve_batch(Fs, [Bd, Bd[:1].repeat(3, 1)], tol=1e-10)
+        assert torch.equal(Xb[0], X)
+        for F in Fs:
+            F.close()
+
+
+@pytest.mark.parametrize("nx,nz", [(65, 65), (41, 140)])
+def test_nested_forced_tile_pivoting(helm, nx, nz):
+    m, w, B, h = _system(nx, nz, 5)
+    Fo = oracle.Factor(oracle.Grid(nx, nz, h, h), m, w)
+    Xo = Fo.solve(B)
+    Fo.close()
+    helm.set_tile_pivoting(True)
+    try:
+        F = helm.factor(helm.Grid(nx, nz, h, h), m, w)
+    finally:
+        helm.set_tile_pivoting(False)
+    X, info = F.solve(torch.as_tensor(B, device="cuda"), tol=1e-10)
+    F.close()
+    assert info.max_relres <= 1e-10
+    assert_cols(X.cpu().numpy(), Xo, 1e-9, what="forced pivoting")
