@@ -85,14 +85,15 @@ struct NdShape {
     int w, h, nsep, nring, nw, nu;   // nu: most rows of u of a level
     int nleaf, leaf;          // leaf tiles
     int nstep, step;          // levels
-    int box;                  // per node of the box: row (z rows, then w rows) | i << 12 | j << 22
+    int box;                  // per node of the box: its row (z rows, then w rows)
     int zst;                  // per z row: i, j, and the w rows left, right, above, below it (-1: none), as shorts
     int wst;                  // per w row: i, j, and the z rows left, right, above, below it
     int tab0, ntab;           // all of the shape's tables
     int pad_;
 };
 struct NdSub {
-    int shape, x0, z0;
+    int shape, x0, z0, w, h;
+    int nsep, nring;          // rows of its separators and its ring
     int row;                  // row of its first separator node
     int ring;                 // its ring's rows in the ring table
     int urow;                 // its ring contributions' first row

@@ -1014,29 +1014,32 @@ struct SubCtx {
 };
 
 // this thread's (node, column) pairs of the box, node fastest (grid rows are
-// read along): f(i, entry of the box table, column)
+// read along): f(i, node of the box, column)
 template <typename F>
 __device__ __forceinline__ void nd_sub_each(const SubCtx& x, F f) {
-    const int nb = x.h.w * x.h.h;
+    const int nb = x.s.w * x.s.h;
     const float inv = 1.0f / (float)nb;
 #pragma unroll
     for (int i = 0; i < SUB_LD; ++i) {
         const int e = min((int)threadIdx.x + SUB_T * i, 16 * nb - 1);
         const int c = (int)(((float)e + 0.5f) * inv);
-        f(i, x.tab[x.h.box + e - c * nb], c);
+        f(i, e - c * nb, c);
     }
 }
+__device__ __forceinline__ int nd_sub_node(const SubCtx& x, int n) {   // its grid node
+    const int j = (int)(((float)n + 0.5f) * (1.0f / (float)x.s.w));
+    return (x.s.z0 + j) * x.d.cf.nx + x.s.x0 + n - j * x.s.w;
+}
 __device__ __forceinline__ void nd_sub_fetch(const SubCtx& x, double2 (&b)[SUB_LD]) {
-    nd_sub_each(x, [&](int i, int e, int c) {
-        const int k = (x.s.z0 + (e >> 22)) * x.d.cf.nx + x.s.x0 + ((e >> 12) & 1023);
-        b[i] = gld(x.d.B + (size_t)min(x.c0 + c, x.d.S - 1) * x.d.ldb + k);
+    nd_sub_each(x, [&](int i, int n, int c) {
+        b[i] = gld(x.d.B + (size_t)min(x.c0 + c, x.d.S - 1) * x.d.ldb + nd_sub_node(x, n));
     });
 }
 // leaf nodes only if !seps
 __device__ __forceinline__ void nd_sub_place(const SubCtx& x, const double2 (&b)[SUB_LD], bool seps, double2 (*v)[SUB_RS]) {
     const int nz = x.h.nsep + x.h.nring;
-    nd_sub_each(x, [&](int i, int e, int c) {
-        const int r = e & 4095;
+    nd_sub_each(x, [&](int i, int n, int c) {
+        const int r = x.tab[x.h.box + n];
         if (seps || r >= nz) v[r][c] = make_double2(b[i].x, x.conj ? -b[i].y : b[i].y);
     });
 }
@@ -1114,21 +1117,23 @@ __device__ __forceinline__ void nd_sub_stencil(const SubCtx& x, int tab, int row
     }
 }
 
-// Which subtree and column block a workgroup takes; false: none.
-__device__ __forceinline__ bool nd_sub_start(const NdTabs& t, const NdJobTab* jtab, int nsub, int nct,
-                                             SubCtx& x, int* stab) {
+// Which subtree and column block a workgroup takes; false: none.  The right-
+// hand sides (and the ring's indices) need its record only: they are on their
+// way before the shape's tables are.
+__device__ __forceinline__ bool nd_sub_start(const NdTabs& t, const NdJobTab* jtab, int nsub, int nct, SubCtx& x) {
     const int b = blockIdx.x, k = b >> 3;
-    const int sub = (k / nct) * 8 + (b & 7);
+    const int per = (nsub + 7) >> 3, sub = (b & 7) * per + k / nct;
     if (sub >= nsub) return false;
     x.d = nd_record(jtab->j, blockIdx.y);
     x.s = nd_record(t.subs, sub);
     x.c0 = 16 * (k % nct);
-    if (x.c0 >= x.d.S) return false;
+    return x.c0 < x.d.S;
+}
+__device__ __forceinline__ void nd_sub_tables(const NdTabs& t, SubCtx& x, int* stab) {
     x.h = nd_record(t.shapes, x.s.shape);
     const int* src = t.tabs + x.h.tab0;
     for (int i = threadIdx.x; i < x.h.ntab; i += SUB_T) stab[i] = src[i];
     x.tab = stab - x.h.tab0;
-    return true;
 }
 
 __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_forward(NdTabs t, int nsub, int nct, int rows,
@@ -1136,19 +1141,19 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_forward(NdTabs t, int nsub,
     extern __shared__ __attribute__((aligned(16))) double2 sub_smem[];
     double2 (*z)[SUB_RS] = (double2(*)[SUB_RS])sub_smem;
     SubCtx x;
-    if (!nd_sub_start(t, jtab, nsub, nct, x, (int*)(sub_smem + SUB_RS * rows))) return;
+    if (!nd_sub_start(t, jtab, nsub, nct, x)) return;
     x.conj = conj;
-    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lr = l & 15, lg = l >> 4;
-    const int nz = x.h.nsep + x.h.nring, S = x.d.S;
-    double2 (*wv)[SUB_RS] = z + nz;
-    double2 (*u)[SUB_RS] = wv;   // ring contributions, once the leaves' results are used
-    __syncthreads();
-    const int c0 = x.c0;
     double2 b[SUB_LD], g[SUB_K];
     nd_sub_fetch(x, b);
+    nd_sub_tables(t, x, (int*)(sub_smem + SUB_RS * rows));
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lr = l & 15, lg = l >> 4;
+    const int nz = x.h.nsep + x.h.nring, S = x.d.S, c0 = x.c0;
+    double2 (*wv)[SUB_RS] = z + nz;
+    double2 (*u)[SUB_RS] = wv;   // ring contributions, once the leaves' results are used
+    for (int q = tid; q < 16 * x.h.nring; q += SUB_T) z[x.h.nsep + (q >> 4)][q & 15] = make_double2(0.0, 0.0);
+    __syncthreads();
     if (w < x.h.nleaf) nd_sub_leaf_ops(x, nd_rec<NdLeaf>(x.tab, x.h.leaf, w), g);
     const double2* sfac = x.d.fac + x.s.fac;
-    for (int q = tid; q < 16 * x.h.nring; q += SUB_T) z[x.h.nsep + (q >> 4)][q & 15] = make_double2(0.0, 0.0);
     nd_sub_place(x, b, true, z);
     __syncthreads();
     nd_sub_leaves(x, g, wv);
@@ -1226,25 +1231,28 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
     double2 (*z)[SUB_RS] = (double2(*)[SUB_RS])sub_smem;
     double2 (*part)[16][16] = (double2(*)[16][16])(sub_smem + SUB_RS * rows);   // second halves' sums
     SubCtx x;
-    if (!nd_sub_start(t, jtab, nsub, nct, x, (int*)(part + SUB_W / 2))) return;
+    if (!nd_sub_start(t, jtab, nsub, nct, x)) return;
     x.conj = conj;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lr = l & 15, lg = l >> 4;
-    const int nz = x.h.nsep + x.h.nring, S = x.d.S;
+    const int S = x.d.S, c0 = x.c0, half = w & 1;
+    double2 b[SUB_LD], zr[4];
+    // separator and ring rows, by 16 columns, up to four per thread ahead
+    const double2* zp[4];
+    const int nz = x.s.nsep + x.s.nring;
+    auto zrow = [&](int q) {
+        const int r = q >> 4, c = min(c0 + (q & 15), S - 1);
+        return r < x.s.nsep ? x.d.y + (size_t)(x.s.row + r) * S + c
+                            : x.d.a + (size_t)t.ring[x.s.ring + r - x.s.nsep] * S + c;
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) zp[i] = zrow(min(tid + SUB_T * i, 16 * nz - 1));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) zr[i] = gld(zp[i]);
+    nd_sub_fetch(x, b);
+    nd_sub_tables(t, x, (int*)(part + SUB_W / 2));
     double2 (*wv)[SUB_RS] = z + nz;
     const double2* sfac = x.d.fac + x.s.fac;
     __syncthreads();
-    // separator and ring rows by 16 columns, up to four per thread ahead
-    const int c0 = x.c0, half = w & 1;
-    const double2* yv = x.d.y + (size_t)x.s.row * S;
-    const int* ring = t.ring + x.s.ring;
-    auto zrow = [&](int q) {   // separator and ring rows, by 16 columns
-        const int r = q >> 4, c = min(c0 + (q & 15), S - 1);
-        return gld(r < x.h.nsep ? yv + (size_t)r * S + c : x.d.a + (size_t)ring[r - x.h.nsep] * S + c);
-    };
-    double2 b[SUB_LD], zr[4];   // up to four of these per thread ahead
-    nd_sub_fetch(x, b);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) zr[i] = zrow(min(tid + SUB_T * i, 16 * nz - 1));
     // operands of steps s0 .. of a front's contraction, in fours: the pivots
     // (4 of them), then the ring; a level's first are loaded a level ahead
     double2 m[SUB_BK];
@@ -1265,11 +1273,11 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
         const int n = steps(f);
         ops(f, half ? (n + 1) / 2 : 0, half ? n : (n + 1) / 2);
     };
-    first(x.h.nstep - 1);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         if (tid + SUB_T * i < 16 * nz) z[(tid + SUB_T * i) >> 4][tid & 15] = zr[i];
-    for (int q = tid + 4 * SUB_T; q < 16 * nz; q += SUB_T) z[q >> 4][q & 15] = zrow(q);
+    for (int q = tid + 4 * SUB_T; q < 16 * nz; q += SUB_T) z[q >> 4][q & 15] = gld(zrow(q));
+    first(x.h.nstep - 1);
     nd_sub_place(x, b, false, z);
     __syncthreads();
     for (int q = x.h.nstep - 1; q >= 0; --q) {
@@ -1319,12 +1327,11 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
     nd_sub_leaves(x, g, wv);
     __syncthreads();
     const int nc = min(16, S - c0);
-    nd_sub_each(x, [&](int i, int e, int c) {
-        const int k = (x.s.z0 + (e >> 22)) * x.d.cf.nx + x.s.x0 + ((e >> 12) & 1023);
-        double2 v = z[e & 4095][c];
+    nd_sub_each(x, [&](int i, int n, int c) {
+        double2 v = z[x.tab[x.h.box + n]][c];
         if (conj) v.y = -v.y;
-        if (c < nc && tid + SUB_T * i < 16 * x.h.w * x.h.h)
-            nd_put_x(x.d.X + (size_t)(c0 + c) * x.d.ldx + k, v, add);
+        if (c < nc && tid + SUB_T * i < 16 * x.s.w * x.s.h)
+            nd_put_x(x.d.X + (size_t)(c0 + c) * x.d.ldx + nd_sub_node(x, n), v, add);
     });
 }
 
@@ -1358,16 +1365,28 @@ __device__ __forceinline__ void nd_reduce(v4d& re, v4d& im, double (*red)[2][4][
     }
 }
 
+// Workgroup b runs on XCD b % 8: an XCD takes a contiguous range of a level's
+// tiles (neighbouring fronts, which read the same rows), and the column
+// blocks of a tile one after another (they read the same part of the factor).
+__device__ __forceinline__ bool nd_place(int rows, int nct, int& row, int& col) {
+    const int b = blockIdx.x, k = b >> 3, per = (rows + 7) >> 3;
+    row = (b & 7) * per + k / nct;
+    col = k % nct;
+    return row < rows && row < ((b & 7) + 1) * per;
+}
+
 template <int RT>
-__global__ __launch_bounds__(256, 4) void k_nd_forward(NdTabs t, int first, int row0, int parity,
+__global__ __launch_bounds__(256, 4) void k_nd_forward(NdTabs t, int first, int row0, int rows, int nct, int parity,
                                                     const NdJobTab* __restrict__ jtab) {
     constexpr int KS = 4 / RT, CH = RT == 4 ? 32 : 64;   // staged rows
     __shared__ double2 sy[2][CH][16];
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lr = l & 15, lg = l >> 4;
-    const NdJob d = nd_record(jtab->j, blockIdx.z);
-    const int c0 = 16 * blockIdx.y, S = d.S;
+    int e0, cb;
+    if (!nd_place(rows, nct, e0, cb)) return;
+    const NdJob d = nd_record(jtab->j, blockIdx.y);
+    const int c0 = 16 * cb, S = d.S;
     if (c0 >= S) return;
-    const NdTile tl = nd_record(t.tiles, row0 + (int)blockIdx.x);
+    const NdTile tl = nd_record(t.tiles, row0 + e0);
     const NdFront f = nd_record(t.fronts, first + tl.front);
     const int c16 = min(c0 + lr, S - 1);
     const bool on = c0 + lr < S;
@@ -1453,13 +1472,15 @@ __global__ __launch_bounds__(256, 4) void k_nd_forward(NdTabs t, int first, int 
 // them in LDS for several tiles was slower at every level (401^2, 64 columns,
 // 5 systems: levels of 19 to 80 us against 28 to 90 us).
 template <bool SPLIT>
-__global__ __launch_bounds__(256) void k_nd_backward(NdTabs t, int first, int row0, int rows,
+__global__ __launch_bounds__(256) void k_nd_backward(NdTabs t, int first, int row0, int rows, int nct,
                                                      const NdJobTab* __restrict__ jtab) {
     __shared__ double red[SPLIT ? 3 : 1][2][4][64];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
-    const int e0 = SPLIT ? (int)blockIdx.x : 4 * (int)blockIdx.x + w;
-    const NdJob d = nd_record(jtab->j, blockIdx.z);
-    const int c0 = 16 * blockIdx.y, S = d.S;
+    int e0, cb;
+    if (!nd_place(SPLIT ? rows : (rows + 3) >> 2, nct, e0, cb)) return;
+    if (!SPLIT) e0 = 4 * e0 + w;
+    const NdJob d = nd_record(jtab->j, blockIdx.y);
+    const int c0 = 16 * cb, S = d.S;
     if (c0 >= S || e0 >= rows) return;
     const NdTile tl = nd_record(t.tiles, row0 + e0);
     const NdFront f = nd_record(t.fronts, first + tl.front);
@@ -1594,19 +1615,21 @@ void launch_nd_sub_backward(const NdTabs& t, const NdPlan& p, const NdJobTab* dj
 }
 
 void launch_nd_forward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st) {
-    const dim3 grid(lv.frows, (smax + 15) / 16, n);
-#define HELM_ND(RT) hipLaunchKernelGGL(k_nd_forward<RT>, grid, dim3(256), 0, st, t, lv.first, lv.frow0, lv.parity, djobs)
+    const int nct = (smax + 15) / 16;
+    const dim3 grid(8 * ((lv.frows + 7) / 8) * nct, n);
+#define HELM_ND(RT) hipLaunchKernelGGL(k_nd_forward<RT>, grid, dim3(256), 0, st, t, lv.first, lv.frow0, lv.frows, nct, lv.parity, djobs)
     if (lv.frt == 4) HELM_ND(4);
     else HELM_ND(1);
 #undef HELM_ND
 }
 void launch_nd_backward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st) {
+    const int nct = (smax + 15) / 16;
     if (lv.fmax > 96)
-        hipLaunchKernelGGL(k_nd_backward<true>, dim3(lv.brows, (smax + 15) / 16, n), dim3(256), 0, st, t, lv.first,
-                           lv.brow0, lv.brows, djobs);
+        hipLaunchKernelGGL(k_nd_backward<true>, dim3(8 * ((lv.brows + 7) / 8) * nct, n), dim3(256), 0, st, t, lv.first,
+                           lv.brow0, lv.brows, nct, djobs);
     else
-        hipLaunchKernelGGL(k_nd_backward<false>, dim3((lv.brows + 3) / 4, (smax + 15) / 16, n), dim3(256), 0, st, t,
-                           lv.first, lv.brow0, lv.brows, djobs);
+        hipLaunchKernelGGL(k_nd_backward<false>, dim3(8 * (((lv.brows + 3) / 4 + 7) / 8) * nct, n), dim3(256), 0, st, t,
+                           lv.first, lv.brow0, lv.brows, nct, djobs);
 }
 
 }  // namespace helm

@@ -205,7 +205,7 @@ NdShape make_shape(int leaf, int w, int h, int mask, std::vector<int>& tabs) {
     for (int j = 0; j < h; ++j)
         for (int i = 0; i < w; ++i) {
             const int z = zrow[at(i, j)];
-            boxt[(size_t)j * w + i] = (z >= 0 ? z : S.nsep + S.nring + wrow[at(i, j)]) | i << 12 | j << 22;
+            boxt[(size_t)j * w + i] = (z >= 0 ? z : S.nsep + S.nring + wrow[at(i, j)]);
         }
     auto stencil = [&](const std::vector<int>& vi, const std::vector<int>& vj, const std::vector<int>& row) {
         std::vector<short> t;
@@ -320,6 +320,10 @@ bool nd_build(int nx, int nz, NdPlan* plan) {
             P.sub_tab = std::max(P.sub_tab, S.ntab);
             if (S.nleaf > ND_SUB_LEAVES) return false;
         }
+        s.w = w;
+        s.h = h;
+        s.nsep = P.shapes[s.shape].nsep;
+        s.nring = P.shapes[s.shape].nring;
         for (int r = 0; r < b.size; ++r) {   // its boxes in the shape's order
             P.fronts[id[q + r]].fac = P.fac_elems;
             P.fac_elems += box_elems(box[q + r], 0, nx, 0, nz);
