@@ -238,24 +238,21 @@ __global__ __launch_bounds__(64, 2) void k_nd_leaf(NdTabs t, int first, const Nd
         int K = -1;
         for (uint32_t cand = y.pivot ? 0u : left; cand; cand &= cand - 1) {
             const int c = __builtin_ctz(cand);
+            double2 q[4];   // the tile is symmetric: its columns are its rows
 #pragma unroll
             for (int j = 0, i = 0; j < LT; ++j)
 #pragma unroll
                 for (int ii = 0; ii <= j; ++ii, ++i)
                     if (ii == j && j == c) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) sC[16 * c + lg + 4 * e][lr] = make_double2(re[i][e], im[i][e]);
+                        for (int e = 0; e < 4; ++e) q[e] = make_double2(re[i][e], im[i][e]);
                     }
-            __syncthreads();
-            double2 q[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) q[e] = sC[16 * c + lr][4 * lg + e];
             const float thr = TAU2 * __uint_as_float(wave_max_u32(__float_as_uint(nd_max2(q))));
             bool small = false;
             gj16_wave<double>(q, thr, small);
             if (!small) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sW[16 * c + lr][4 * lg + e] = q[e];
+                for (int e = 0; e < 4; ++e) sW[16 * c + lg + 4 * e][lr] = q[e];
                 nd_grown(y, nd_max2(q), true);
                 K = c;
                 break;

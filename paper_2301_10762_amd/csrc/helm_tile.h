@@ -61,19 +61,21 @@ __device__ __forceinline__ typename CT<T>::c swz_row_c(typename CT<T>::c v, int 
     return r;
 }
 
-// 1 / p for complex p, reciprocal of |p|^2 refined by Newton steps
-__device__ __forceinline__ double2 crcp(double2 p) {
-    const double n = p.x * p.x + p.y * p.y;
+// 1 / n, refined by Newton steps
+__device__ __forceinline__ double rcp_refined(double n) {
     double y = __builtin_amdgcn_rcp(n);
     y = y * (2.0 - n * y);
-    y = y * (2.0 - n * y);
-    return make_double2(p.x * y, -p.y * y);
+    return y * (2.0 - n * y);
 }
-__device__ __forceinline__ float2 crcp(float2 p) {
-    const float n = p.x * p.x + p.y * p.y;
-    float y = __builtin_amdgcn_rcpf(n);
-    y = y * (2.0f - n * y);
-    return make_float2(p.x * y, -p.y * y);
+__device__ __forceinline__ float rcp_refined(float n) {
+    const float y = __builtin_amdgcn_rcpf(n);
+    return y * (2.0f - n * y);
+}
+// 1 / p for complex p
+template <typename C>
+__device__ __forceinline__ C crcp(C p) {
+    const auto y = rcp_refined(p.x * p.x + p.y * p.y);
+    return mk<C>(p.x * y, -p.y * y);
 }
 
 template <typename T>
@@ -171,15 +173,17 @@ struct RowScratch {
 
 // ------------------------------------------------ blocked unpivoted inverse --
 // The diagonal tile [[A, B], [C, D]] (16 x 16 quadrants) is inverted as
-//     A^-1,  X = A^-1 B,  Y = C A^-1,  S = D - Y B,  S^-1,
+//     A^-1,  X = A^-1 B,  Y = C A^-1,  S = D - C X,  S^-1,
 //     T12 = -X S^-1,  T21 = -S^-1 Y,  T22 = S^-1,  T11 = A^-1 - X T21,
 // which is unpivoted Gauss-Jordan on the whole tile with its pivots taken in
 // the same order (those of A, then those of S), so the small-pivot test is
-// the same one.  The two 16 x 16 inverses are done by one wavefront each in
-// registers (lane l holds row l % 16, columns 4 (l / 16) .. +3), exchanging
-// the pivot row and column by cross-lane reads, with no barrier; the six
-// 16 x 16 products run on the matrix cores from LDS.
-
+// the same one.  This is a serial chain and bounds a panel step, so it stays
+// in one wavefront's registers as far as it goes: lane l = 16 g + r holds row
+// r and columns acc_row(g, e) of A, which after the inversion is the first
+// operand of the matrix-core product X = A^-1 B; X comes out as the second
+// operand of C X; and S comes out as the rows of S^T, whose inverse is
+// (S^-1)^T, again an operand.  A second wavefront forms Y beside it and T21,
+// T11 after it.
 template <typename C> __device__ __forceinline__ C lane_read(C v, int lane);
 template <> __device__ __forceinline__ float2 lane_read(float2 v, int lane) {
     float2 r;
@@ -210,97 +214,122 @@ template <> __device__ __forceinline__ double2 lane_bcast(double2 v, int lane) {
 }
 
 // the value of lane P of each row of 16 lanes, in every lane of that row
-// (DPP row broadcast; P compile-time)
-template <int P> __device__ __forceinline__ int row_bcast_i(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, 0x150 + P, 0xF, 0xF, false);
+// (DPP row broadcast, complex128 halves whole; P compile-time)
+template <int P> __device__ __forceinline__ float row_bcast_p(float v) {
+    return __builtin_amdgcn_update_dpp(v, v, 0x150 + P, 0xF, 0xF, true);
 }
-template <int P> __device__ __forceinline__ float2 row_bcast(float2 v) {
-    return make_float2(__int_as_float(row_bcast_i<P>(__float_as_int(v.x))),
-                       __int_as_float(row_bcast_i<P>(__float_as_int(v.y))));
+template <int P> __device__ __forceinline__ double row_bcast_p(double v) {
+    return __builtin_amdgcn_update_dpp(v, v, 0x150 + P, 0xF, 0xF, true);
 }
-template <int P> __device__ __forceinline__ double2 row_bcast(double2 v) {
-    return make_double2(__hiloint2double(row_bcast_i<P>(__double2hiint(v.x)), row_bcast_i<P>(__double2loint(v.x))),
-                        __hiloint2double(row_bcast_i<P>(__double2hiint(v.y)), row_bcast_i<P>(__double2loint(v.y))));
+template <int P, typename C> __device__ __forceinline__ C row_bcast(C v) {
+    return mk<C>(row_bcast_p<P>(v.x), row_bcast_p<P>(v.y));
 }
 
-// One pivot of gj16_wave (below).
+// One pivot of gj16_wave (below): piv is a_pp and y = 1 / |a_pp|^2 on entry,
+// those of the next pivot on return.
 template <typename T, int P>
-__device__ __forceinline__ void gj16_pivot(typename CT<T>::c (&a)[4], float thr, bool& small, int r, int g) {
+__device__ __forceinline__ void gj16_pivot(typename CT<T>::c (&a)[4], typename CT<T>::c& piv, T& y, float thr,
+                                           bool& small, int r, int g) {
     using C = typename CT<T>::c;
-    constexpr int GP = P >> 2, EP = P & 3;
-    const C f0 = lane_read(a[EP], r + 16 * GP);            // a[r][p], from another row of lanes
+    // place of column P and P + 1: lane group, entry
+    constexpr bool F64 = sizeof(T) == 8;
+    constexpr int GP = F64 ? P & 3 : P >> 2, EP = F64 ? P >> 2 : P & 3;
+    constexpr int N = P + 1, GN = F64 ? N & 3 : N >> 2, EN = F64 ? (N >> 2) & 3 : N & 3;
+    C f = lane_read(a[EP], r + 16 * GP);                   // a[r][p], from another row of lanes
     C pr[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) pr[e] = row_bcast<P>(a[e]);   // a[p][4g + e], lane p of this row of lanes
-    const C piv = lane_bcast(a[EP], P + 16 * GP);          // a[p][p]
-    if (!((float)(piv.x * piv.x + piv.y * piv.y) >= thr)) small = true;
-    const C dv = crcp(piv);
-    C f = f0;
+    for (int e = 0; e < 4; ++e) pr[e] = row_bcast<P>(a[e]);   // a[p][..], lane p of this row of lanes
     if (r == P) f.x -= (T)1;
-    const C fs = cmul(f, dv);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    // (f / a_pp) from f conj(a_pp), which does not wait for the reciprocal
+    const C fs = mk<C>((f.x * piv.x + f.y * piv.y) * y, (f.y * piv.x - f.x * piv.y) * y);
+    auto update = [&](int e) {
         const C up = mk<C>(fma(-fs.x, pr[e].x, fma(fs.y, pr[e].y, a[e].x)),
                            fma(-fs.x, pr[e].y, fma(-fs.y, pr[e].x, a[e].y)));
         if (e == EP) a[e] = HELM_CSEL(g == GP, mk<C>((r == P ? (T)1 : (T)0) - fs.x, -fs.y), up);
         else a[e] = up;
+    };
+    // the next pivot's entry first: its reciprocal is the serial part
+    update(EN);
+    if (P < 15) {
+        piv = lane_bcast(a[EN], N + 16 * GN);
+        const T n = piv.x * piv.x + piv.y * piv.y;
+        if (!((float)n >= thr)) small = true;
+        y = rcp_refined(n);
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (e != EN) update(e);
 }
 
-// Unpivoted Gauss-Jordan of a 16 x 16 tile held by one wavefront (layout
-// above), in a uniform form with no special case for the pivot row: for
-// pivot p, with f = (column p) - e_p and d = 1 / a_pp, every entry off
-// column p takes a_ij -= (f_i d) a_pj, and column p becomes e_p - f d, which
-// leaves the inverse in place.  Every lane reads the old pivot row at its columns and
-// its row's entry of column p from the lanes that hold them (the row by a
-// DPP broadcast within each row of 16 lanes, the column entry by a
-// cross-lane read).  Sets small if |a_pp|^2 < thr for some pivot.
+// Unpivoted Gauss-Jordan of a 16 x 16 tile held by one wavefront (lane
+// 16 g + r: row r, columns acc_row(g, e)), in a uniform form with no special
+// case for the pivot row: for pivot p, with f = (column p) - e_p and
+// d = 1 / a_pp, every entry off column p takes a_ij -= (f_i d) a_pj, and
+// column p becomes e_p - f d, which leaves the inverse in place.  Every lane
+// reads the old pivot row at its columns and its row's entry of column p from
+// the lanes that hold them (the row by a DPP broadcast within each row of 16
+// lanes, the column entry by a cross-lane read).  Sets small if
+// |a_pp|^2 < thr for some pivot.
 template <typename T>
 __device__ __forceinline__ void gj16_wave(typename CT<T>::c (&a)[4], float thr, bool& small) {
+    using C = typename CT<T>::c;
     const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
-    gj16_pivot<T, 0>(a, thr, small, r, g);
-    gj16_pivot<T, 1>(a, thr, small, r, g);
-    gj16_pivot<T, 2>(a, thr, small, r, g);
-    gj16_pivot<T, 3>(a, thr, small, r, g);
-    gj16_pivot<T, 4>(a, thr, small, r, g);
-    gj16_pivot<T, 5>(a, thr, small, r, g);
-    gj16_pivot<T, 6>(a, thr, small, r, g);
-    gj16_pivot<T, 7>(a, thr, small, r, g);
-    gj16_pivot<T, 8>(a, thr, small, r, g);
-    gj16_pivot<T, 9>(a, thr, small, r, g);
-    gj16_pivot<T, 10>(a, thr, small, r, g);
-    gj16_pivot<T, 11>(a, thr, small, r, g);
-    gj16_pivot<T, 12>(a, thr, small, r, g);
-    gj16_pivot<T, 13>(a, thr, small, r, g);
-    gj16_pivot<T, 14>(a, thr, small, r, g);
-    gj16_pivot<T, 15>(a, thr, small, r, g);
+    C piv = lane_bcast(a[0], 0);
+    const T n = piv.x * piv.x + piv.y * piv.y;
+    if (!((float)n >= thr)) small = true;
+    T y = rcp_refined(n);
+    gj16_pivot<T, 0>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 1>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 2>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 3>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 4>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 5>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 6>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 7>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 8>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 9>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 10>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 11>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 12>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 13>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 14>(a, piv, y, thr, small, r, g);
+    gj16_pivot<T, 15>(a, piv, y, thr, small, r, g);
 }
 
-// D = Cadd + sign * A B for 16 x 16 complex blocks in LDS (row stride 33),
-// by one wavefront on the matrix cores; Cadd may be null.  D may alias Cadd
-// (each lane reads its own entries of Cadd before writing them) but not A
-// or B.
+// One wavefront's part of a 16 x 16 complex product on the matrix cores:
+// d = c0 + sign A B, with A read by rows from LDS (stride 33) or from
+// registers (a[e] = A[lr][acc_row(lg, e)]), B from LDS or from registers
+// (b[e] = B[acc_row(lg, e)][lr]); results as b is.
 template <typename T>
-__device__ __forceinline__ void mm16(const typename CT<T>::c* A, const typename CT<T>::c* B,
-                                     const typename CT<T>::c* Cadd, typename CT<T>::c* D, T sign) {
+__device__ __forceinline__ void row_ops(const typename CT<T>::c* A, typename CT<T>::c (&a)[4]) {
+    const int l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] = A[lr * 33 + acc_row<T>(lg, e)];
+}
+template <typename T>
+__device__ __forceinline__ void col_ops(const typename CT<T>::c* B, typename CT<T>::c (&b)[4]) {
+    const int l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = B[acc_row<T>(lg, e) * 33 + lr];
+}
+template <typename T>
+__device__ __forceinline__ void col_put(typename CT<T>::c* D, const typename CT<T>::c (&d)[4]) {
+    const int l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) D[acc_row<T>(lg, e) * 33 + lr] = d[e];
+}
+template <typename T>
+__device__ __forceinline__ void mm16(const typename CT<T>::c (&a)[4], const typename CT<T>::c (&b)[4],
+                                     const typename CT<T>::c (&c0)[4], T sign, typename CT<T>::c (&d)[4]) {
     using C = typename CT<T>::c;
     using V = typename CT<T>::v4;
-    const int l = threadIdx.x & 63, lr = l & 15, lg = l >> 4;
     V re, im;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { re[e] = 0; im[e] = 0; }
+    for (int e = 0; e < 4; ++e) { re[e] = c0[e].x; im[e] = c0[e].y; }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const C x = A[lr * 33 + 4 * q + lg], y = B[(4 * q + lg) * 33 + lr];
-        cmfma<T, V>(re, im, x.x, x.y, y.x, y.y);
-    }
+    for (int e = 0; e < 4; ++e) cmfma<T, V>(re, im, sign * a[e].x, sign * a[e].y, b[e].x, b[e].y);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int row = acc_row<T>(lg, e);
-        C v = mk<C>(sign * re[e], sign * im[e]);
-        if (Cadd) v = cadd(Cadd[row * 33 + lr], v);
-        D[row * 33 + lr] = v;
-    }
+    for (int e = 0; e < 4; ++e) d[e] = mk<C>(re[e], im[e]);
 }
 
 // The unpivoted inverse of the kb x kb tile in a[] (256-thread layout of the
@@ -342,39 +371,55 @@ __device__ __forceinline__ bool inv_blocked_core(int kb, typename CT<T>::c* L2, 
     using C = typename CT<T>::c;
     const int t = threadIdx.x, w = t >> 6, l = t & 63;
     C* L = L2;               // the tile, then its inverse
-    C* Lb = L2 + 32 * 33;    // X (rows 0..15) and Y (rows 16..31)
+    C* Lb = L2 + 32 * 33;    // X
     const float thr = tau2 * fmaxf(fmaxf(sh.amax[0], sh.amax[1]), fmaxf(sh.amax[2], sh.amax[3]));
-    const int lr = l & 15, lg = l >> 4;
     bool small = false;
-    // A^-1 in place (wave 0)
-    if (w == 0) {
-        C q[4];
+    C* B = L + 16;
+    C* Cq = L + 16 * 33;
+    C* D = Cq + 16;
+    C q[4], x[4], o[4], d[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) q[e] = L[lr * 33 + 4 * lg + e];
+    for (int e = 0; e < 4; ++e) o[e] = mk<C>(0, 0);
+    if (w == 0) {   // A^-1, kept as rows
+        const int lr = l & 15, lg = l >> 4;
+        row_ops<T>(L, q);
         gj16_wave<T>(q, thr, small);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) L[lr * 33 + 4 * lg + e] = q[e];
+        for (int e = 0; e < 4; ++e) L[lr * 33 + acc_row<T>(lg, e)] = q[e];
     }
     if (kb == 32) {
         __syncthreads();
-        if (w == 0) mm16<T>(L, L + 16, nullptr, Lb, (T)1);                          // X = A^-1 B
-        else if (w == 1) mm16<T>(L + 16 * 33, L, nullptr, Lb + 16 * 33, (T)1);       // Y = C A^-1
-        __syncthreads();
-        if (w == 0) mm16<T>(Lb + 16 * 33, L + 16, L + 16 * 33 + 16, L + 16 * 33 + 16, (T)-1);   // S = D - Y B
-        __syncthreads();
         if (w == 0) {
-            C q[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) q[e] = L[(16 + lr) * 33 + 16 + 4 * lg + e];
-            gj16_wave<T>(q, thr, small);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) L[(16 + lr) * 33 + 16 + 4 * lg + e] = q[e];
+            C b[4], c[4];
+            col_ops<T>(B, b);
+            row_ops<T>(Cq, c);
+            col_ops<T>(D, d);
+            mm16<T>(q, b, o, (T)1, x);      // X = A^-1 B
+            mm16<T>(c, x, d, (T)-1, d);     // S = D - C X: the rows of S^T
+            col_put<T>(Lb, x);
+            gj16_wave<T>(d, thr, small);    // the rows of (S^-1)^T
+            col_put<T>(D, d);
+        } else if (w == 1) {
+            C c[4], b[4];
+            row_ops<T>(Cq, c);
+            col_ops<T>(L, b);
+            mm16<T>(c, b, o, (T)1, x);      // Y = C A^-1
         }
         __syncthreads();
-        if (w == 0) mm16<T>(Lb, L + 16 * 33 + 16, nullptr, L + 16, (T)-1);              // T12 = -X S^-1
-        else if (w == 1) mm16<T>(L + 16 * 33 + 16, Lb + 16 * 33, nullptr, L + 16 * 33, (T)-1);   // T21 = -S^-1 Y
-        __syncthreads();
-        if (w == 0) mm16<T>(Lb, L + 16 * 33, L, L, (T)-1);                              // T11 = A^-1 - X T21
+        if (w == 0) {
+            row_ops<T>(Lb, q);
+            mm16<T>(q, d, o, (T)-1, x);     // T12 = -X S^-1
+            col_put<T>(B, x);
+        } else if (w == 1) {
+            C a[4];
+            row_ops<T>(D, a);
+            mm16<T>(a, x, o, (T)-1, q);     // T21 = -S^-1 Y
+            col_put<T>(Cq, q);
+            row_ops<T>(Lb, a);
+            col_ops<T>(L, d);
+            mm16<T>(a, q, d, (T)-1, x);     // T11 = A^-1 - X T21
+            col_put<T>(L, x);
+        }
     }
     if (small) sh.small = 1;
     __syncthreads();
