@@ -1093,9 +1093,11 @@ int nd_solve_jobs(std::vector<SolveJob*>& jobs, bool adjoint, double tol, hipStr
             for (size_t q = 0; q < act.size(); ++q) {
                 const int c = act[q];
                 rels[c] = rel[q];
-                // one correction too where a box near resonance cost digits:
-                // the plain solve is otherwise far below any tolerance used
-                const bool more = !(rel[q] <= tol) || (iters[c] == 0 && rel[q] > 0.01 * tol);
+                // a correction too where a box near resonance cost digits (a
+                // plain solve is otherwise far below any tolerance used); a
+                // refined solve, whose tolerance is its accuracy, keeps one
+                // digit in reserve, one in FP64 two
+                const bool more = !(rel[q] <= tol) || (iters[c] == 0 && rel[q] > (refined ? 0.1 : 0.01) * tol);
                 if (more && iters[c] < MAX_IR) next.push_back(c);
             }
             act = next;
