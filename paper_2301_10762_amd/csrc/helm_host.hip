@@ -787,6 +787,31 @@ int sweep_group(helm_factor_s* const* fs, int n, const void* const* Ys, const in
                 const int64_t* ldx, const int* Ss, bool conj_b, hipStream_t st) {
     const bool fp32 = fs[0]->prec == HELM_FP32_IR;
     const size_t es = elem_bytes(fs[0]->prec);
+    // narrow systems by themselves: which way a system is swept (and so the
+    // order of its sums) does not depend on what else is in the group
+    const int narrow = (int)std::count_if(fs, fs + n, [](const helm_factor_s* f) { return f->np <= SWC_NP; });
+    if (narrow > 0 && narrow < n) {
+        for (int kind = 0; kind < 2; ++kind) {
+            std::vector<helm_factor_s*> f2;
+            std::vector<const void*> y2;
+            std::vector<void*> x2;
+            std::vector<int64_t> ly, lx;
+            std::vector<int> s2;
+            for (int c = 0; c < n; ++c)
+                if ((fs[c]->np <= SWC_NP) == (kind == 0)) {
+                    f2.push_back(fs[c]);
+                    y2.push_back(Ys[c]);
+                    x2.push_back(Xs[c]);
+                    ly.push_back(ldy[c]);
+                    lx.push_back(ldx[c]);
+                    s2.push_back(Ss[c]);
+                }
+            if (int rc = sweep_group(f2.data(), (int)f2.size(), y2.data(), ly.data(), x2.data(), lx.data(), s2.data(),
+                                     conj_b, st))
+                return rc;
+        }
+        return HELM_OK;
+    }
     Scratch sc(st);
     SweepTab stab;
     std::memset(&stab, 0, sizeof(stab));
@@ -844,6 +869,8 @@ int sweep_group(helm_factor_s* const* fs, int n, const void* const* Ys, const in
                 t.Bm = si.Mout;
                 // the bottom front's first backward step reads buffer nfwd & 1
                 t.Zp = (si.nfwd & 1) ? si.Y1 : si.Y0;
+                // narrow fronts: the top front's E w_{k-1}
+                if (narrow) si.Zp = t.Y0;
             }
             si.tiles_s = sweep_col_tiles(Ss[c]);
             si.tile0 = groups;
@@ -857,6 +884,17 @@ int sweep_group(helm_factor_s* const* fs, int n, const void* const* Ys, const in
         g_solves += Ss[c];
     }
     launch_put_sweep_table(stab, dtab, st);
+    if (narrow) {
+        int np_max = 16;
+        for (int c = 0; c < nf; ++c) np_max = std::max(np_max, tab[c].np);
+        KernelTimer::Pair p;
+        const bool tm = g_timer.begin(2, st, &p);
+        launch_sweep_chain(dtab, nf, st_max, np_max, fp32, conj_b, st);
+        if (tm) g_timer.end(p, 2, st);
+        g_launches += 3;
+        HIPCHECK(hipGetLastError());
+        return HELM_OK;
+    }
     launch_sweep_init(dtab, nf, itot, fp32, conj_b, st);
     const int uni = sweep_uniform(stab, nf);
     int np_max = 16;

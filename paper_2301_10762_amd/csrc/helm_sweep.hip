@@ -269,6 +269,205 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep(int n, int tstep, int g
     }
 }
 
+// ------------------------------------------------------------ narrow grids --
+// Fronts of at most SWC_NP nodes a row: a step's product is smaller than a
+// launch (np = 80 in complex64: 2 us of work in a launch of 3.6 us), so one
+// workgroup takes a front and 16 columns through all its rows, with the
+// coupling vector in LDS and the next row's factor block and vectors on
+// their way while this row is multiplied.  The fronts meet between two
+// launches: the first goes forward to row k, the second starts with row k in
+// both fronts' workgroups (each needs x_k) and goes back.  Wider blocks keep
+// a launch per step, whose row tiles then fill more compute units.
+// A front's row tiles times ks parts of the contraction are one wavefront
+// each; the parts are summed in order.
+constexpr int SWC_W = 16, SWC_T = 64 * SWC_W;
+constexpr int SWC_E = SWC_NP * 16 / SWC_T + (SWC_NP * 16 % SWC_T != 0);   // vector entries per thread
+
+template <typename T, bool FWD, bool CONJB, int CN>
+__global__ __launch_bounds__(SWC_T) void k_sweep_chain(const SweepTab* __restrict__ tab) {
+    using C = typename CT<T>::c;
+    using V = typename CT<T>::v4;
+    extern __shared__ __attribute__((aligned(16))) char chain_smem[];
+    C (*red)[16][17] = (C(*)[16][17])chain_smem;          // [wavefront]
+    C (*sy)[17] = (C(*)[17])(red + SWC_W);                // the coupling vector
+    const SweepInfo d = load_entry(tab->c, blockIdx.y);
+    const int S = d.S, s0 = 16 * blockIdx.x, np = d.np, nx = d.nx;
+    if (s0 >= S) return;
+    const bool bottom = d.Mout != nullptr;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lr = l & 15, lg = l >> 4;
+    // rows: forward all of a bottom front's, a top front's but row k;
+    // backward row k, then the front's from there
+    const int kk = d.row0 + d.dir * (bottom ? d.nfwd : d.nfwd - 1);
+    const int steps = FWD ? (bottom ? d.nfwd : d.nfwd - 1) : d.nbwd + 1;
+    auto row = [&](int t) { return FWD ? d.row0 + d.dir * t : t == 0 ? kk : d.brow0 - d.dir * (t - 1); };
+    // this thread's entries of the vectors: row i, column c (rows along the
+    // right-hand sides)
+    int ei[SWC_E], ec[SWC_E];
+    bool own[SWC_E], in[SWC_E];
+#pragma unroll
+    for (int e = 0; e < SWC_E; ++e) {
+        const int q = tid + SWC_T * e;
+        own[e] = q < 16 * np;
+        ec[e] = own[e] ? q / np : 0;
+        ei[e] = own[e] ? q - ec[e] * np : 0;
+        in[e] = own[e] && ei[e] < nx && s0 + ec[e] < S;
+    }
+    const C zero = mk<C>(0.0, 0.0);
+    const C* Bv = (const C*)d.B;
+    C* X = (C*)d.X;
+    // forward: the right-hand side of row j + dir; backward: w of row j
+    auto fetch = [&](C (&v)[SWC_E], const C* src, int64_t ld, int j) {
+#pragma unroll
+        for (int e = 0; e < SWC_E; ++e)
+            v[e] = gld(src + (size_t)min(s0 + ec[e], S - 1) * ld + (size_t)j * nx + min(ei[e], nx - 1));
+    };
+    // this wavefront's part of a product
+    const int rt = np >> 4, ks = rt <= 4 ? 4 : 2, it = w / ks, part = w - it * ks;
+    const int cb = part * rt / ks, ce = it < rt ? (part + 1) * rt / ks : cb;
+    C g[CN][4];
+    auto gload = [&](int c, int j) {
+        if (it >= rt) return;
+        const int cc = min(cb + c, max(ce - 1, 0));
+        const C* G = (const C*)d.G + (size_t)j * np * np + (size_t)it * (np >> 2) * 64;
+        if constexpr (sizeof(T) == 4) {
+            typedef float gv4f __attribute__((ext_vector_type(4)));
+            const HELM_GLOBAL gv4f* p = (const HELM_GLOBAL gv4f*)(G + 4 * l + (size_t)cc * 256);
+            const gv4f a = p[0], b = p[1];
+            g[c][0] = mk<C>(a.x, a.y);
+            g[c][1] = mk<C>(a.z, a.w);
+            g[c][2] = mk<C>(b.x, b.y);
+            g[c][3] = mk<C>(b.z, b.w);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) g[c][q] = gld(G + l + (size_t)(4 * cc + q) * 64);
+        }
+    };
+    C pre[SWC_E];
+    if (FWD) {
+        if (steps == 0) return;
+        fetch(pre, Bv, d.ldb, d.row0);
+#pragma unroll
+        for (int e = 0; e < SWC_E; ++e)
+            if (own[e]) sy[ei[e]][ec[e]] = in[e] ? conj_if(pre[e], CONJB) : zero;
+    } else {
+        // y_k: what the bottom front left (or b_k, read and conjugated by the
+        // forward launch's type), less the top front's E w_{k-1}
+        const C* M = (const C*)(bottom ? d.Mout : d.Bm);
+        const C* top = (const C*)(bottom ? d.Zp : d.Y0);
+        fetch(pre, Bv, d.ldb, kk);
+#pragma unroll
+        for (int e = 0; e < SWC_E; ++e) {
+            const size_t at = bt<T>(ei[e], s0 + ec[e], np);
+            C v = M ? gld(M + at) : conj_if(pre[e], CONJB);
+            if (kk > 0) {
+                const C q = gld(top + at);
+                v = mk<C>(v.x - q.x, v.y - q.y);
+            }
+            if (own[e]) sy[ei[e]][ec[e]] = in[e] ? v : zero;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CN; ++c) gload(c, row(0));
+    if (FWD) fetch(pre, Bv, d.ldb, min(max(row(0) + d.dir, 0), d.nz - 1));
+    __syncthreads();
+    // one row: cur holds its vectors, ahead takes the next row's (two sets in
+    // turn: a copy between them would wait for the loads)
+    auto step = [&](int t, C (&cur)[SWC_E], C (&ahead)[SWC_E]) {
+        const int j = row(t), jn = row(min(t + 1, steps - 1));
+        V p1, p2, p3;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { p1[e] = 0; p2[e] = 0; p3[e] = 0; }
+#pragma unroll
+        for (int c = 0; c < CN; ++c) {
+            if (cb + c < ce) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const C y = sy[16 * (cb + c) + 4 * q + lg][lr];
+                    cmfma3<T, V>(p1, p2, p3, g[c][q].x, g[c][q].y, y.x, y.y);
+                }
+            }
+            // this row's vectors are waited for here, where only older loads
+            // are in flight, not behind the next row's
+            if (c == 0) {
+#pragma unroll
+                for (int e = 0; e < SWC_E; ++e) asm volatile("" : "+v"(cur[e].x), "+v"(cur[e].y));
+            }
+            gload(c, jn);
+        }
+        if (it < rt) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                red[w][acc_row<T>(lg, e)][lr] = mk<C>(p1[e] - p2[e], p3[e] - p1[e] - p2[e]);
+        }
+        // what the next step needs beside its factor block
+        if (FWD) fetch(ahead, Bv, d.ldb, min(max(jn + d.dir, 0), d.nz - 1));
+        else fetch(ahead, X, d.ldx, jn);
+        __syncthreads();
+        const bool last = t + 1 == steps;
+#pragma unroll
+        for (int e = 0; e < SWC_E; ++e) {
+            if (!own[e]) continue;
+            const int i = ei[e], r = i & 15, wv = (i >> 4) * ks;
+            C part_q[4];   // all read before the first is added
+#pragma unroll
+            for (int q = 0; q < 4; ++q) part_q[q] = red[wv + min(q, ks - 1)][r][ec[e]];
+            C sum = cadd(part_q[0], part_q[1]);
+            if (ks == 4) sum = cadd(cadd(sum, part_q[2]), part_q[3]);
+            const T sr = sum.x, si = sum.y;
+            const T cz = (T)(i >= nx ? 0.0 : ((i == 0 || i == nx - 1) ? -0.5 * d.cz : -d.cz));
+            C* xo = X + (size_t)(s0 + ec[e]) * d.ldx + (size_t)j * nx + i;
+            C nxt = zero;
+            if (FWD) {
+                const C bn = conj_if(cur[e], CONJB);
+                if (in[e]) {
+                    gst(xo, mk<C>(sr, si));
+                    nxt = last && !bottom ? mk<C>(cz * sr, cz * si) : mk<C>(bn.x - cz * sr, bn.y - cz * si);
+                }
+                if (last) gst((C*)(bottom ? d.Mout : d.Y0) + bt<T>(i, s0 + ec[e], np), nxt);
+            } else if (in[e]) {
+                const C xn = t == 0 ? mk<C>(sr, si) : mk<C>(cur[e].x - sr, cur[e].y - si);
+                if (t > 0 || !bottom) gst(xo, xn);
+                nxt = mk<C>(cz * xn.x, cz * xn.y);
+            }
+            sy[i][ec[e]] = nxt;
+        }
+        __syncthreads();
+    };
+    C other[SWC_E];
+    for (int t = 0; t < steps; t += 2) {
+        step(t, pre, other);
+        if (t + 1 < steps) step(t + 1, other, pre);
+    }
+}
+
+template <typename T, int CN>
+static void launch_sweep_chain_t(const SweepTab* dtab, int nf, int nct, int np_max, bool conj_b, hipStream_t st) {
+    using C = typename CT<T>::c;
+    const size_t lds = sizeof(C) * 17 * (16 * SWC_W + (size_t)np_max);
+    const dim3 grid(nct, nf), block(SWC_T);
+    auto go = [&](auto kernel) {
+        if (lds > 65536)
+            (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(kernel, grid, block, lds, st, dtab);
+    };
+    if (conj_b) {
+        go(k_sweep_chain<T, true, true, CN>);
+        go(k_sweep_chain<T, false, true, CN>);
+    } else {
+        go(k_sweep_chain<T, true, false, CN>);
+        go(k_sweep_chain<T, false, false, CN>);
+    }
+}
+void launch_sweep_chain(const SweepTab* dtab, int nf, int nct, int np_max, bool fp32, bool conj_b, hipStream_t st) {
+    if (np_max <= 64) {
+        if (fp32) launch_sweep_chain_t<float, 1>(dtab, nf, nct, np_max, conj_b, st);
+        else launch_sweep_chain_t<double, 1>(dtab, nf, nct, np_max, conj_b, st);
+    } else {
+        if (fp32) launch_sweep_chain_t<float, 3>(dtab, nf, nct, np_max, conj_b, st);
+        else launch_sweep_chain_t<double, 3>(dtab, nf, nct, np_max, conj_b, st);
+    }
+}
+
 void launch_sweep_init(const SweepTab* dtab, int n, int total, bool fp32, bool conj_b, hipStream_t st) {
     if (fp32) {
         if (conj_b) hipLaunchKernelGGL((k_sweep_init<float, true>), dim3(total), dim3(256), 0, st, dtab, n);
