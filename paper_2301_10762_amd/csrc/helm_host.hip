@@ -789,7 +789,7 @@ int sweep_group(helm_factor_s* const* fs, int n, const void* const* Ys, const in
     const size_t es = elem_bytes(fs[0]->prec);
     // narrow systems by themselves: which way a system is swept (and so the
     // order of its sums) does not depend on what else is in the group
-    const int narrow = (int)std::count_if(fs, fs + n, [](const helm_factor_s* f) { return f->np <= SWC_NP; });
+    const int narrow = (int)std::count_if(fs, fs + n, [=](const helm_factor_s* f) { return sweep_narrow(f->np, fp32); });
     if (narrow > 0 && narrow < n) {
         for (int kind = 0; kind < 2; ++kind) {
             std::vector<helm_factor_s*> f2;
@@ -798,7 +798,7 @@ int sweep_group(helm_factor_s* const* fs, int n, const void* const* Ys, const in
             std::vector<int64_t> ly, lx;
             std::vector<int> s2;
             for (int c = 0; c < n; ++c)
-                if ((fs[c]->np <= SWC_NP) == (kind == 0)) {
+                if (sweep_narrow(fs[c]->np, fp32) == (kind == 0)) {
                     f2.push_back(fs[c]);
                     y2.push_back(Ys[c]);
                     x2.push_back(Xs[c]);

@@ -28,8 +28,8 @@ int sweep_uniform(const SweepTab& tab, int n);
 int sweep_unroll(int np_max);
 void launch_sweep(const SweepTab* dtab, int n, int t, int uni, int unroll, int groups, int st, bool fp32,
                   bool forward, bool conj_b, hipStream_t st_);
-// both sweeps of fronts of at most SWC_NP nodes a row, in two launches
-constexpr int SWC_NP = 96;
+// both sweeps of narrow fronts, in two launches; np: padded nodes a row
+inline bool sweep_narrow(int np, bool fp32) { return np <= (fp32 ? 96 : 64); }
 void launch_sweep_chain(const SweepTab* dtab, int nf, int nct, int np_max, bool fp32, bool conj_b, hipStream_t st);
 int sweep_row_tiles(int np);
 int sweep_col_tiles(int S);

@@ -270,18 +270,22 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep(int n, int tstep, int g
 }
 
 // ------------------------------------------------------------ narrow grids --
-// Fronts of at most SWC_NP nodes a row: a step's product is smaller than a
-// launch (np = 80 in complex64: 2 us of work in a launch of 3.6 us), so one
-// workgroup takes a front and 16 columns through all its rows, with the
-// coupling vector in LDS and the next row's factor block and vectors on
-// their way while this row is multiplied.  The fronts meet between two
-// launches: the first goes forward to row k, the second starts with row k in
-// both fronts' workgroups (each needs x_k) and goes back.  Wider blocks keep
-// a launch per step, whose row tiles then fill more compute units.
+// A step's product is then smaller than a launch (np = 80 in complex64: 2 us
+// of work in a launch of 3.6 us), so one workgroup takes a front and 16
+// columns through all its rows, with the coupling vector in LDS and the next
+// row's factor block and vectors on their way while this row is multiplied.
+// The fronts meet between two launches: the first goes forward to row k, the
+// second starts with row k in both fronts' workgroups (each needs x_k) and
+// goes back.  A row takes 1.3 us (np = 16) to 2.5 us; the matrix cores of one
+// compute unit bound it from np = 64 (complex128) or 96 (complex64) on, where
+// a launch per step, whose row tiles fill several, takes over.  Solves of 64
+// columns, launches against this, in us: complex128 48 x 60 242 / 160,
+// 64 x 90 360 / 268, 80 x 60 264 / 320; complex64 with its refinement 48 x 60
+// 555 / 300, 80 x 60 602 / 459, 96 x 60 605 / 473.
 // A front's row tiles times ks parts of the contraction are one wavefront
 // each; the parts are summed in order.
 constexpr int SWC_W = 16, SWC_T = 64 * SWC_W;
-constexpr int SWC_E = SWC_NP * 16 / SWC_T + (SWC_NP * 16 % SWC_T != 0);   // vector entries per thread
+constexpr int SWC_E = 2;   // vector entries per thread (at most 96 x 16)
 
 template <typename T, bool FWD, bool CONJB, int CN>
 __global__ __launch_bounds__(SWC_T) void k_sweep_chain(const SweepTab* __restrict__ tab) {
@@ -459,13 +463,9 @@ static void launch_sweep_chain_t(const SweepTab* dtab, int nf, int nct, int np_m
     }
 }
 void launch_sweep_chain(const SweepTab* dtab, int nf, int nct, int np_max, bool fp32, bool conj_b, hipStream_t st) {
-    if (np_max <= 64) {
-        if (fp32) launch_sweep_chain_t<float, 1>(dtab, nf, nct, np_max, conj_b, st);
-        else launch_sweep_chain_t<double, 1>(dtab, nf, nct, np_max, conj_b, st);
-    } else {
-        if (fp32) launch_sweep_chain_t<float, 3>(dtab, nf, nct, np_max, conj_b, st);
-        else launch_sweep_chain_t<double, 3>(dtab, nf, nct, np_max, conj_b, st);
-    }
+    if (!fp32) launch_sweep_chain_t<double, 1>(dtab, nf, nct, np_max, conj_b, st);
+    else if (np_max <= 64) launch_sweep_chain_t<float, 1>(dtab, nf, nct, np_max, conj_b, st);
+    else launch_sweep_chain_t<float, 3>(dtab, nf, nct, np_max, conj_b, st);
 }
 
 void launch_sweep_init(const SweepTab* dtab, int n, int total, bool fp32, bool conj_b, hipStream_t st) {
