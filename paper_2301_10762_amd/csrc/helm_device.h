@@ -136,8 +136,8 @@ __device__ __forceinline__ double half_at_ends(int idx, int n) { return (idx == 
 __device__ __forceinline__ double x_coupling(const Coef& c, int j) { return (c.hz / c.hx) * half_at_ends(j, c.nz); }
 __device__ __forceinline__ double z_coupling(const Coef& c, int i) { return (c.hx / c.hz) * half_at_ends(i, c.nx); }
 
-// A(m, w) at node (i, j), diagonal entry
-__device__ __forceinline__ double2 diag_entry(const Coef& c, int i, int j) {
+// A(m, w) at node (i, j), diagonal entry, from m there
+__device__ __forceinline__ double2 diag_value(const Coef& c, int i, int j, double mk_) {
     double cx = x_coupling(c, j), cz = z_coupling(c, i);
     double s = 0.0;
     if (i > 0) s += cx;
@@ -148,8 +148,13 @@ __device__ __forceinline__ double2 diag_entry(const Coef& c, int i, int j) {
     double bnd = 0.0;
     if (j == 0 || j == c.nz - 1) bnd += 0.5 * c.hx * ((i > 0 ? 1 : 0) + (i < c.nx - 1 ? 1 : 0));
     if (i == 0 || i == c.nx - 1) bnd += 0.5 * c.hz * ((j > 0 ? 1 : 0) + (j < c.nz - 1 ? 1 : 0));
-    double mk_ = *((const HELM_GLOBAL double*)c.m + (size_t)j * c.nx + i);
     return make_double2(s - c.omega * c.omega * mass * mk_, -c.omega * bnd * sqrt(mk_));
+}
+__device__ __forceinline__ double m_at(const Coef& c, int i, int j) {
+    return *((const HELM_GLOBAL double*)c.m + (size_t)j * c.nx + i);
+}
+__device__ __forceinline__ double2 diag_entry(const Coef& c, int i, int j) {
+    return diag_value(c, i, j, m_at(c, i, j));
 }
 
 // entry (r, q) of the padded diagonal block A_j (identity in the padding)

@@ -21,6 +21,8 @@
 #include "helm_launch.h"
 #include "helm_tile.h"
 
+#include <type_traits>
+
 namespace helm {
 
 // ----------------------------------------------------------------- launches --
@@ -85,19 +87,56 @@ __device__ __forceinline__ const C* next_a_source(const ChainInfo& d, int jl) {
     return (d.Ain && jl + 1 == d.nblk - 1) ? (const C*)d.Ain : nullptr;
 }
 
-// Entry (r, c) of the next block's first diagonal tile, A_{j+1} - E G_j E,
-// from the entry g of G_j (the Schur complement on a block's last panel).
-template <typename C>
-__device__ __forceinline__ C next_schur(const ChainInfo& d, const C* Asrc, int jn, int r, int c, C g) {
-    double2 a1;
-    if (Asrc) {
-        const C v = gld(Asrc + (size_t)r * d.np + c);
-        a1 = make_double2(v.x, v.y);
-    } else {
-        a1 = block_entry(d.cf, jn, r, c);
+// What a lane needs to form entries of A_{j+1} - E G_j E in its columns: the
+// couplings and the diagonal entries, prepared while the step's operands are
+// on their way.  (Formed entry by entry after the product, with its divisions
+// and its load of m behind the branch on the diagonal, this was 20 k of the
+// 36 k cycles of a block's last step at np = 48.)
+template <int NC>
+struct NextBlock {
+    double cx, ez;        // x coupling of the row, z coupling between the rows
+    double2 dg[NC];       // diagonal entries of the lane's columns
+};
+// mk: m at the lane's columns (clamped) of row jn
+template <int NC>
+__device__ __forceinline__ NextBlock<NC> next_block(const Coef& c, int jn, const int (&col)[NC], const double (&mk)[NC]) {
+    NextBlock<NC> b;
+    b.cx = x_coupling(c, jn);
+    b.ez = c.hx / c.hz;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+        b.dg[q] = diag_value(c, min(col[q], c.nx - 1), jn, mk[q]);
+        asm volatile("" : "+v"(b.dg[q].x), "+v"(b.dg[q].y));   // here, not where it is used
     }
-    const double s = row_coupling(d.cf, r) * row_coupling(d.cf, c);
-    return mk<C>(a1.x - s * (double)g.x, a1.y - s * (double)g.y);
+    asm volatile("" : "+v"(b.cx), "+v"(b.ez));
+    return b;
+}
+// entry (r, col) of A_{j+1} (block_entry)
+template <int NC>
+__device__ __forceinline__ double2 next_entry(const Coef& c, const NextBlock<NC>& b, int q, int r, int col) {
+    const bool in = r < c.nx && col < c.nx, diag = r == col, side = r == col + 1 || col == r + 1;
+    return make_double2(diag ? (in ? b.dg[q].x : 1.0) : (in && side ? -b.cx : 0.0), diag && in ? b.dg[q].y : 0.0);
+}
+// entry a of A_{j+1} (or of the merge block) less that of E G_j E, with g that
+// of G_j; ez: hx / hz
+template <typename C>
+__device__ __forceinline__ C next_schur(const Coef& c, double ez, double2 a, int r, int col, C g) {
+    const double er = r < c.nx ? -(ez * half_at_ends(r, c.nx)) : 0.0;
+    const double ec = col < c.nx ? -(ez * half_at_ends(col, c.nx)) : 0.0;
+    const double s = er * ec;
+    return mk<C>(a.x - s * (double)g.x, a.y - s * (double)g.y);
+}
+// the same in one, for the tile that is inverted next
+template <typename C>
+__device__ __forceinline__ C next_schur(const ChainInfo& d, const NextBlock<1>& b, const C* Asrc, int r, int col, C g) {
+    double2 a;
+    if (Asrc) {
+        const C v = gld(Asrc + (size_t)r * d.np + col);
+        a = make_double2(v.x, v.y);
+    } else {
+        a = next_entry(d.cf, b, 0, r, col);
+    }
+    return next_schur<C>(d.cf, b.ez, a, r, col, g);
 }
 
 // workgroup that prepares the next step's inverted diagonal tile
@@ -132,6 +171,7 @@ __device__ __forceinline__ void next_tile(const ChainInfo& d, const PanelStep& p
     // entries outside the kb x kbn tiles are zeroed when they are placed.
     // T arrives transposed (Tt[c][k]): read it in order, place it as sT[k][c]
     C tl[4], xa[4], xb[4], xz[4];
+    const double mk1[1] = {m_at(d.cf, min(16 * wc + lr, d.cf.nx - 1), jn)};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int idx = t + 256 * i;
@@ -147,6 +187,14 @@ __device__ __forceinline__ void next_tile(const ChainInfo& d, const PanelStep& p
         xz[e] = gld(X + (size_t)(kn0 + min(rr, kbn - 1)) * np + kn0 + min(cc, kbn - 1));
     }
     __builtin_amdgcn_sched_barrier(0);   // keep every load ahead of the first wait
+    C am[4];   // the merge block's entries, or A's
+    NextBlock<1> nb{};
+    if (Asrc) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            am[e] = gld(Asrc + (size_t)min(16 * wr + acc_row<T>(lg, e), kbn - 1) * np + min(16 * wc + lr, kbn - 1));
+    }
+    if (ps.last_panel) nb = next_block<1>(d.cf, jn, {16 * wc + lr}, mk1);
     const C cz = mk<C>(0.0, 0.0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -206,12 +254,13 @@ __device__ __forceinline__ void next_tile(const ChainInfo& d, const PanelStep& p
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int rr = 16 * wr + acc_row<T>(lg, e), cc = 16 * wc + lr;
-                C v = mk<C>(0.0, 0.0);
-                if (rr < kbn && cc < kbn) {
-                    v = mk<C>(zr[e], zi[e]);
-                    if (ps.last_panel) v = next_schur<C>(d, Asrc, jn, rr, cc, v);
-                    m2 = fmaxf(m2, (float)(v.x * v.x + v.y * v.y));
+                C v = mk<C>(zr[e], zi[e]);
+                if (ps.last_panel) {
+                    const double2 a = Asrc ? make_double2(am[e].x, am[e].y) : next_entry(d.cf, nb, 0, rr, cc);
+                    v = next_schur<C>(d.cf, nb.ez, a, rr, cc, v);
                 }
+                v = HELM_CSEL(rr < kbn && cc < kbn, v, mk<C>(0.0, 0.0));
+                m2 = fmaxf(m2, (float)(v.x * v.x + v.y * v.y));
                 L2[rr * 33 + cc] = v;
             }
             const uint32_t wm = wave_max_u32(__float_as_uint(m2));
@@ -232,7 +281,9 @@ __device__ __forceinline__ void next_tile(const ChainInfo& d, const PanelStep& p
     }
     if (ps.last_panel && act) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a[e] = next_schur<C>(d, Asrc, jn, r, 4 * cg + e, a[e]);
+        for (int e = 0; e < 4; ++e)
+            a[e] = next_schur<C>(d, next_block<1>(d.cf, jn, {4 * cg + e}, {m_at(d.cf, min(4 * cg + e, d.cf.nx - 1), jn)}),
+                                 Asrc, r, 4 * cg + e, a[e]);
     }
     __syncthreads();   // sXa is reused as the inversion buffer
     bool small;
@@ -298,6 +349,17 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
         vr[q] = R[q] < np;
         vc[q] = Cc[q] < np;
     }
+    const int row_b = d.row0 + d.dir * ps.j, rn = row_b + d.dir;
+    C* An = nullptr;
+    const C* Asrc = nullptr;
+    if (ps.last_panel) {
+        if (ps.j + 1 < d.nblk) {
+            An = (C*)d.G + (size_t)rn * np * np;
+            Asrc = next_a_source<C>(d, ps.j);
+        } else if (d.Aout) {
+            An = (C*)d.Aout;
+        }
+    }
     // 1. global loads, all issued up front: X_{I,K} (rows of this tile, panel
     //    columns) and T for the W product, V_J = X_{K,J} for the update (kept
     //    in registers until W is done), and this tile of X'
@@ -305,6 +367,8 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
     // every load is issued at a clamped (in-range) address; out-of-range and
     // identity entries are substituted afterwards
     C xik[8], tv[4], vv[8], xt[2][2][4];
+    const int rm = min(max(rn, 0), d.cf.nz - 1);
+    const double mk2[2] = {m_at(d.cf, min(Cc[0] + lr, d.cf.nx - 1), rm), m_at(d.cf, min(Cc[1] + lr, d.cf.nx - 1), rm)};
     {
         const int rr = t >> 2, c8 = 8 * (t & 3), row = min(I0 + rr, np - 1);
 #pragma unroll
@@ -326,6 +390,8 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
                                         min(Cc[bj] + lr, np - 1));
     }
     __builtin_amdgcn_sched_barrier(0);   // keep every load ahead of the first wait
+    NextBlock<2> nb{};
+    if (An) nb = next_block<2>(d.cf, rm, {Cc[0] + lr, Cc[1] + lr}, mk2);
     const C zero = mk<C>(0.0, 0.0);
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -429,47 +495,38 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
     // 5. store; after the last panel also D_next = A_next - E Y E, into the
     //    front's next block, or into the merge block after a bottom front's
     //    last block
-    const int row_b = d.row0 + d.dir * ps.j, rn = row_b + d.dir;
-    C* An = nullptr;
-    const C* Asrc = nullptr;
-    if (ps.last_panel) {
-        if (ps.j + 1 < d.nblk) {
-            An = (C*)d.G + (size_t)rn * np * np;
-            Asrc = next_a_source<C>(d, ps.j);
-        } else if (d.Aout) {
-            An = (C*)d.Aout;
-        }
-    }
-    const bool schur = An != nullptr;
+    auto store = [&](auto mode) {   // 0: Y alone, 1: and D_next from A's entries, 2: and from the merge block
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+        for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            if (!(vr[bi] && vc[bj])) continue;
-            const int col = Cc[bj] + lr;
-            V gre, gim;
-            cacc_final<GAUSS, V>(a1[bi][bj], a2[bi][bj], a3[bi][bj], gre, gim);
+            for (int bj = 0; bj < 2; ++bj) {
+                if (!(vr[bi] && vc[bj])) continue;
+                const int col = Cc[bj] + lr;
+                V gre, gim;
+                cacc_final<GAUSS, V>(a1[bi][bj], a2[bi][bj], a3[bi][bj], gre, gim);
+                C am[4];
+                if (mode == 2) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = R[bi] + acc_row<T>(lg, e);
-                const C g = mk<C>(gre[e], gim[e]);
-                // the finished inverse goes to the sweeps' operand layout
-                yst(Y + (ps.last_panel ? (sizeof(T) == 4 ? a_tiled4(row, col, np) : a_tiled(row, col, np))
-                                       : (size_t)row * np + col),
-                    g);
-                if (schur) {
-                    double2 a1;
-                    if (Asrc) {
-                        const C v = gld(Asrc + (size_t)row * np + col);
-                        a1 = make_double2(v.x, v.y);
-                    } else {
-                        a1 = block_entry(d.cf, rn, row, col);
-                    }
-                    const double s = row_coupling(d.cf, row) * row_coupling(d.cf, col);
-                    yst(An + (size_t)row * np + col, mk<C>(a1.x - s * (double)g.x, a1.y - s * (double)g.y));
+                    for (int e = 0; e < 4; ++e) am[e] = gld(Asrc + (size_t)(R[bi] + acc_row<T>(lg, e)) * np + col);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int row = R[bi] + acc_row<T>(lg, e);
+                    const C g = mk<C>(gre[e], gim[e]);
+                    // the finished inverse goes to the sweeps' operand layout
+                    yst(Y + (ps.last_panel ? (sizeof(T) == 4 ? a_tiled4(row, col, np) : a_tiled(row, col, np))
+                                           : (size_t)row * np + col),
+                        g);
+                    if (mode > 0)
+                        yst(An + (size_t)row * np + col,
+                            next_schur<C>(d.cf, nb.ez, mode == 2 ? make_double2(am[e].x, am[e].y)
+                                                                 : next_entry(d.cf, nb, bj, row, col), row, col, g));
                 }
             }
-        }
+    };
+    if (!An) store(std::integral_constant<int, 0>{});
+    else if (!Asrc) store(std::integral_constant<int, 1>{});
+    else store(std::integral_constant<int, 2>{});
 }
 
 // Workgroups 0 .. n-1 of a step launch prepare the next diagonal tile of
