@@ -926,36 +926,10 @@ struct SolveJob {
     helm_info* info;
 };
 
-// residual norms: max over columns of ||B - A X|| / ||B||; optionally writes
-// r (complex128, ld N) and/or its complex64 copy (conjugated when adjoint)
-int residual_norms(const helm_factor_s* f, int adjoint, const double* B, int64_t ldb, const double* X, int64_t ldx,
-                   double* R, float* R32, int S, hipStream_t st, double* maxrel) {
-    Scratch sc(st);
-    const int64_t N = N_of(f->g);
-    const int nblk = (int)((N + 255) / 256);
-    double *partial, *norms;
-    int rc = sc.get(&partial, sizeof(double) * 2 * (size_t)nblk * S);
-    if (rc) return rc;
-    if ((rc = sc.get(&norms, sizeof(double) * 2 * S))) return rc;
-    launch_residual(coef_of(f), adjoint, B, ldb, X, ldx, R, N, R32, S, partial, nblk, st);
-    launch_norms_finish(partial, nblk, S, norms, st);
-    g_launches += 2;
-    std::vector<double> h(2 * S);
-    HIPCHECK(hipMemcpyAsync(h.data(), norms, sizeof(double) * 2 * S, hipMemcpyDeviceToHost, st));
-    HIPCHECK(hipStreamSynchronize(st));
-    double mx = 0.0;
-    for (int s = 0; s < S; ++s) {
-        double rr = std::sqrt(h[2 * s]), bb = std::sqrt(h[2 * s + 1]);
-        double rel = bb > 0.0 ? rr / bb : (rr > 0.0 ? INFINITY : 0.0);
-        if (!(rel <= mx)) mx = rel;   // NaN propagates
-    }
-    *maxrel = mx;
-    return HELM_OK;
-}
-
-// The same for several (factor, B, X) at once: every residual is launched,
-// then one copy brings all norms back (a copy per request held up the next
-// launch: 30 us of idle GPU each).  maxrel[c] per request.
+// Residual norms of several (factor, B, X) at once, max over columns of
+// ||B - A X|| / ||B||: every residual is launched, then one copy brings all
+// norms back (a copy per request held up the next launch: 30 us of idle GPU
+// each).  maxrel[c] per request.
 struct ResidualReq {
     const helm_factor_s* f;
     const double* B;
@@ -977,16 +951,20 @@ int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStr
     int rc = sc.get(&norms, sizeof(double) * tot);
     if (rc) return rc;
     size_t off = 0;
-    for (int c = 0; c < n; ++c) {
-        const ResidualReq& r = rq[c];
-        const int64_t N = N_of(r.f->g);
-        const int nblk = (int)((N + 255) / 256);
-        double* partial;
-        if ((rc = sc.get(&partial, sizeof(double) * 2 * (size_t)nblk * r.S))) return rc;
-        launch_residual(coef_of(r.f), adjoint, r.B, r.ldb, r.X, r.ldx, r.R, N, r.R32, r.S, partial, nblk, st);
-        launch_norms_finish(partial, nblk, r.S, norms + off, st);
+    for (int c0 = 0; c0 < n; c0 += RES_MAX) {
+        const int k = std::min(RES_MAX, n - c0);
+        ResTab tab{};
+        for (int c = 0; c < k; ++c) {
+            const ResidualReq& r = rq[c0 + c];
+            const int64_t N = N_of(r.f->g);
+            double* partial;
+            if ((rc = sc.get(&partial, sizeof(double) * 2 * (size_t)residual_blocks(N) * r.S))) return rc;
+            tab.j[c] = {coef_of(r.f), r.B, r.X, r.R, r.R32, partial, norms + off, r.ldb, r.ldx, N, r.S, 0, 0, 0};
+            off += 2 * (size_t)r.S;
+        }
+        launch_residual(tab, k, adjoint, st);
+        launch_norms_finish(tab, k, st);
         g_launches += 2;
-        off += 2 * (size_t)r.S;
     }
     HIPCHECK(hipMemcpyAsync(h.data(), norms, sizeof(double) * tot, hipMemcpyDeviceToHost, st));
     HIPCHECK(hipStreamSynchronize(st));
@@ -1002,6 +980,10 @@ int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStr
         off += 2 * (size_t)rq[c].S;
     }
     return HELM_OK;
+}
+int residual_norms(const helm_factor_s* f, int adjoint, const double* B, int64_t ldb, const double* X, int64_t ldx,
+                   double* R, float* R32, int S, hipStream_t st, double* maxrel) {
+    return residual_norms_batch({{f, B, ldb, X, ldx, R, R32, S}}, adjoint, st, maxrel);
 }
 
 constexpr int MAX_IR = 10;
@@ -1035,7 +1017,7 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
     int rc;
     if ((rc = sc.get(&dtab, sizeof(NdJobTab)))) return rc;
     std::vector<double*> R(n, nullptr), part(n, nullptr);
-    const int nblk = (int)((N + 255) / 256);
+    const int nblk = residual_blocks(N);
     for (int c = 0; c < n; ++c) {
         NdJob& d = tab.j[c];
         const size_t S = (size_t)std::min(js[c]->S, cols);
@@ -1056,7 +1038,8 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
     const NdTabs t = nd_tabs(P);
     const int L = (int)P.levels.size();
     for (int c0 = 0; c0 < smax; c0 += cols) {
-        int wide = 0;
+        int wide = 0, nres = 0;
+        ResTab rt{};
         for (int c = 0; c < n; ++c) {
             NdJob& d = tab.j[c];
             d.S = std::max(0, std::min(cols, js[c]->S - c0));
@@ -1064,11 +1047,14 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
             d.X = (double2*)js[c]->X + (size_t)c0 * js[c]->ld;
             wide = std::max(wide, d.S);
             if (correct && d.S > 0) {
-                launch_residual(d.cf, adjoint ? 1 : 0, (const double*)d.B, js[c]->ld, (const double*)d.X, js[c]->ld,
-                                R[c], N, nullptr, d.S, part[c], nblk, st);
-                g_launches += 1;
+                rt.j[nres++] = {d.cf, (const double*)d.B, (const double*)d.X, R[c], nullptr, part[c], nullptr,
+                                js[c]->ld, js[c]->ld, N, d.S, 0, 0, 0};
                 d.B = (const double2*)R[c];
             }
+        }
+        if (nres) {
+            launch_residual(rt, nres, adjoint ? 1 : 0, st);
+            g_launches += 1;
         }
         launch_nd_put_jobs(tab, dtab, st);
         if (P.nrow_up) launch_nd_in(t, dtab, n, P.nrow_up, wide, adjoint, st);
@@ -2465,13 +2451,15 @@ int helm_residual(const helm_grid* grid, const double* m_dev, double omega, int 
     hipStream_t st = S_(stream);
     Scratch sc(st);
     const int64_t N = N_of(*grid);
-    const int nblk = (int)((N + 255) / 256);
+    const int nblk = residual_blocks(N);
     double* partial;
     if ((rc = sc.get(&partial, sizeof(double) * 2 * (size_t)nblk * S))) return rc;
     Coef cf{m_dev, omega, grid->hx, grid->hz, grid->nx, grid->nz};
     // r is written with leading dimension ld when requested
-    launch_residual(cf, adjoint, B_dev, ld, X_dev, ld, r_dev, ld, nullptr, S, partial, nblk, st);
-    launch_norms_finish(partial, nblk, S, norms_dev, st);
+    ResTab tab{};
+    tab.j[0] = {cf, B_dev, X_dev, r_dev, nullptr, partial, norms_dev, ld, ld, ld, S, 0, 0, 0};
+    launch_residual(tab, 1, adjoint, st);
+    launch_norms_finish(tab, 1, st);
     g_launches += 2;
     HIPCHECK(hipGetLastError());
     return HELM_OK;

@@ -28,6 +28,8 @@
 #include "helm_device.h"
 #include "helm_launch.h"
 
+#include <algorithm>
+
 namespace helm {
 // ------------------------------------------------------ elementwise / FP64 --
 __global__ void k_check_model(const double* m, int64_t n, int* flag) {
@@ -60,15 +62,24 @@ __global__ void k_zero(uint32_t* p, size_t n32) {
 // pairs are numbered to give each XCD one contiguous range of them: the rows
 // above and below a block, which the stencil reads, then belong to blocks
 // on the same XCD and come from its L2 instead of being fetched again by
-// every neighbour's XCD.  The grid has 8 * per_xcd workgroups; numbers past
-// the nblk * ceil(S / RES_CS) pairs return at once.
+// every neighbour's XCD.  A job has 8 * per_xcd workgroups; numbers past the
+// nblk * ceil(S / RES_CS) pairs return at once.  All jobs of a batch go in
+// one launch, and so do their norms (201^2, four systems of 32 columns: four
+// launches of 12 us each and four of 4 us).
 constexpr int RES_CS = 2;
 
-__global__ __launch_bounds__(256) void k_residual(Coef cf, int adjoint, const double2* __restrict__ B, int64_t ldb,
-                                                  const double2* __restrict__ X, int64_t ldx,
-                                                  double2* __restrict__ R, int64_t ldr, float2* __restrict__ R32,
-                                                  int S, double* __restrict__ partial, int nblk, int per_xcd) {
+__global__ __launch_bounds__(256) void k_residual(const ResTab tab, int adjoint) {
     __shared__ double sr[RES_CS][4], sb[RES_CS][4];
+    const ResJob d = tab.j[blockIdx.y];
+    const Coef cf = d.cf;
+    const double2* __restrict__ B = (const double2*)d.B;
+    const double2* __restrict__ X = (const double2*)d.X;
+    double2* __restrict__ R = (double2*)d.R;
+    float2* __restrict__ R32 = (float2*)d.R32;
+    double* __restrict__ partial = d.partial;
+    const int64_t ldb = d.ldb, ldx = d.ldx, ldr = d.ldr;
+    const int S = d.S, nblk = d.nblk, per_xcd = d.per_xcd;
+    if ((int)(blockIdx.x >> 3) >= per_xcd) return;
     const int pair = (int)(blockIdx.x & 7u) * per_xcd + (int)(blockIdx.x >> 3);
     const int ncg = (S + RES_CS - 1) / RES_CS;
     if ((int64_t)pair >= (int64_t)nblk * ncg) return;
@@ -140,9 +151,13 @@ __global__ __launch_bounds__(256) void k_residual(Coef cf, int adjoint, const do
 
 // per column s: the sums of the per-block partials, one workgroup per
 // column, strided partial sums then a fixed-order tree in LDS
-__global__ __launch_bounds__(256) void k_norms_finish(const double* partial, int nblk, int S, double* norms) {
+__global__ __launch_bounds__(256) void k_norms_finish(const ResTab tab) {
     __shared__ double sa[256], sc[256];
-    const int s = blockIdx.x, t = threadIdx.x;
+    const ResJob d = tab.j[blockIdx.y];
+    const double* partial = d.partial;
+    double* norms = d.norms;
+    const int s = blockIdx.x, t = threadIdx.x, nblk = d.nblk;
+    if (s >= d.S) return;
     double a = 0.0, c = 0.0;
     for (int q = t; q < nblk; q += 256) {
         a += partial[((size_t)s * nblk + q) * 2];
@@ -562,14 +577,24 @@ void launch_put_sweep_table(const SweepTab& tab, SweepTab* dst, hipStream_t st) 
 void launch_check_model(const double* m, int64_t n, int* flag, hipStream_t st) {
     hipLaunchKernelGGL(k_check_model, grid1(n), dim3(256), 0, st, m, n, flag);
 }
-void launch_residual(const Coef& cf, int adjoint, const double* B, int64_t ldb, const double* X, int64_t ldx,
-                     double* R, int64_t ldr, float* R32, int S, double* partial, int nblk, hipStream_t st) {
-    const int per_xcd = (int)(((int64_t)nblk * ((S + RES_CS - 1) / RES_CS) + 7) / 8);
-    hipLaunchKernelGGL(k_residual, dim3(8 * per_xcd), dim3(256), 0, st, cf, adjoint, (const double2*)B, ldb,
-                       (const double2*)X, ldx, (double2*)R, ldr, (float2*)R32, S, partial, nblk, per_xcd);
+int residual_blocks(int64_t N) { return (int)((N + 255) / 256); }
+void launch_residual(ResTab tab, int n, int adjoint, hipStream_t st) {
+    int most = 0;
+    for (int c = 0; c < n; ++c) {
+        ResJob& d = tab.j[c];
+        d.nblk = residual_blocks((int64_t)d.cf.nx * d.cf.nz);
+        d.per_xcd = (int)(((int64_t)d.nblk * ((d.S + RES_CS - 1) / RES_CS) + 7) / 8);
+        most = std::max(most, d.per_xcd);
+    }
+    hipLaunchKernelGGL(k_residual, dim3(8 * most, n), dim3(256), 0, st, tab, adjoint);
 }
-void launch_norms_finish(const double* partial, int nblk, int S, double* norms, hipStream_t st) {
-    hipLaunchKernelGGL(k_norms_finish, dim3(S), dim3(256), 0, st, partial, nblk, S, norms);
+void launch_norms_finish(ResTab tab, int n, hipStream_t st) {
+    int most = 0;
+    for (int c = 0; c < n; ++c) {
+        tab.j[c].nblk = residual_blocks((int64_t)tab.j[c].cf.nx * tab.j[c].cf.nz);
+        most = std::max(most, tab.j[c].S);
+    }
+    hipLaunchKernelGGL(k_norms_finish, dim3(most, n), dim3(256), 0, st, tab);
 }
 void launch_c128_to_c64(const double* src, int64_t lds, float* dst, int64_t ldd, int64_t N, int S, int conj,
                         hipStream_t st) {

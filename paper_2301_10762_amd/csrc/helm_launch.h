@@ -34,10 +34,27 @@ void launch_sweep_chain(const SweepTab* dtab, int nf, int nct, int np_max, bool 
 int sweep_row_tiles(int np);
 int sweep_col_tiles(int S);
 void launch_check_model(const double* m, int64_t n, int* flag, hipStream_t st);
-void launch_residual(const Coef& cf, int adjoint, const double* B, int64_t ldb, const double* X,
-                     int64_t ldx, double* R, int64_t ldr, float* R32, int S, double* partial,
-                     int nblk, hipStream_t st);
-void launch_norms_finish(const double* partial, int nblk, int S, double* norms, hipStream_t st);
+// Residuals r = B - A X of up to RES_MAX jobs in one launch: R and R32 (or
+// null) take r and its complex64 copy (conjugated if adjoint), partial the
+// sums of squares of residual_blocks() blocks per column; then norms, per
+// column the squares' sums of r and B.
+constexpr int RES_MAX = 16;
+struct ResJob {
+    Coef cf;
+    const double *B, *X;
+    double* R;
+    float* R32;
+    double *partial, *norms;
+    int64_t ldb, ldx, ldr;
+    int S, nblk, per_xcd, pad_;   // nblk, per_xcd: set by the launchers
+};
+struct ResTab {
+    ResJob j[RES_MAX];
+};
+static_assert(sizeof(ResTab) <= 4000, "passed as a kernel argument");
+int residual_blocks(int64_t N);
+void launch_residual(ResTab tab, int n, int adjoint, hipStream_t st);
+void launch_norms_finish(ResTab tab, int n, hipStream_t st);
 void launch_c128_to_c64(const double* src, int64_t lds, float* dst, int64_t ldd, int64_t N, int S,
                         int conj, hipStream_t st);
 void launch_c64_to_c128(const float* src, int64_t lds, double* dst, int64_t ldd, int64_t N, int S,

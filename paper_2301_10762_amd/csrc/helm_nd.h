@@ -130,7 +130,7 @@ struct NdPlan {
     const NdSub* d_subs = nullptr;
     const NdShape* d_shapes = nullptr;
     size_t col_bytes() const {       // sweep scratch per right-hand side, with a residual
-        return sizeof(double) * 2 * ((size_t)nx * nz + (size_t)(nrow_up + nrow + urows[0] + urows[1]));
+        return sizeof(double) * 2 * ((size_t)nx * nz + (size_t)nx * nz / 256 + 1 + (size_t)(nrow_up + nrow + urows[0] + urows[1]));
     }
 };
 
