@@ -19,6 +19,8 @@
 #include "helm_launch.h"
 #include "helm_tile.h"
 
+#include <type_traits>
+
 namespace helm {
 
 // Records of the plan and of the launch tables are read as whole words
@@ -382,12 +384,13 @@ __device__ __forceinline__ void nd_gj(double2 (&a)[4], int kb, const NdSys& y, i
     if (zero >= 0 && t == 0) report_zero_pivot(y.status, front, k0 + zero);
     __syncthreads();
 }
+template <typename W>
 __device__ __forceinline__ void nd_invert(double2 (&a)[4], int kb, const NdSys& y, int front, int k0, NdScratch& sh,
-                                          double2* L2) {
+                                          double2* L2, W beside) {
     const int t = threadIdx.x, r = t >> 3, cg = t & 7;
     const bool act = r < kb && 4 * cg < kb;
     bool pivot = y.pivot;
-    if (!pivot) pivot = inv_blocked<double>(a, kb, L2, sh.row, TAU2);
+    if (!pivot) pivot = inv_blocked<double>(a, kb, L2, sh.row, TAU2, beside);
     if (pivot) nd_gj(a, kb, y, front, k0, sh, L2);
     double2 q[4];
 #pragma unroll
@@ -397,7 +400,7 @@ __device__ __forceinline__ void nd_invert(double2 (&a)[4], int kb, const NdSys& 
 
 // ------------------------------------------------------------- narrow fronts --
 // A front of at most 32 pivots in one workgroup.  The pivot block is inverted
-// whole (G), the couplings F^T (one row per ring node) stay in LDS; each
+// whole (G), the couplings F^T (one row per ring node) are gathered beside it and stay in LDS; each
 // wavefront then takes rows of ring tiles by itself: R_I = G F_I, whose
 // accumulators are also the A operand of the next product (the FP64 result
 // holds rows g + 4 e of column r in lane 16 g + r), so for the tiles J >= I
@@ -429,15 +432,28 @@ __global__ __launch_bounds__(KP == 16 ? 256 : 512) void k_nd_front(NdTabs t, int
             a[e] = nd_entry(kids, true, sidx[in ? r : 0], sidx[in ? 4 * cg + e : 0]);
             if (!in) a[e] = make_double2(0.0, 0.0);
         }
-        // F^T: the ring index fastest, so that a child's rows are read along
-        for (int k = w; k < KP; k += NW)
-#pragma unroll 2
+        // F^T, the ring index fastest, so that a child's rows are read along:
+        // by the wavefronts that the inversion leaves free (all of them
+        // before it when every tile is to be pivoted)
+        auto couple = [&](int k0, auto nk) {
+            constexpr int NK = decltype(nk)::value, PER = (KP + NK - 1) / NK;
             for (int i = l; i < 16 * nb; i += 64) {
-                double2 v = make_double2(0.0, 0.0);
-                if (k < pp) v = nd_entry(kids, true, sidx[k], sidx[pp + i]);
-                sF[(size_t)i * LD + k] = v;
+                const NdIndex c = sidx[pp + i];
+                double2 v[PER];
+#pragma unroll
+                for (int q = 0; q < PER; ++q) {
+                    const int k = k0 + NK * q;
+                    v[q] = nd_entry(kids, true, sidx[min(k, pp - 1)], c);
+                    if (k >= pp) v[q] = make_double2(0.0, 0.0);
+                }
+#pragma unroll
+                for (int q = 0; q < PER; ++q)
+                    if (k0 + NK * q < KP) sF[(size_t)i * LD + k0 + NK * q] = v[q];
             }
-        nd_invert(a, pp, y, first + (int)blockIdx.x, 0, sh, L2);
+        };
+        if (y.pivot) couple(w, std::integral_constant<int, NW>{});
+        nd_invert(a, pp, y, first + (int)blockIdx.x, 0, sh, L2,
+                  [&] { couple(w - 1, std::integral_constant<int, NW - 1>{}); });
     }
     __syncthreads();
     double2* fac = y.fac + f.fac;
@@ -445,9 +461,7 @@ __global__ __launch_bounds__(KP == 16 ? 256 : 512) void k_nd_front(NdTabs t, int
         if (l < p) gst(fac + c * p + l, L2[l * 33 + c]);
     double2* S = (parity ? y.work[1] : y.work[0]) + f.s;
     const int np = pp >> 4;
-    for (int v = 0; v < nb; v += NW) {
-        const int I = (v / NW) & 1 ? v + NW - 1 - w : v + w;   // long and short rows in turn
-        if (I >= nb) continue;
+    for (int I = w; I < nb; I += NW) {
         double2 s[4];
         auto gather = [&](int J) {
             const NdIndex& c = sidx[pp + 16 * J + lr];
@@ -458,14 +472,15 @@ __global__ __launch_bounds__(KP == 16 ? 256 : 512) void k_nd_front(NdTabs t, int
         double2 ra[KP / 4];   // -R_I, as results and as operand
 #pragma unroll
         for (int kt = 0; kt < KP / 16; ++kt) {
-            v4d wr, wi;
+            v4d p1, p2, p3, wr, wi;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { wr[e] = 0.0; wi[e] = 0.0; }
+            for (int e = 0; e < 4; ++e) { p1[e] = 0.0; p2[e] = 0.0; p3[e] = 0.0; }
             if (kt < np)
                 for (int m = 0; m < pp; m += 4) {
                     const double2 g = L2[(16 * kt + lr) * 33 + m + lg], x = sF[(size_t)(16 * I + lr) * LD + m + lg];
-                    cmfma<double, v4d>(wr, wi, g.x, g.y, x.x, x.y);
+                    cmfma3<double, v4d>(p1, p2, p3, g.x, g.y, x.x, x.y);
                 }
+            cacc_final<true, v4d>(p1, p2, p3, wr, wi);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int i = 16 * I + lr, k = 16 * kt + lg + 4 * e;
@@ -473,24 +488,31 @@ __global__ __launch_bounds__(KP == 16 ? 256 : 512) void k_nd_front(NdTabs t, int
                 ra[4 * kt + e] = make_double2(-wr[e], -wi[e]);
             }
         }
-        for (int J = I; J < nb; ++J) {
-            v4d re, im;
+        // half of the tiles of row I of the symmetric complement, J = I, I + 1,
+        // ... around the ring: every wavefront takes as many
+        const int half = (nb & 1) || I < nb / 2 ? nb / 2 + 1 : nb / 2;
+        for (int d = 0, J = I; d < half; ++d) {
+            v4d a1, a2, a3, re, im;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 re[e] = s[e].x;
                 im[e] = s[e].y;
             }
-            if (J + 1 < nb) gather(J + 1);
+            cacc_seed<true, v4d>(a1, a2, a3, re, im);
+            const int J1 = J + 1 < nb ? J + 1 : 0;
+            if (d + 1 < half) gather(J1);
 #pragma unroll
             for (int q = 0; q < KP / 4; ++q) {
                 const double2 x = sF[(size_t)(16 * J + lr) * LD + 4 * q + lg];
-                cmfma<double, v4d>(re, im, ra[q].x, ra[q].y, x.x, x.y);
+                cmfma3<double, v4d>(a1, a2, a3, ra[q].x, ra[q].y, x.x, x.y);
             }
+            cacc_final<true, v4d>(a1, a2, a3, re, im);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int i = 16 * I + lg + 4 * e, j = 16 * J + lr;
-                if (i < b && j < b) gst(S + (int64_t)i * b + j, make_double2(re[e], im[e]));
+                if (i < b && j < b) gst(S + (J < I ? (int64_t)j * b + i : (int64_t)i * b + j), make_double2(re[e], im[e]));
             }
+            J = J1;
         }
     }
 }
@@ -535,7 +557,7 @@ __global__ __launch_bounds__(256) void k_nd_gather(NdTabs t, int first, int coun
             a[e] = nd_entry(kids, true, sr[r], sc[4 * cg + e]);
             if (r >= f.pp || 4 * cg >= f.pp) a[e] = make_double2(0.0, 0.0);
         }
-        nd_invert(a, min(KB, f.pp), y, first + b, 0, sh, L2);
+        nd_invert(a, min(KB, f.pp), y, first + b, 0, sh, L2, NoWork{});
         store_inverse<double>(min(KB, f.pp), L2, nd_tslot(f, work, 0));
         return;
     }

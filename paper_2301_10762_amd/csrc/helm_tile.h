@@ -339,12 +339,17 @@ __device__ __forceinline__ void mm16(const typename CT<T>::c (&a)[4], const type
 // The second half: the tile already in L2 (rows 0 .. kb-1, stride 33),
 // each wavefront's largest |a_ij|^2 in sh.amax and sh.small cleared, all
 // visible to the workgroup.
-template <typename T>
-__device__ __forceinline__ bool inv_blocked_core(int kb, typename CT<T>::c* L2, RowScratch<T>& sh, float tau2);
+// beside(): work for the other wavefronts while the first inverts A.
+struct NoWork {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <typename T, typename W = NoWork>
+__device__ __forceinline__ bool inv_blocked_core(int kb, typename CT<T>::c* L2, RowScratch<T>& sh, float tau2,
+                                                 W beside = W());
 
-template <typename T>
+template <typename T, typename W = NoWork>
 __device__ __forceinline__ bool inv_blocked(typename CT<T>::c (&a)[4], int kb, typename CT<T>::c* L2,
-                                            RowScratch<T>& sh, float tau2) {
+                                            RowScratch<T>& sh, float tau2, W beside = W()) {
     const int t = threadIdx.x, w = t >> 6, l = t & 63;
     const int r = t >> 3, cg = t & 7;
     const bool act = (r < kb) && (4 * cg < kb);
@@ -363,11 +368,12 @@ __device__ __forceinline__ bool inv_blocked(typename CT<T>::c (&a)[4], int kb, t
         }
     }
     __syncthreads();
-    return inv_blocked_core<T>(kb, L2, sh, tau2);
+    return inv_blocked_core<T>(kb, L2, sh, tau2, beside);
 }
 
-template <typename T>
-__device__ __forceinline__ bool inv_blocked_core(int kb, typename CT<T>::c* L2, RowScratch<T>& sh, float tau2) {
+template <typename T, typename W>
+__device__ __forceinline__ bool inv_blocked_core(int kb, typename CT<T>::c* L2, RowScratch<T>& sh, float tau2,
+                                                 W beside) {
     using C = typename CT<T>::c;
     const int t = threadIdx.x, w = t >> 6, l = t & 63;
     C* L = L2;               // the tile, then its inverse
@@ -386,6 +392,8 @@ __device__ __forceinline__ bool inv_blocked_core(int kb, typename CT<T>::c* L2, 
         gj16_wave<T>(q, thr, small);
 #pragma unroll
         for (int e = 0; e < 4; ++e) L[lr * 33 + acc_row<T>(lg, e)] = q[e];
+    } else {
+        beside();
     }
     if (kb == 32) {
         __syncthreads();
