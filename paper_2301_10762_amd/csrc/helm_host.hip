@@ -292,6 +292,69 @@ struct Scratch {
     }
 };
 
+// Pinned host memory that kernels write the few words the host waits for
+// (norms, statuses) into, so that no copy follows them: a copy to pageable
+// memory is staged and took 15 to 25 us of each wait.  Blocks of 4, 64 and
+// 1024 KB are kept for reuse, at most PIN_KEEP of a size.  A block goes back
+// once its stream has been waited for.
+struct PinPool {
+    static constexpr int SIZES = 3;
+    static constexpr size_t PIN_KEEP = 16;
+    std::mutex mu;
+    std::vector<void*> free[SIZES];
+    static size_t bytes_of(int k) { return (size_t)4096 << (k == 0 ? 0 : k == 1 ? 4 : 8); }
+};
+PinPool g_pins;
+struct HostBlock {
+    hipStream_t st;
+    void* p = nullptr;
+    int kind = -1;
+    bool waited = true;
+    explicit HostBlock(hipStream_t s) : st(s) {}
+    HostBlock(const HostBlock&) = delete;
+    HostBlock& operator=(const HostBlock&) = delete;
+    ~HostBlock() {
+        if (!p) return;
+        if (!waited) (void)hipStreamSynchronize(st);
+        if (kind >= 0) {
+            std::lock_guard<std::mutex> lk(g_pins.mu);
+            if (g_pins.free[kind].size() < PinPool::PIN_KEEP) {
+                g_pins.free[kind].push_back(p);
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+    // bytes > 0; the memory is the device's to write from here to wait()
+    template <typename T>
+    int get(T** out, size_t bytes) {
+        kind = -1;
+        for (int k = 0; k < PinPool::SIZES && kind < 0; ++k)
+            if (bytes <= PinPool::bytes_of(k)) kind = k;
+        if (kind >= 0) {
+            std::lock_guard<std::mutex> lk(g_pins.mu);
+            auto& v = g_pins.free[kind];
+            if (!v.empty()) {
+                p = v.back();
+                v.pop_back();
+            }
+        }
+        if (!p && hipHostMalloc(&p, kind >= 0 ? PinPool::bytes_of(kind) : bytes, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+            return fail(HELM_ENOMEM, "pinned host allocation failed");
+        }
+        waited = false;
+        *out = (T*)p;
+        return HELM_OK;
+    }
+    int wait() {
+        HIPCHECK(hipStreamSynchronize(st));
+        waited = true;
+        return HELM_OK;
+    }
+};
+
 // Optional live timing of the dominant kernels with HIP events: each run of
 // back-to-back launches of one kind on a stream (the panel steps of a
 // factorisation group, the steps of one forward or one backward sweep) is
@@ -353,23 +416,24 @@ Coef coef_of(const helm_factor_s* f) {
     return c;
 }
 
-// m_k > 0 and finite for every node (m in R^M_+) of each of `count`
-// models; one synchronisation for all
-int check_models(int count, const double* const* ms, const int64_t* ns, hipStream_t st) {
-    Scratch sc(st);
-    int* flag;
-    int rc = sc.get(&flag, sizeof(int));
-    if (rc) return rc;
-    launch_zero(flag, sizeof(int), st);
-    for (int c = 0; c < count; ++c) launch_check_model(ms[c], ns[c], flag, st);
+// m_k > 0 and finite for every node (m in R^M_+) of each of `count` models:
+// *flag (pinned) is nonzero after the next wait for the stream if not
+int check_models(int count, const double* const* ms, const int64_t* ns, HostBlock& hb, int** flag) {
+    if (int rc = hb.get(flag, sizeof(int))) return rc;
+    launch_zero(*flag, sizeof(int), hb.st);
+    for (int c = 0; c < count; ++c) launch_check_model(ms[c], ns[c], *flag, hb.st);
     g_launches += 1 + count;
-    int h = 0;
-    HIPCHECK(hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIPCHECK(hipStreamSynchronize(st));
-    if (h) return fail(HELM_EINVAL, "model must be finite and positive at every node");
+    HIPCHECK(hipGetLastError());
     return HELM_OK;
 }
-int check_model(const double* m, int64_t n, hipStream_t st) { return check_models(1, &m, &n, st); }
+int bad_model() { return fail(HELM_EINVAL, "model must be finite and positive at every node"); }
+int check_model(const double* m, int64_t n, hipStream_t st) {
+    HostBlock hb(st);
+    int* flag;
+    int rc = check_models(1, &m, &n, hb, &flag);
+    if (rc == HELM_OK) rc = hb.wait();
+    return rc ? rc : *flag ? bad_model() : HELM_OK;
+}
 
 // ------------------------------------------------ nested-dissection plans --
 // Panel-step launches of the block factorisation of one system.
@@ -509,7 +573,17 @@ int nd_choose(const helm_grid& g, int prec, std::shared_ptr<NdPlan>* out) {
     out->reset();
     if (block_steps(g) <= ND_MIN_STEPS || N_of(g) > ND_MAX_NODES) return HELM_OK;
     const int64_t np = pad16(g.nx);
-    return g_plans.get(g.nx, g.nz, np * np * g.nz * (int64_t)elem_bytes(prec) / 16, out);
+    int rc;
+    try {
+        rc = g_plans.get(g.nx, g.nz, np * np * g.nz * (int64_t)elem_bytes(prec) / 16, out);
+    } catch (const std::bad_alloc&) {
+        rc = HELM_ENOMEM;
+    }
+    if (rc == HELM_ENOMEM) {   // no room for a plan: the block factorisation needs none
+        out->reset();
+        return HELM_OK;
+    }
+    return rc;
 }
 
 // Factor at most ND_MAXS systems of one plan together.  zero[c] is set where
@@ -546,9 +620,12 @@ int nd_factor_group(helm_factor_s* const* fs, int n, int pivot, hipStream_t st, 
     if (tu) g_timer.end(pu, launches, st);
     g_launches += 2 + launches;
     HIPCHECK(hipGetLastError());
-    std::vector<int> hs(4 * n);
-    HIPCHECK(hipMemcpyAsync(hs.data(), status, sizeof(int) * hs.size(), hipMemcpyDeviceToHost, st));
-    HIPCHECK(hipStreamSynchronize(st));
+    HostBlock hb(st);
+    int* hs;
+    if ((rc = hb.get(&hs, sizeof(int) * 4 * n))) return rc;
+    launch_copy_words(status, hs, 4 * n, st);
+    g_launches += 1;
+    if ((rc = hb.wait())) return rc;
     for (int c = 0; c < n; ++c) {
         zero[c] = hs[4 * c];
         fs[c]->grown = hs[4 * c + 3] != 0;
@@ -650,9 +727,11 @@ int factor_group(helm_factor_s* const* fs, int n, int pivot, hipStream_t st, boo
     if (tu) g_timer.end(pu, Tmax, st);
     g_launches += 2 + (int64_t)Tmax;
     HIPCHECK(hipGetLastError());
-    std::vector<int> hs(4 * 2 * n);   // statuses (room for 2 fronts per system)
-    HIPCHECK(hipMemcpyAsync(hs.data(), status, sizeof(int) * hs.size(), hipMemcpyDeviceToHost, st));
-    HIPCHECK(hipStreamSynchronize(st));
+    HostBlock hb(st);
+    int* hs;   // statuses (room for 2 fronts per system)
+    if ((rc = hb.get(&hs, sizeof(int) * 4 * 2 * n))) return rc;
+    HIPCHECK(hipMemcpyAsync(hs, status, sizeof(int) * 4 * 2 * n, hipMemcpyDeviceToHost, st));
+    if ((rc = hb.wait())) return rc;
     for (int c = 0; c < nf; ++c)
         if (hs[4 * c])
             return fail(HELM_ESINGULAR, "zero pivot in a diagonal tile: system " + std::to_string(owner[c]) +
@@ -681,6 +760,9 @@ void destroy(helm_factor_s* f) {
 // working memory of the fronts factored in one group
 constexpr size_t ND_WORK_BYTES = (size_t)8 << 30;
 
+int factor_checked(int count, const helm_grid* grids, const double* const* m_devs, const double* omegas, int prec,
+                   hipStream_t st, helm_factor_t* outs);
+
 int factor_many(int count, const helm_grid* grids, const double* const* m_devs, const double* omegas, int prec,
                 hipStream_t st, helm_factor_t* outs) {
     if (count <= 0 || !grids || !m_devs || !omegas || !outs) return fail(HELM_EINVAL, "bad batch arguments");
@@ -693,7 +775,28 @@ int factor_many(int count, const helm_grid* grids, const double* const* m_devs, 
         if (!std::isfinite(omegas[c]) || omegas[c] < 0.0) return fail(HELM_EINVAL, "omega must be finite and >= 0");
         ns[c] = N_of(grids[c]);
     }
-    if (int rc = check_models(count, m_devs, ns.data(), st)) return rc;
+    // the models are checked on the device while the factorisation is being
+    // queued; the answer is read after its own wait and comes before any
+    // other error (a wait of its own left the GPU idle for 50 us)
+    HostBlock hb(st);
+    int* flag;
+    int rc = check_models(count, m_devs, ns.data(), hb, &flag);
+    if (rc) return rc;
+    rc = factor_checked(count, grids, m_devs, omegas, prec, st, outs);
+    if (int rw = hb.wait()) rc = rc ? rc : rw;
+    else if (*flag) {
+        if (rc == HELM_OK)
+            for (int c = 0; c < count; ++c) {
+                destroy(outs[c]);
+                outs[c] = nullptr;
+            }
+        rc = bad_model();
+    }
+    return rc;
+}
+
+int factor_checked(int count, const helm_grid* grids, const double* const* m_devs, const double* omegas, int prec,
+                   hipStream_t st, helm_factor_t* outs) {
     keep_pool_memory();
     std::vector<helm_factor_s*> fs(count, nullptr);
     auto cleanup = [&]() {
@@ -747,10 +850,13 @@ int factor_many(int count, const helm_grid* grids, const double* const* m_devs, 
             }
         std::vector<int> zero(grp.size(), 0);
         int rc = nd_factor_group(grp.data(), (int)grp.size(), g_force_pivot, st, zero.data());
-        // a zero pivot inside a box: the block factorisation, whose blocks
-        // reach the absorbing boundary, takes the system
+        // a zero pivot inside a box, or no room to work in: the block
+        // factorisation, whose blocks reach the absorbing boundary, takes the
+        // system
+        const bool room_left = rc != HELM_ENOMEM;
+        if (!room_left) rc = HELM_OK;
         for (size_t q = 0; q < grp.size() && rc == HELM_OK; ++q)
-            if (zero[q]) {
+            if (zero[q] || !room_left) {
                 g_cache.put(grp[q]->G, grp[q]->gbytes, st);
                 grp[q]->nd.reset();
                 rc = store(grp[q], block_bytes(grp[q]));
@@ -927,9 +1033,9 @@ struct SolveJob {
 };
 
 // Residual norms of several (factor, B, X) at once, max over columns of
-// ||B - A X|| / ||B||: every residual is launched, then one copy brings all
-// norms back (a copy per request held up the next launch: 30 us of idle GPU
-// each).  maxrel[c] per request.
+// ||B - A X|| / ||B||, maxrel[c] per request.  The norms are written straight
+// into pinned host memory (a copy per request held up the next launch: 30 us
+// of idle GPU each).
 struct ResidualReq {
     const helm_factor_s* f;
     const double* B;
@@ -944,11 +1050,20 @@ int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStr
     const int n = (int)rq.size();
     if (n == 0) return HELM_OK;
     Scratch sc(st);
-    double* norms;
+    HostBlock hb(st);
+    double *h, *norms;
+    std::vector<double> copy;
     size_t tot = 0;
     for (auto& r : rq) tot += 2 * (size_t)r.S;
-    std::vector<double> h(tot);
-    int rc = sc.get(&norms, sizeof(double) * tot);
+    int rc;
+    if (g_arena) {   // nothing may be allocated, pinned memory neither
+        copy.resize(tot);
+        h = copy.data();
+        rc = sc.get(&norms, sizeof(double) * tot);
+    } else {
+        rc = hb.get(&h, sizeof(double) * tot);
+        norms = h;
+    }
     if (rc) return rc;
     size_t off = 0;
     for (int c0 = 0; c0 < n; c0 += RES_MAX) {
@@ -966,8 +1081,9 @@ int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStr
         launch_norms_finish(tab, k, st);
         g_launches += 2;
     }
-    HIPCHECK(hipMemcpyAsync(h.data(), norms, sizeof(double) * tot, hipMemcpyDeviceToHost, st));
-    HIPCHECK(hipStreamSynchronize(st));
+    HIPCHECK(hipGetLastError());
+    if (g_arena) HIPCHECK(hipMemcpyAsync(h, norms, sizeof(double) * tot, hipMemcpyDeviceToHost, st));
+    if ((rc = hb.wait())) return rc;
     off = 0;
     for (int c = 0; c < n; ++c) {
         double mx = 0.0;
@@ -1010,29 +1126,42 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
         cols = (int)std::min<size_t>(smax, std::max<size_t>(1, room / (P.col_bytes() * n)));
         if (cols > 16) cols = cols / 16 * 16;
     }
-    Scratch sc(st);
     NdJobTab tab;
     std::memset(&tab, 0, sizeof(tab));
     NdJobTab* dtab;
-    int rc;
-    if ((rc = sc.get(&dtab, sizeof(NdJobTab)))) return rc;
     std::vector<double*> R(n, nullptr), part(n, nullptr);
     const int nblk = residual_blocks(N);
+    std::unique_ptr<Scratch> sc;
+    auto take = [&]() -> int {
+        int rc;
+        if ((rc = sc->get(&dtab, sizeof(NdJobTab)))) return rc;
+        for (int c = 0; c < n; ++c) {
+            NdJob& d = tab.j[c];
+            const size_t S = (size_t)std::min(js[c]->S, cols);
+            if ((rc = sc->get(&d.a, sizeof(double2) * (size_t)std::max(P.nrow_up, 1) * S))) return rc;
+            if ((rc = sc->get(&d.y, sizeof(double2) * (size_t)std::max(P.nrow, 1) * S))) return rc;
+            for (int q = 0; q < 2; ++q)
+                if ((rc = sc->get(&d.u[q], sizeof(double2) * (size_t)std::max<int64_t>(P.urows[q], 1) * S))) return rc;
+            if (correct) {
+                if ((rc = sc->get(&R[c], sizeof(double2) * (size_t)N * S))) return rc;
+                if ((rc = sc->get(&part[c], sizeof(double) * 2 * (size_t)nblk * S))) return rc;
+            }
+        }
+        return HELM_OK;
+    };
+    for (;;) {   // fewer columns at a time where memory is short
+        sc = std::make_unique<Scratch>(st);
+        const int rc = take();
+        if (rc == HELM_OK) break;
+        if (rc != HELM_ENOMEM || cols == 1) return rc;
+        cols = cols > 32 ? cols / 32 * 16 : cols > 16 ? 16 : (cols + 1) / 2;
+    }
     for (int c = 0; c < n; ++c) {
         NdJob& d = tab.j[c];
-        const size_t S = (size_t)std::min(js[c]->S, cols);
         d.cf = coef_of(js[c]->f);
         d.fac = (const double2*)js[c]->f->G;
         d.ldx = js[c]->ld;
         d.ldb = correct ? N : js[c]->ld;
-        if ((rc = sc.get(&d.a, sizeof(double2) * (size_t)std::max(P.nrow_up, 1) * S))) return rc;
-        if ((rc = sc.get(&d.y, sizeof(double2) * (size_t)std::max(P.nrow, 1) * S))) return rc;
-        for (int q = 0; q < 2; ++q)
-            if ((rc = sc.get(&d.u[q], sizeof(double2) * (size_t)std::max<int64_t>(P.urows[q], 1) * S))) return rc;
-        if (correct) {
-            if ((rc = sc.get(&R[c], sizeof(double2) * (size_t)N * S))) return rc;
-            if ((rc = sc.get(&part[c], sizeof(double) * 2 * (size_t)nblk * S))) return rc;
-        }
         g_solves += js[c]->S;
     }
     const NdTabs t = nd_tabs(P);

@@ -36,8 +36,12 @@ __global__ void k_check_model(const double* m, int64_t n, int* flag) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) {
         double v = m[i];
-        if (!(v > 0.0) || !isfinite(v)) atomicOr(flag, 1);
+        if (!(v > 0.0) || !isfinite(v)) *flag = 1;   // pinned host memory
     }
+}
+
+__global__ void k_copy_words(const int* src, int* dst, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) dst[i] = src[i];
 }
 
 __global__ void k_zero(uint32_t* p, size_t n32) {
@@ -684,6 +688,9 @@ void launch_gamma(const double* m, int nx, int nz, double alpha, double mu, doub
 }
 void launch_sum_scalar(const double* part, int n, double* out, hipStream_t st) {
     hipLaunchKernelGGL(k_sum_scalar, dim3(1), dim3(64), 0, st, part, n, out);
+}
+void launch_copy_words(const int* src, int* dst, int n, hipStream_t st) {
+    hipLaunchKernelGGL(k_copy_words, dim3(1), dim3(256), 0, st, src, dst, n);
 }
 void launch_zero(void* p, size_t bytes, hipStream_t st) {
     size_t n32 = (bytes + 3) / 4;

@@ -97,6 +97,7 @@ void launch_gamma(const double* m, int nx, int nz, double alpha, double mu, doub
                   int nblk, hipStream_t st);
 void launch_sum_scalar(const double* part, int n, double* out, hipStream_t st);
 void launch_zero(void* p, size_t bytes, hipStream_t st);
+void launch_copy_words(const int* src, int* dst, int n, hipStream_t st);   // n words, to pinned memory
 void launch_tile_inverse(int count, int kb, int pivot, const double* A, double* T, int* status, hipStream_t st);
 void launch_mfma_probe(int prec, const double* A, const double* B, double* D, hipStream_t st);
 

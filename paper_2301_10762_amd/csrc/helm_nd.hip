@@ -408,7 +408,7 @@ __device__ __forceinline__ void nd_invert(double2 (&a)[4], int kb, const NdSys& 
 // No tile is held across a barrier, so registers and latency stay low.
 // A tile's children's parts are loaded while the one before is multiplied.
 template <int KP>
-__global__ __launch_bounds__(KP == 16 ? 256 : 512) void k_nd_front(NdTabs t, int first, int parity, int fmax,
+__global__ __launch_bounds__(KP == 16 ? 256 : 512, KP == 16 ? 4 : 2) void k_nd_front(NdTabs t, int first, int parity, int fmax,
                                                                    const NdSysTab* __restrict__ stab) {
     extern __shared__ __attribute__((aligned(16))) char nd_smem[];
     constexpr int LD = KP + 1, NTH = KP == 16 ? 256 : 512, NW = NTH / 64;
