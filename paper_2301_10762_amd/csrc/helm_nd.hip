@@ -724,14 +724,16 @@ __device__ __forceinline__ void nd_update_tile(const NdFront& f, const NdSys& y,
         v4d wre[2], wim[2];
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
+            v4d q1, q2, q3;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { wre[cb][e] = 0; wim[cb][e] = 0; }
+            for (int e = 0; e < 4; ++e) { q1[e] = 0; q2[e] = 0; q3[e] = 0; }
 #pragma unroll
             for (int s8 = 0; s8 < 8; ++s8) {
                 const int k = 4 * s8 + lg;
                 const double2 av = sW[16 * w + lr][k], bv = sT[k][cb * 16 + lr];
-                cmfma<double, v4d>(wre[cb], wim[cb], av.x, av.y, bv.x, bv.y);
+                cmfma3<double, v4d>(q1, q2, q3, av.x, av.y, bv.x, bv.y);
             }
+            cacc_final<true, v4d>(q1, q2, q3, wre[cb], wim[cb]);
         }
         double2 tk[2][4];   // rows of K: T - I, read before the buffers are rewritten
 #pragma unroll
@@ -759,21 +761,23 @@ __device__ __forceinline__ void nd_update_tile(const NdFront& f, const NdSys& y,
             sV[cc][k] = vv[q];
         }
     }
-    v4d re[2][2], im[2][2];
+    v4d a1[2][2], a2[2][2], a3[2][2];
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj) {
             const int col = Cc[bj] + lr;
             const bool inK = col >= k0 && col < k0 + kb;
+            v4d re, im;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int row = R[bi] + acc_row<double>(lg, e);
                 double2 v = csel_parts(inK, make_double2(row == col ? 1.0 : 0.0, 0.0), xt[bi][bj][e]);
                 v = csel_parts(vr[bi] && vc[bj], v, zero);
-                re[bi][bj][e] = v.x;
-                im[bi][bj][e] = v.y;
+                re[e] = v.x;
+                im[e] = v.y;
             }
+            cacc_seed<true, v4d>(a1[bi][bj], a2[bi][bj], a3[bi][bj], re, im);
         }
     __syncthreads();
     for (int kk = 0; kk < kb; kk += 16) {
@@ -792,7 +796,8 @@ __device__ __forceinline__ void nd_update_tile(const NdFront& f, const NdSys& y,
 #pragma unroll
                 for (int bj = 0; bj < 2; ++bj)
                     if (vr[bi] && vc[bj])
-                        cmfma<double, v4d>(re[bi][bj], im[bi][bj], av[bi][s].x, av[bi][s].y, bv[bj][s].x, bv[bj][s].y);
+                        cmfma3<double, v4d>(a1[bi][bj], a2[bi][bj], a3[bi][bj], av[bi][s].x, av[bi][s].y, bv[bj][s].x,
+                                            bv[bj][s].y);
     }
     const bool last = step + 1 == f.npan;
     double2* fac = y.fac + f.fac;
@@ -802,10 +807,12 @@ __device__ __forceinline__ void nd_update_tile(const NdFront& f, const NdSys& y,
         for (int bj = 0; bj < 2; ++bj) {
             if (!(vr[bi] && vc[bj])) continue;
             const int col = Cc[bj] + lr;
+            v4d re, im;
+            cacc_final<true, v4d>(a1[bi][bj], a2[bi][bj], a3[bi][bj], re, im);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int row = R[bi] + acc_row<double>(lg, e);
-                const double2 g = make_double2(re[bi][bj][e], im[bi][bj][e]);
+                const double2 g = make_double2(re[e], im[e]);
                 if (!last) {
                     yst(Y + (int64_t)row * fp + col, g);
                 } else if (row < f.p) {
