@@ -3,10 +3,12 @@
 
 Workload (one "step"): the 401 x 401 layered-model configuration with five
 frequencies (1.5, 2.25, 3, 4.5, 6 Hz at 25 m spacing), 64 point sources per
-frequency: factor the five systems A(m, w) (block chains batched in shared
-launches) and solve all 5 x 64 right-hand sides to a relative residual
-<= 1e-10.  The headline form factors in complex64 on the matrix cores and
-refines in FP64; the plain FP64 form is timed beside it.
+frequency: factor the five systems A(m, w) (nested dissection, the five
+systems' fronts in shared launches) and solve all 5 x 64 right-hand sides to a
+relative residual <= 1e-10.  The headline form is the refined one (its factors
+are held in complex128 at this size, and a system is corrected when its
+residual is above a tenth of the tolerance); the plain FP64 form, which keeps
+two digits in reserve, is timed beside it.
 
 Metric: right-hand-side solves per second (5 x 64 per step / step time),
 with p50/p99 step latency.  Inputs are seeded synthetic layered models
@@ -16,9 +18,10 @@ Schedule: the K timed steps run as a pipeline of independent batches
 (paper_2301_10762_amd.pipeline): the factorisations of the next F steps run
 side by side, each on a stream of its own (F = --factor-streams, default 2:
 three batches in flight), while step k is solved on another stream; every step
-is still factored and solved in full, with the same kernels.  The serial schedule (one step at a time) is timed first and reported
-beside it, with the per-step latency percentiles and the per-kernel timings
-that the roofline figure uses.
+is still factored and solved in full, with the same kernels.  The serial
+schedule (one step at a time) is timed first and reported beside it, with the
+per-step latency percentiles and the per-kernel timings that the roofline
+figure uses.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
 """
@@ -35,10 +38,11 @@ sys.path.insert(0, ROOT)
 
 METRIC = "Helmholtz RHS solves/s at 401^2 (rel. residual<=1e-10) vs FP64 plain; p50/p99 ms"
 TOL = 1e-10
-PEAK = {"fp64": 78.6, "fp32_ir": 157.3}           # dense matrix-core TFLOP/s (MI355X)
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_factor_step_401x401_5freq_64src_fp32ir_traffic.txt")
+# dense FP64 matrix-core TFLOP/s (MI355X): nested-dissection factors are complex128 in both precisions
+PEAK = {"fp64": 78.6, "fp32_ir": 78.6}
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "nested_dissection_401x401_5freq_64src_traffic.txt")
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2301_10762_amd", "csrc", f)
-               for f in ("helm_factor.hip", "helm_device.h", "helm_internal.h")]
+               for f in ("helm_nd.hip", "helm_nd.h", "helm_nd_plan.hip", "helm_tile.h", "helm_device.h")]
 
 
 def parse():
@@ -55,8 +59,7 @@ def parse():
     p.add_argument("--factor-streams", type=int, default=2,
                    help="factorisations side by side in the pipelined schedule (2: three batches in flight)")
     p.add_argument("--fp64-factor-streams", type=int, default=1,
-                   help="the same for plain complex128 factors, whose heavier steps gain nothing from a second "
-                        "factorisation beside the first (1: two batches in flight)")
+                   help="the same for the plain FP64 form (1: two batches in flight)")
     p.add_argument("--no-extras", action="store_true",
                    help="skip the factor-only, forward+adjoint (misfit and gradient) and Gauss-Newton timings")
     p.add_argument("--profile-copy", action="store_true",
@@ -81,7 +84,7 @@ def percentile(xs, q):
 
 
 def src_sha():
-    """Digest of the sources the factorisation-step kernel is compiled from."""
+    """Digest of the sources the factorisation's kernels are compiled from."""
     h = hashlib.sha256()
     for path in KERNEL_SRCS:
         with open(path, "rb") as f:
@@ -90,9 +93,9 @@ def src_sha():
 
 
 def read_traffic(prec):
-    """HBM bytes per k_factor_step launch from the committed counter summary
+    """HBM bytes per factorisation launch from the committed counter summary
     (lines "key: value"), or None when it is missing, was taken for another
-    precision, or the kernel's sources changed since."""
+    precision, or the kernels' sources changed since."""
     if not os.path.exists(TRAFFIC_FILE):
         return None
     kv = {}
@@ -107,6 +110,27 @@ def read_traffic(prec):
         return float(kv["hbm_bytes_per_launch"])
     except (KeyError, ValueError):
         return None
+
+
+def dissection_flops(nx, nz, leaf=36):
+    """Complex multiply-adds x 8 of the nested-dissection factorisation of an
+    nx x nz grid: a box is cut across its longer side by a line of nodes until
+    it has at most `leaf` of them.  A front of p pivots and b ring nodes takes
+    p^3 + p^2 b + p b (b + 1) / 2 (inverse, R = G F, symmetric Schur
+    complement), a leaf its inverse p^3."""
+    def box(x0, x1, z0, z1):
+        w, h = x1 - x0, z1 - z0
+        if w * h <= leaf:
+            return (w * h) ** 3
+        b = w * ((z0 > 0) + (z1 < nz)) + h * ((x0 > 0) + (x1 < nx))
+        if w >= h:
+            p, s = h, x0 + (w - 1) // 2
+            inner = box(x0, s, z0, z1) + box(s + 1, x1, z0, z1)
+        else:
+            p, s = w, z0 + (h - 1) // 2
+            inner = box(x0, x1, z0, s) + box(x0, x1, s + 1, z1)
+        return inner + p ** 3 + p * p * b + p * b * (b + 1) // 2
+    return 8.0 * box(0, nx, 0, nz)
 
 
 def cpu_model():
@@ -582,12 +606,12 @@ def main():
     value = solves / total
     ms_per_step = total / args.steps * 1e3
 
-    # roofline of the dominant kernel: the factorisation (one k_factor_step
-    # launch per panel step of all the systems of a group).  Algorithmic work: the block factorisation's
-    # canonical count 8 * (4/3) * n_z * n_x^3 flops per frequency; the timed
-    # region factors all five frequencies once per step.
+    # roofline of the dominant part, the factorisation.  Algorithmic work: the
+    # dissection's own count; the timed region factors all five frequencies
+    # once per step, and a launch takes a level (or a panel step of one) of all
+    # five.
     nx, nz = w.nx, w.nz
-    factor_flops = args.steps * n_omega * 8.0 * (4.0 / 3.0) * nz * nx ** 3
+    factor_flops = args.steps * n_omega * dissection_flops(nx, nz)
     upd_ms, upd_n = kt.get("factor_step", (0.0, 0))
     flops_per_launch = factor_flops / upd_n if upd_n else float("nan")
     avg_upd_s = upd_ms / upd_n * 1e-3 if upd_n else float("nan")
@@ -595,8 +619,8 @@ def main():
     traffic = read_traffic(prec)
     roofline = {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK[prec], "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK[prec], 4), "traffic": traffic,
-                "kernel": "k_factor_step (one launch per panel step of the five factorisations), timed over "
-                          "the serial steps",
+                "kernel": "nested-dissection factorisation of the five systems (k_nd_leaf, k_nd_front, k_nd_gather, "
+                          "k_nd_step, k_nd_schur: mean over its launches), timed over the serial steps",
                 "avg_launch_us": round(avg_upd_s * 1e6, 2), "timed_launches": upd_n,
                 "flops_per_launch": flops_per_launch}
     kernels = {}
@@ -687,7 +711,7 @@ def main():
         "metric": METRIC, "value": round(value, 2), "unit": "solves/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": round(ms_per_step, 3), "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None,
-        "dtype": "c64 factor + c128 refinement" if prec == "fp32_ir" else "c128",
+        "dtype": "c128 factor + c128 refinement" if prec == "fp32_ir" else "c128",
         "data": "synthetic (seeded layered model + 5% Gaussian random field; Marmousi not available)",
         "config": {"workload": "c3_layered_401: 401x401 grid (25 m), 5 frequencies 1.5-6 Hz, 64 point sources "
                                "per frequency, all solved to rel. residual <= 1e-10",
