@@ -86,10 +86,10 @@ struct NdShape {
     int nleaf, leaf;          // leaf tiles
     int nstep, step;          // levels
     int box;                  // per node of the box: its row (z rows, then w rows)
-    int zst;                  // per z row: i, j, and the w rows left, right, above, below it (-1: none), as shorts
-    int wst;                  // per w row: i, j, and the z rows left, right, above, below it
+    // per z row beside a w row, as shorts: the row, its i, j, and the w rows
+    // left, right, above, below it (-1: none); per w row beside a z row: the same
+    int zst, nzst, wst, nwst;
     int tab0, ntab;           // all of the shape's tables
-    int pad_;
 };
 struct NdSub {
     int shape, x0, z0, w, h;

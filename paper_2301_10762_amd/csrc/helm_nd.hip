@@ -1117,29 +1117,28 @@ __device__ __forceinline__ void nd_sub_leaves(const SubCtx& x, const double2 (&g
     }
 }
 
-// v[r] += sum over r's neighbours in `from` of coupling x value (six shorts
-// per row: its i, j in the box and the neighbours' rows)
+// v[r] += sum over r's neighbours in `from` of coupling x value, for the rows
+// that have any (eight shorts each: the row, its i, j in the box and the
+// neighbours' rows, read at a valid row where there is none)
 __device__ __forceinline__ void nd_sub_stencil(const SubCtx& x, int tab, int rows, double2 (*v)[SUB_RS],
                                                const double2 (*from)[SUB_RS]) {
-    const short* st = (const short*)(x.tab + tab);
+    const double rx = x.d.cf.hz / x.d.cf.hx, rz = x.d.cf.hx / x.d.cf.hz;
     for (int q = threadIdx.x; q < 16 * rows; q += SUB_T) {
-        const int r = q >> 4, c = q & 15;
-        const short* e = st + 6 * r;
-        const double cx = x_coupling(x.d.cf, x.s.z0 + e[1]), cz = z_coupling(x.d.cf, x.s.x0 + e[0]);
-        double2 a = v[r][c];
-        bool any = false;
+        const int* e = x.tab + tab + 4 * (q >> 4);
+        const int e0 = e[0], e1 = e[1], e2 = e[2], e3 = e[3], c = q & 15;
+        const int r = e0 & 0xffff, n[4] = {e1 >> 16, (int)(short)e2, e2 >> 16, (int)(short)e3};
+        const double cx = rx * half_at_ends(x.s.z0 + (int)(short)e1, x.d.cf.nz);
+        const double cz = rz * half_at_ends(x.s.x0 + (e0 >> 16), x.d.cf.nx);
+        double2 a = v[r][c], y[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y[k] = from[max(n[k], 0)][c];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int n = e[2 + k];
-            if (n >= 0) {
-                const double2 y = from[n][c];
-                const double g = k < 2 ? cx : cz;
-                a.x += g * y.x;
-                a.y += g * y.y;
-                any = true;
-            }
+            const double g = n[k] < 0 ? 0.0 : k < 2 ? cx : cz;
+            a.x += g * (n[k] < 0 ? 0.0 : y[k].x);
+            a.y += g * (n[k] < 0 ? 0.0 : y[k].y);
         }
-        if (any) v[r][c] = a;
+        v[r][c] = a;
     }
 }
 
@@ -1195,7 +1194,7 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_forward(NdTabs t, int nsub,
         for (int p = 0; p < 4; ++p) r[p] = gld(R + min(4 * p + lg, f.p - 1));
     };
     ops(0);
-    nd_sub_stencil(x, x.h.zst, nz, z, wv);
+    nd_sub_stencil(x, x.h.zst, x.h.nzst, z, wv);
     __syncthreads();
     for (int q = 0; q < x.h.nstep; ++q) {
         const NdStep st = nd_rec<NdStep>(x.tab, x.h.step, q);
@@ -1348,7 +1347,7 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
     }
     double2 g[SUB_K];
     if (w < x.h.nleaf) nd_sub_leaf_ops(x, nd_rec<NdLeaf>(x.tab, x.h.leaf, w), g);
-    nd_sub_stencil(x, x.h.wst, x.h.nw, wv, z);
+    nd_sub_stencil(x, x.h.wst, x.h.nwst, wv, z);
     __syncthreads();
     nd_sub_leaves(x, g, wv);
     __syncthreads();

@@ -207,15 +207,21 @@ NdShape make_shape(int leaf, int w, int h, int mask, std::vector<int>& tabs) {
             const int z = zrow[at(i, j)];
             boxt[(size_t)j * w + i] = (z >= 0 ? z : S.nsep + S.nring + wrow[at(i, j)]);
         }
-    auto stencil = [&](const std::vector<int>& vi, const std::vector<int>& vj, const std::vector<int>& row) {
+    // rows with a neighbour in `row` only
+    auto stencil = [&](const std::vector<int>& vi, const std::vector<int>& vj, const std::vector<int>& row, int& count) {
         std::vector<short> t;
+        count = 0;
         for (size_t q = 0; q < vi.size(); ++q) {
             const int i = vi[q], j = vj[q];
             auto nb = [&](int a, int b) {
                 return (short)(a < -1 || a > w || b < -1 || b > h ? -1 : row[at(a, b)]);
             };
-            for (int v : {i, j}) t.push_back((short)v);
-            for (short v : {nb(i - 1, j), nb(i + 1, j), nb(i, j - 1), nb(i, j + 1)}) t.push_back(v);
+            const short n[4] = {nb(i - 1, j), nb(i + 1, j), nb(i, j - 1), nb(i, j + 1)};
+            if (n[0] < 0 && n[1] < 0 && n[2] < 0 && n[3] < 0) continue;
+            ++count;
+            for (int v : {(int)q, i, j}) t.push_back((short)v);
+            for (short v : n) t.push_back(v);
+            t.push_back(0);
         }
         std::vector<int> o(t.size() / 2);
         std::copy(t.begin(), t.end(), (short*)o.data());
@@ -234,8 +240,8 @@ NdShape make_shape(int leaf, int w, int h, int mask, std::vector<int>& tabs) {
     S.nstep = (int)steps.size();
     S.step = put_tab(tabs, steps);
     S.box = put_tab(tabs, boxt);
-    S.zst = put_tab(tabs, stencil(zi, zj, wrow));
-    S.wst = put_tab(tabs, stencil(wi, wj, zrow));
+    S.zst = put_tab(tabs, stencil(zi, zj, wrow, S.nzst));
+    S.wst = put_tab(tabs, stencil(wi, wj, zrow, S.nwst));
     S.ntab = (int)tabs.size() - S.tab0;
     return S;
 }
