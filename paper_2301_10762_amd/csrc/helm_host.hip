@@ -1186,7 +1186,6 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
             g_launches += 1;
         }
         launch_nd_put_jobs(tab, dtab, st);
-        if (P.nrow_up) launch_nd_in(t, dtab, n, P.nrow_up, wide, adjoint, st);
         KernelTimer::Pair p;
         const bool tm = g_timer.begin(2, st, &p);
         launch_nd_sub_forward(t, P, dtab, n, wide, adjoint, st);
@@ -1194,8 +1193,7 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
         for (int q = L - 1; q >= P.upper; --q) launch_nd_backward(t, P.levels[q], dtab, n, wide, st);
         launch_nd_sub_backward(t, P, dtab, n, wide, correct, adjoint, st);
         if (tm) g_timer.end(p, 2 + 2 * (L - P.upper), st);
-        if (P.nrow_up) launch_nd_out(t, dtab, n, P.nrow_up, wide, correct, adjoint, st);
-        g_launches += 5 + 2 * (L - P.upper);
+        g_launches += 3 + 2 * (L - P.upper);
     }
     HIPCHECK(hipGetLastError());
     return HELM_OK;

@@ -12,6 +12,7 @@ namespace helm {
 // take about 57 KB of LDS, so that two workgroups share a CU.
 constexpr int ND_SUB = 170;
 constexpr int ND_SUB_LEAVES = 16;   // 16-row tiles of its leaves, at most
+constexpr int ND_SUB_EXT = 224;     // nodes with the separators right of it and below it, at most
 
 // One front of the elimination tree: the p pivots of a box's separator line
 // (or all nodes of a leaf box) and the b nodes of the ring around the box,
@@ -85,7 +86,11 @@ struct NdShape {
     int w, h, nsep, nring, nw, nu;   // nu: most rows of u of a level
     int nleaf, leaf;          // leaf tiles
     int nstep, step;          // levels
-    int box;                  // per node of the box: its row (z rows, then w rows)
+    // per node of the box and of the separators right of it and below it: its
+    // row (z rows, then w rows; the nx outer ones from xrow on)
+    int box, nx, xrow;
+    int xring;                // the outer nodes' places in the ring (-1: the corner)
+    int xback;                // and z rows (xrow: the corner)
     // per z row beside a w row, as shorts: the row, its i, j, and the w rows
     // left, right, above, below it (-1: none); per w row beside a z row: the same
     int zst, nzst, wst, nwst;
@@ -93,6 +98,8 @@ struct NdShape {
 };
 struct NdSub {
     int shape, x0, z0, w, h;
+    int ew, eh;               // with the separators right of it and below it
+    int corner;               // row of the node right of and below it, or -1
     int nsep, nring;          // rows of its separators and its ring
     int row;                  // row of its first separator node
     int ring;                 // its ring's rows in the ring table
@@ -114,7 +121,8 @@ struct NdPlan {
     std::vector<NdSub> subs;
     std::vector<NdShape> shapes;
     std::vector<int> tabs;           // the shapes' tables (NdLeaf, NdFwd, NdBwd, NdStep and index tables)
-    int sub_rows = 0, sub_tab = 0;   // most z, w rows of a subtree in LDS, words of a shape's tables
+    int sub_rows = 0, sub_brows = 0; // most rows of a subtree in LDS, forward and backward
+    int sub_tab = 0;                 // words of a shape's tables
     int sub_parity = 0;
     int nrow = 0, nrow_up = 0;       // separator nodes, those above the subtrees
     int nsub = 0;
@@ -186,9 +194,6 @@ bool nd_narrow(int pmax, int fmax);
 // factorisation of one level; returns the number of launches
 int launch_nd_level(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, int n, hipStream_t st);
 // right-hand sides of the rows above the subtrees (conjugated when conj), and their solutions back: X = a, or X += a
-void launch_nd_in(const NdTabs& t, const NdJobTab* djobs, int n, int rows, int smax, bool conj, hipStream_t st);
-void launch_nd_out(const NdTabs& t, const NdJobTab* djobs, int n, int rows, int smax, bool add, bool conj,
-                   hipStream_t st);
 void launch_nd_forward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st);
 void launch_nd_backward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st);
 // the subtrees' sweeps: from B to ring contributions, and from the rings' solutions to X

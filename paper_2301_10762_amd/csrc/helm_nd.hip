@@ -942,30 +942,6 @@ __global__ __launch_bounds__(256, 2) void k_nd_schur(NdTabs t, int first, int ti
 // Backward, root first: x = G y - R x_ring.  All sums have one fixed order,
 // and no result depends on the other columns or systems of a launch.
 
-// Right-hand sides of the rows above the subtrees (conjugated for adjoint
-// solves), and their solutions back: 32 rows by 32 columns per workgroup,
-// turned in LDS.
-__global__ __launch_bounds__(256) void k_nd_in(const int* __restrict__ nodeof, int rows, int conj,
-                                               const NdJobTab* __restrict__ jtab) {
-    __shared__ double2 tile[32][33];
-    const NdJob d = nd_record(jtab->j, blockIdx.z);
-    const int r0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
-    if (c0 >= d.S) return;
-    const int n = threadIdx.x & 31, c8 = threadIdx.x >> 5, k = nodeof[min(r0 + n, rows - 1)];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        double2 v = gld(d.B + (size_t)min(c0 + c8 + 8 * q, d.S - 1) * d.ldb + k);
-        if (conj) v.y = -v.y;
-        tile[n][c8 + 8 * q] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int r = c8 + 8 * q;
-        if (r0 + r < rows && c0 + n < d.S) gst(d.a + (size_t)(r0 + r) * d.S + c0 + n, tile[r][n]);
-    }
-}
-
 __device__ __forceinline__ void nd_put_x(double2* x, double2 v, bool add) {
     if (add) {
         const double2 o = gld(x);
@@ -974,48 +950,31 @@ __device__ __forceinline__ void nd_put_x(double2* x, double2 v, bool add) {
     gst(x, v);
 }
 
-__global__ __launch_bounds__(256) void k_nd_out(const int* __restrict__ nodeof, int rows, int conj, int add,
-                                                const NdJobTab* __restrict__ jtab) {
-    __shared__ double2 tile[32][33];
-    const NdJob d = nd_record(jtab->j, blockIdx.z);
-    const int r0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
-    if (c0 >= d.S) return;
-    const int n = threadIdx.x & 31, c8 = threadIdx.x >> 5;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int r = c8 + 8 * q;
-        tile[r][n] = gld(d.a + (size_t)min(r0 + r, rows - 1) * d.S + min(c0 + n, d.S - 1));
-    }
-    __syncthreads();
-    const int k = nodeof[min(r0 + n, rows - 1)];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int c = c0 + c8 + 8 * q;
-        if (r0 + n < rows && c < d.S) {
-            double2 v = tile[n][c8 + 8 * q];
-            if (conj) v.y = -v.y;
-            nd_put_x(d.X + (size_t)c * d.ldx + k, v, add);
-        }
-    }
-}
-
 // ------------------------------------------------------------------ subtrees --
 // One workgroup sweeps a subtree (a box of about 12 x 12 nodes: four leaves,
 // three separators) with 16 columns of vectors in LDS, so that the bottom
 // levels cost one launch and one pass over the right-hand sides instead of a
 // launch and a round trip of ring contributions per level (401^2, 64 columns,
-// 5 systems: forward levels of 415 + 659 + 411 us).  It takes several blocks
-// of 16 columns in turn: the tables and a leaf tile of G per wavefront stay,
-// the next block's right-hand sides are loaded while this one is swept, and
-// the factor's other operands come from the XCD's L2 a phase ahead (with one
-// block per workgroup every phase waited for its tables and operands: 29 us
-// per workgroup, 1164 us in all).  Workgroup b runs on XCD b % 8: the column
-// blocks of a subtree follow one another on one XCD.
+// 5 systems: forward levels of 415 + 659 + 411 us).  It also moves the upper
+// separators' right-hand sides and solutions, those right of its box and
+// below it, which extend the runs it reads and writes (a launch of its own
+// each way took 110 and 144 us there).
+// Two workgroups share a compute unit.  What bounds them is their own phases,
+// not memory: with every load of right-hand sides and operands and every
+// store left out they took 278 of 345 us forward and 370 of 535 us backward
+// (201^2, four systems of 256 columns), the matrix cores being busy for about
+// half of that.  The right-hand sides, the ring's indices and the next
+// phase's operands are therefore on their way ahead of their use; a third
+// workgroup per unit (80 registers) gained nothing, and column blocks in turn
+// in one workgroup spilled.
+// Workgroup b runs on XCD b % 8: an XCD takes neighbouring subtrees, and the
+// column blocks of a subtree one after another.
 // LDS rows of 16 columns: z rows (separators, then the ring), then w rows
-// (leaf nodes).
+// (leaf nodes), then the outer nodes.
 constexpr int SUB_T = 512, SUB_W = SUB_T / 64;
 constexpr int SUB_RS = 17;                                  // LDS row: 16 columns, padded (the box goes in by nodes)
 constexpr int SUB_LD = (ND_SUB * 16 + SUB_T - 1) / SUB_T;   // (node, column) pairs per thread
+constexpr int SUB_LDX = (ND_SUB_EXT * 16 + SUB_T - 1) / SUB_T;
 constexpr int SUB_LJ = ND_SUB_LEAVES / SUB_W;               // leaf row tiles per wavefront
 constexpr int SUB_K = 9;                                    // MFMA steps (of 4) of a leaf's 36 nodes
 
@@ -1039,34 +998,34 @@ struct SubCtx {
     int c0, conj;            // first column
 };
 
-// this thread's (node, column) pairs of the box, node fastest (grid rows are
-// read along): f(i, node of the box, column)
-template <typename F>
+// this thread's (node, column) pairs of the box (EXT: with its part of the
+// upper separators), node fastest (grid rows are read along): f(pair, entry
+// of the box table, grid node, column, whether it is one)
+template <bool EXT, typename F>
 __device__ __forceinline__ void nd_sub_each(const SubCtx& x, F f) {
-    const int nb = x.s.w * x.s.h;
-    const float inv = 1.0f / (float)nb;
+    const int w = EXT ? x.s.ew : x.s.w, nb = w * (EXT ? x.s.eh : x.s.h);
+    const float inv = 1.0f / (float)nb, invw = 1.0f / (float)w;
 #pragma unroll
-    for (int i = 0; i < SUB_LD; ++i) {
-        const int e = min((int)threadIdx.x + SUB_T * i, 16 * nb - 1);
-        const int c = (int)(((float)e + 0.5f) * inv);
-        f(i, e - c * nb, c);
+    for (int q = 0; q < (EXT ? SUB_LDX : SUB_LD); ++q) {
+        const int p = (int)threadIdx.x + SUB_T * q, e = min(p, 16 * nb - 1);
+        const int c = (int)(((float)e + 0.5f) * inv), n = e - c * nb;
+        const int j = (int)(((float)n + 0.5f) * invw), i = n - j * w;
+        f(q, j * x.s.ew + i, (x.s.z0 + j) * x.d.cf.nx + x.s.x0 + i, c, p == e);
     }
 }
-__device__ __forceinline__ int nd_sub_node(const SubCtx& x, int n) {   // its grid node
-    const int j = (int)(((float)n + 0.5f) * (1.0f / (float)x.s.w));
-    return (x.s.z0 + j) * x.d.cf.nx + x.s.x0 + n - j * x.s.w;
-}
-__device__ __forceinline__ void nd_sub_fetch(const SubCtx& x, double2 (&b)[SUB_LD]) {
-    nd_sub_each(x, [&](int i, int n, int c) {
-        b[i] = gld(x.d.B + (size_t)min(x.c0 + c, x.d.S - 1) * x.d.ldb + nd_sub_node(x, n));
+template <bool EXT, int N>
+__device__ __forceinline__ void nd_sub_fetch(const SubCtx& x, double2 (&b)[N]) {
+    nd_sub_each<EXT>(x, [&](int q, int, int k, int c, bool) {
+        b[q] = gld(x.d.B + (size_t)min(x.c0 + c, x.d.S - 1) * x.d.ldb + k);
     });
 }
-// leaf nodes only if !seps
-__device__ __forceinline__ void nd_sub_place(const SubCtx& x, const double2 (&b)[SUB_LD], bool seps, double2 (*v)[SUB_RS]) {
+// EXT: every row; else the leaves' alone
+template <bool EXT, int N>
+__device__ __forceinline__ void nd_sub_place(const SubCtx& x, const double2 (&b)[N], double2 (*v)[SUB_RS]) {
     const int nz = x.h.nsep + x.h.nring;
-    nd_sub_each(x, [&](int i, int n, int c) {
+    nd_sub_each<EXT>(x, [&](int q, int n, int, int c, bool) {
         const int r = x.tab[x.h.box + n];
-        if (seps || r >= nz) v[r][c] = make_double2(b[i].x, x.conj ? -b[i].y : b[i].y);
+        if (EXT || r >= nz) v[r][c] = make_double2(b[q].x, x.conj ? -b[q].y : b[q].y);
     });
 }
 
@@ -1168,8 +1127,8 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_forward(NdTabs t, int nsub,
     SubCtx x;
     if (!nd_sub_start(t, jtab, nsub, nct, x)) return;
     x.conj = conj;
-    double2 b[SUB_LD], g[SUB_K];
-    nd_sub_fetch(x, b);
+    double2 b[SUB_LDX], g[SUB_K];
+    nd_sub_fetch<true>(x, b);
     nd_sub_tables(t, x, (int*)(sub_smem + SUB_RS * rows));
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lr = l & 15, lg = l >> 4;
     const int nz = x.h.nsep + x.h.nring, S = x.d.S, c0 = x.c0;
@@ -1179,8 +1138,14 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_forward(NdTabs t, int nsub,
     __syncthreads();
     if (w < x.h.nleaf) nd_sub_leaf_ops(x, nd_rec<NdLeaf>(x.tab, x.h.leaf, w), g);
     const double2* sfac = x.d.fac + x.s.fac;
-    nd_sub_place(x, b, true, z);
+    nd_sub_place<true>(x, b, z);
     __syncthreads();
+    // the upper rows' right-hand sides
+    for (int q = tid; q < 16 * x.h.nx; q += SUB_T) {
+        const int e = q >> 4, c = q & 15, k = x.tab[x.h.xring + e];
+        const int row = k >= 0 ? t.ring[x.s.ring + k] : x.s.corner;
+        if (c0 + c < S) gst(x.d.a + (size_t)row * S + c0 + c, z[x.h.xrow + e][c]);
+    }
     nd_sub_leaves(x, g, wv);
     __syncthreads();
     double2 r[4];   // this wavefront's operands of the next level
@@ -1261,6 +1226,7 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lr = l & 15, lg = l >> 4;
     const int S = x.d.S, c0 = x.c0, half = w & 1;
     double2 b[SUB_LD], zr[4];
+    const double2 corner = gld(x.d.a + (size_t)max(x.s.corner, 0) * S + min(c0 + (tid & 15), S - 1));
     // separator and ring rows, by 16 columns, up to four per thread ahead
     const double2* zp[4];
     const int nz = x.s.nsep + x.s.nring;
@@ -1273,7 +1239,7 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
     for (int i = 0; i < 4; ++i) zp[i] = zrow(min(tid + SUB_T * i, 16 * nz - 1));
 #pragma unroll
     for (int i = 0; i < 4; ++i) zr[i] = gld(zp[i]);
-    nd_sub_fetch(x, b);
+    nd_sub_fetch<false>(x, b);
     nd_sub_tables(t, x, (int*)(part + SUB_W / 2));
     double2 (*wv)[SUB_RS] = z + nz;
     const double2* sfac = x.d.fac + x.s.fac;
@@ -1303,7 +1269,7 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
         if (tid + SUB_T * i < 16 * nz) z[(tid + SUB_T * i) >> 4][tid & 15] = zr[i];
     for (int q = tid + 4 * SUB_T; q < 16 * nz; q += SUB_T) z[q >> 4][q & 15] = gld(zrow(q));
     first(x.h.nstep - 1);
-    nd_sub_place(x, b, false, z);
+    nd_sub_place<false>(x, b, z);
     __syncthreads();
     for (int q = x.h.nstep - 1; q >= 0; --q) {
         const NdStep st = nd_rec<NdStep>(x.tab, x.h.step, q);
@@ -1347,16 +1313,18 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
     }
     double2 g[SUB_K];
     if (w < x.h.nleaf) nd_sub_leaf_ops(x, nd_rec<NdLeaf>(x.tab, x.h.leaf, w), g);
+    if (tid < 16) z[x.h.xrow][tid] = corner;   // may lie in the sums' room, which is free now
     nd_sub_stencil(x, x.h.wst, x.h.nwst, wv, z);
     __syncthreads();
     nd_sub_leaves(x, g, wv);
     __syncthreads();
     const int nc = min(16, S - c0);
-    nd_sub_each(x, [&](int i, int n, int c) {
-        double2 v = z[x.tab[x.h.box + n]][c];
+    nd_sub_each<true>(x, [&](int, int n, int k, int c, bool own) {
+        int r = x.tab[x.h.box + n];
+        if (r >= x.h.xrow) r = x.tab[x.h.xback + r - x.h.xrow];
+        double2 v = z[r][c];
         if (conj) v.y = -v.y;
-        if (c < nc && tid + SUB_T * i < 16 * x.s.w * x.s.h)
-            nd_put_x(x.d.X + (size_t)(c0 + c) * x.d.ldx + nd_sub_node(x, n), v, add);
+        if (c < nc && own) nd_put_x(x.d.X + (size_t)(c0 + c) * x.d.ldx + k, v, add);
     });
 }
 
@@ -1609,15 +1577,6 @@ int launch_nd_level(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, in
     return 1 + lv.npan + (lv.stiles ? 1 : 0);
 }
 
-void launch_nd_in(const NdTabs& t, const NdJobTab* djobs, int n, int rows, int smax, bool conj, hipStream_t st) {
-    hipLaunchKernelGGL(k_nd_in, dim3((rows + 31) / 32, (smax + 31) / 32, n), dim3(256), 0, st, t.nodeof, rows,
-                       conj ? 1 : 0, djobs);
-}
-void launch_nd_out(const NdTabs& t, const NdJobTab* djobs, int n, int rows, int smax, bool add, bool conj,
-                   hipStream_t st) {
-    hipLaunchKernelGGL(k_nd_out, dim3((rows + 31) / 32, (smax + 31) / 32, n), dim3(256), 0, st, t.nodeof, rows,
-                       conj ? 1 : 0, add ? 1 : 0, djobs);
-}
 template <typename K>
 static dim3 nd_sub_grid(K kernel, const NdPlan& p, int nct, int n, size_t lds) {
     if (lds > 65536)
@@ -1634,9 +1593,9 @@ void launch_nd_sub_forward(const NdTabs& t, const NdPlan& p, const NdJobTab* djo
 void launch_nd_sub_backward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool add,
                             bool conj, hipStream_t st) {
     const int nct = (smax + 15) / 16;
-    const size_t lds = (size_t)p.sub_rows * SUB_RS * 16 + SUB_W / 2 * 4096 + 4 * (size_t)p.sub_tab;
+    const size_t lds = (size_t)p.sub_brows * SUB_RS * 16 + SUB_W / 2 * 4096 + 4 * (size_t)p.sub_tab;
     hipLaunchKernelGGL(k_nd_sub_backward, nd_sub_grid(k_nd_sub_backward, p, nct, n, lds), dim3(SUB_T), lds, st, t,
-                       p.nsub, nct, p.sub_rows, conj ? 1 : 0, add ? 1 : 0, djobs);
+                       p.nsub, nct, p.sub_brows, conj ? 1 : 0, add ? 1 : 0, djobs);
 }
 
 void launch_nd_forward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st) {

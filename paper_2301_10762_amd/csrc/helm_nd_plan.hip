@@ -201,12 +201,24 @@ NdShape make_shape(int leaf, int w, int h, int mask, std::vector<int>& tabs) {
         S.nu = std::max(S.nu, u);
         if (st.nbwd) steps.push_back(st);
     }
-    std::vector<int> boxt((size_t)w * h);
-    for (int j = 0; j < h; ++j)
-        for (int i = 0; i < w; ++i) {
+    // the box with the separator nodes right of it and below it, which are
+    // its part of the upper rows
+    const int ew = mask & 4 ? w + 1 : w, eh = mask & 8 ? h + 1 : h;
+    S.xrow = S.nsep + S.nring + std::max(S.nw, S.nu);
+    std::vector<int> boxt((size_t)ew * eh), xring, xback;
+    for (int j = 0; j < eh; ++j)
+        for (int i = 0; i < ew; ++i) {
             const int z = zrow[at(i, j)];
-            boxt[(size_t)j * w + i] = (z >= 0 ? z : S.nsep + S.nring + wrow[at(i, j)]);
+            int& b = boxt[(size_t)j * ew + i];
+            if (i < w && j < h) {
+                b = z >= 0 ? z : S.nsep + S.nring + wrow[at(i, j)];
+            } else {
+                b = S.xrow + (int)xring.size();
+                xring.push_back(z >= 0 ? z - S.nsep : -1);
+                xback.push_back(z >= 0 ? z : S.xrow);
+            }
         }
+    S.nx = (int)xring.size();
     // rows with a neighbour in `row` only
     auto stencil = [&](const std::vector<int>& vi, const std::vector<int>& vj, const std::vector<int>& row, int& count) {
         std::vector<short> t;
@@ -240,6 +252,8 @@ NdShape make_shape(int leaf, int w, int h, int mask, std::vector<int>& tabs) {
     S.nstep = (int)steps.size();
     S.step = put_tab(tabs, steps);
     S.box = put_tab(tabs, boxt);
+    S.xring = put_tab(tabs, xring);
+    S.xback = put_tab(tabs, xback);
     S.zst = put_tab(tabs, stencil(zi, zj, wrow, S.nzst));
     S.wst = put_tab(tabs, stencil(wi, wj, zrow, S.nwst));
     S.ntab = (int)tabs.size() - S.tab0;
@@ -322,12 +336,17 @@ bool nd_build(int nx, int nz, NdPlan* plan) {
             keys.push_back({w, h, mask, s.shape});
             P.shapes.push_back(make_shape(leaf, w, h, mask, P.tabs));
             const NdShape& S = P.shapes.back();
-            P.sub_rows = std::max(P.sub_rows, S.nsep + S.nring + std::max(S.nw, S.nu));
+            P.sub_rows = std::max(P.sub_rows, S.xrow + S.nx);
+            P.sub_brows = std::max(P.sub_brows, S.xrow);
             P.sub_tab = std::max(P.sub_tab, S.ntab);
             if (S.nleaf > ND_SUB_LEAVES) return false;
         }
         s.w = w;
         s.h = h;
+        s.ew = b.x1 < nx ? w + 1 : w;
+        s.eh = b.z1 < nz ? h + 1 : h;
+        s.corner = b.x1 < nx && b.z1 < nz ? row[b.z1 * nx + b.x1] : -1;
+        if (s.ew * s.eh > ND_SUB_EXT) return false;
         s.nsep = P.shapes[s.shape].nsep;
         s.nring = P.shapes[s.shape].nring;
         for (int r = 0; r < b.size; ++r) {   // its boxes in the shape's order
