@@ -279,9 +279,10 @@ __global__ __launch_bounds__(64 * SW_WAVES) void k_sweep(int n, int tstep, int g
 // goes back.  A row takes 1.3 us (np = 16) to 2.5 us; the matrix cores of one
 // compute unit bound it from np = 64 (complex128) or 96 (complex64) on, where
 // a launch per step, whose row tiles fill several, takes over.  Solves of 64
-// columns, launches against this, in us: complex128 48 x 60 242 / 160,
-// 64 x 90 360 / 268, 80 x 60 264 / 320; complex64 with its refinement 48 x 60
-// 555 / 300, 80 x 60 602 / 459, 96 x 60 605 / 473.
+// columns, a launch per step against this, in us: complex128 16 x 90 309 /
+// 120, 48 x 60 245 / 159, 64 x 90 366 / 267, 80 x 60 264 / 320 (the launches
+// keep it); complex64 with its refinement 48 x 60 503 / 253, 80 x 60 547 /
+// 372, 96 x 60 554 / 427, 112 x 46 440 / 442 (the launches keep it).
 // A front's row tiles times ks parts of the contraction are one wavefront
 // each; the parts are summed in order.
 constexpr int SWC_W = 16, SWC_T = 64 * SWC_W;
@@ -326,7 +327,11 @@ __global__ __launch_bounds__(SWC_T) void k_sweep_chain(const SweepTab* __restric
             v[e] = gld(src + (size_t)min(s0 + ec[e], S - 1) * ld + (size_t)j * nx + min(ei[e], nx - 1));
     };
     // this wavefront's part of a product
-    const int rt = np >> 4, ks = rt <= 4 ? 4 : 2, it = w / ks, part = w - it * ks;
+    // (five row tiles: halves of 2 and 3 chunks, placed so that no SIMD, which
+    // wavefront w runs on by w % 4, gets more than 7 of the 25)
+    const int rt = np >> 4, ks = rt <= 4 ? 4 : 2;
+    const int it = ks == 4 ? w >> 2 : w < rt ? w : rt == 5 && w == 8 ? rt : w - rt - (rt == 5 && w > 8 ? 1 : 0);
+    const int part = ks == 4 ? w & 3 : w < rt ? 1 : 0;
     const int cb = part * rt / ks, ce = it < rt ? (part + 1) * rt / ks : cb;
     C g[CN][4];
     auto gload = [&](int c, int j) {
@@ -401,7 +406,7 @@ __global__ __launch_bounds__(SWC_T) void k_sweep_chain(const SweepTab* __restric
         if (it < rt) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                red[w][acc_row<T>(lg, e)][lr] = mk<C>(p1[e] - p2[e], p3[e] - p1[e] - p2[e]);
+                red[it * ks + part][acc_row<T>(lg, e)][lr] = mk<C>(p1[e] - p2[e], p3[e] - p1[e] - p2[e]);
         }
         // what the next step needs beside its factor block
         if (FWD) fetch(ahead, Bv, d.ldb, min(max(jn + d.dir, 0), d.nz - 1));

@@ -308,7 +308,7 @@ class Factor:
 
 
 def factor(grid: Grid, m, omega: float, precision="fp64", stream=None) -> Factor:
-    """Factor A(m, w) on the GPU (block-tridiagonal LU, one block per grid row)."""
+    """Factor A(m, w) on the GPU (nested dissection; small and narrow grids row by row)."""
     md = _dev_f64(m, grid.N)
     h = _vp()
     _check(lib().helm_factor(ctypes.byref(grid.c()), _ptr(md), float(omega), _PREC[precision], _stream(stream),
@@ -317,7 +317,7 @@ def factor(grid: Grid, m, omega: float, precision="fp64", stream=None) -> Factor
 
 
 def factor_batch(grids, ms, omegas, precision="fp64", stream=None) -> list:
-    """Factor several systems with their block chains sharing kernel launches."""
+    """Factor several systems; those on one grid share kernel launches."""
     n = len(omegas)
     grids = list(grids) if not isinstance(grids, Grid) else [grids] * n
     mds = [_dev_f64(m, g.N) for m, g in zip(ms, grids)]

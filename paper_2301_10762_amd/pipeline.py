@@ -1,10 +1,10 @@
 """Batches in flight: the factorisation of later batches runs while batch k
 is solved.
 
-Both phases of one batch are latency-bound chains of small launches (one
-launch per panel step of the block factorisation, one per block row of a
-sweep), and neither fills the GPU: a factor step keeps about two
-workgroups per compute unit busy, a sweep step four.  Independent batches
+Both phases of one batch are chains of dependent launches (a launch per level
+and panel step of the factorisation, per level of a sweep), many of them too
+small to fill the GPU: the levels near the root of a nested-dissection tree
+keep fewer workgroups busy than there are compute units.  Independent batches
 (the frequencies of different models, or successive requests) can therefore
 share the GPU: batch k+1 (and with factor_streams = f > 1, batches up to
 k+f, side by side) is factored while batch k is solved on another stream,
