@@ -43,7 +43,7 @@ struct NdFront {
 };
 static_assert(sizeof(NdFront) % 8 == 0, "fronts are read as whole words");
 
-// a 64 x 64 tile of a front's pivot rows or (ti <= tj) of its ring, or a 16-row tile of
+// a 32 x 64 tile of a front's pivot rows or (ti <= tj) a 64 x 64 one of its ring, or a 16-row tile of
 // a front's sweep product; front: index within the level
 struct NdTile {
     int front;
@@ -56,7 +56,7 @@ struct NdLevel {
     bool leaf;                // the leaves
     bool small;               // narrow fronts: one workgroup each
     int npan;                 // panels of the front with most
-    int tile0, tiles;         // 64 x 64 tiles of the pivot rows (wide fronts)
+    int tile0, tiles;         // 32 x 64 tiles of the pivot rows (wide fronts)
     int stile0, stiles;       // and of the rings' upper halves
     // levels above the subtrees
     int frow0, frows, frt;    // forward sweep: groups of frt 16-row tiles of the rings

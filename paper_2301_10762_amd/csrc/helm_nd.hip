@@ -545,7 +545,7 @@ __global__ __launch_bounds__(256) void k_nd_gather(NdTabs t, int first, int coun
     const NdTile tl = lead ? NdTile{b, 0, 0} : nd_record(t.tiles, tile0 + b - count);
     const NdFront f = nd_record(t.fronts, first + tl.front);
     const NdKids kids = nd_kids(t, f, y, parity);
-    const int I0 = TILE * tl.ti, J0 = TILE * tl.tj;
+    const int I0 = KB * tl.ti, J0 = TILE * tl.tj;
     if (tid < 64) sr[tid] = nd_index(t, f, kids, y.cf, min(I0 + tid, f.fp - 1));
     else if (tid < 128) sc[tid - 64] = nd_index(t, f, kids, y.cf, min(J0 + tid - 64, f.fp - 1));
     __syncthreads();
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(256) void k_nd_gather(NdTabs t, int first, int coun
     double2* X = nd_rows(f, work, 0);
     const int cc = tid & 63, col = J0 + cc;
 #pragma unroll 4
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < 8; ++q) {
         const int rr = (tid >> 6) + 4 * q, row = I0 + rr;
         if (row < f.pp && col < f.fp) gst(X + (int64_t)row * f.fp + col, nd_entry(kids, true, sr[rr], sc[cc]));
     }
@@ -578,9 +578,9 @@ __device__ __forceinline__ void nd_next_tile(const NdFront& f, const NdSys& y, i
     double2 (*sA)[33] = (double2(*)[33])smem;                            // X_K'K
     double2 (*sT)[33] = (double2(*)[33])(smem + 1 * 32 * 33 * 16);       // T, then the inversion buffers
     double2 (*sB)[33] = (double2(*)[33])(smem + 2 * 32 * 33 * 16);       // X_KK'
-    double2 (*sP)[33] = (double2(*)[33])(smem + 3 * 32 * 33 * 16);       // X_K'K T
-    NdScratch& sh = *(NdScratch*)(smem + 4 * 32 * 33 * 16);
-    RowScratch<double>& rs = sh.row;
+    double2 (*sP)[33] = sT;                                              // X_K'K T, once T is read
+    NdScratch& sh = *(NdScratch*)sB;                                     // for the pivoted inverse, at the end
+    RowScratch<double>& rs = *(RowScratch<double>*)(smem + 3 * 32 * 33 * 16);
     const int t = threadIdx.x, w = t >> 6, l = t & 63, lr = l & 15, lg = l >> 4, wr = w >> 1, wc = w & 1;
     double2 tl[4], xa[4], xb[4], xz[4];
 #pragma unroll
@@ -620,6 +620,7 @@ __device__ __forceinline__ void nd_next_tile(const NdFront& f, const NdSys& y, i
         const double2 x = sA[16 * wr + lr][4 * s8 + lg], v = sT[4 * s8 + lg][16 * wc + lr];
         cmfma<double, v4d>(pr, pim, x.x, x.y, v.x, v.y);
     }
+    __syncthreads();
 #pragma unroll
     for (int e = 0; e < 4; ++e) sP[16 * wr + acc_row<double>(lg, e)][16 * wc + lr] = make_double2(-pr[e], -pim[e]);
     __syncthreads();
@@ -660,31 +661,31 @@ __device__ __forceinline__ void nd_next_tile(const NdFront& f, const NdSys& y, i
     nd_grown(y, nd_max2(q), act);
 }
 
-// One 64 x 64 tile of a panel step on the pivot rows: Y = X' + W V with
+// One 32 x 64 tile of a panel step on the pivot rows: Y = X' + W V with
 // W = [-X_IK T; T - I on rows of K], V = X_KJ (V_KK = I), X' = X with the K
 // columns cleared (X'_KK = I).  The last panel writes to the factor store.
 __device__ __forceinline__ void nd_update_tile(const NdFront& f, const NdSys& y, int step, int ti, int tj,
                                                const double2* X, double2* Y, const double2* Tcur, char* smem) {
     const int fp = f.fp, pp = f.pp, k0 = step * KB, kb = min(KB, pp - k0);
-    const int I0 = ti * TILE, J0 = tj * TILE;
+    const int I0 = ti * KB, J0 = tj * TILE;
     const int t = threadIdx.x, w = t >> 6, l = t & 63, lr = l & 15, lg = l >> 4, wr = w >> 1, wc = w & 1;
     double2 (*sW)[33] = (double2(*)[33])smem;
-    double2 (*sV)[33] = (double2(*)[33])(smem + 64 * 33 * 16);
+    double2 (*sV)[33] = (double2(*)[33])(smem + 32 * 33 * 16);
     double2 (*sT)[33] = sV;   // T shares the V buffer until W is formed
-    int R[2], Cc[2];
-    bool vr[2], vc[2];
+    const int R = I0 + 16 * wr;
+    const bool vr = R < pp;
+    int Cc[2];
+    bool vc[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        R[q] = I0 + 32 * wr + 16 * q;
         Cc[q] = J0 + 32 * wc + 16 * q;
-        vr[q] = R[q] < pp;
         vc[q] = Cc[q] < fp;
     }
-    double2 xik[8], tv[4], vv[8], xt[2][2][4];
+    double2 xik[4], tv[4], vv[8], xt[2][4];
     {
-        const int rr = t >> 2, c8 = 8 * (t & 3), row = min(I0 + rr, pp - 1);
+        const int rr = t >> 3, c4 = 4 * (t & 7), row = min(I0 + rr, pp - 1);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) xik[q] = gld(X + (int64_t)row * fp + k0 + min(c8 + q, kb - 1));
+        for (int q = 0; q < 4; ++q) xik[q] = gld(X + (int64_t)row * fp + k0 + min(c4 + q, kb - 1));
 #pragma unroll
         for (int q = 0; q < 4; ++q) tv[q] = gld(Tcur + t + 256 * q);
 #pragma unroll
@@ -693,20 +694,17 @@ __device__ __forceinline__ void nd_update_tile(const NdFront& f, const NdSys& y,
             vv[q] = gld(X + (int64_t)(k0 + min(k, kb - 1)) * fp + min(J0 + cc, fp - 1));
         }
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+        for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    xt[bi][bj][e] =
-                        gld(X + (int64_t)min(R[bi] + acc_row<double>(lg, e), pp - 1) * fp + min(Cc[bj] + lr, fp - 1));
+            for (int e = 0; e < 4; ++e)
+                xt[bj][e] = gld(X + (int64_t)min(R + acc_row<double>(lg, e), pp - 1) * fp + min(Cc[bj] + lr, fp - 1));
     }
     __builtin_amdgcn_sched_barrier(0);   // keep every load ahead of the first wait
     const double2 zero = make_double2(0.0, 0.0);
     {
-        const int rr = t >> 2, c8 = 8 * (t & 3);
+        const int rr = t >> 3, c4 = 4 * (t & 7);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) sW[rr][c8 + q] = csel_parts(I0 + rr < pp && c8 + q < kb, xik[q], zero);
+        for (int q = 0; q < 4; ++q) sW[rr][c4 + q] = csel_parts(I0 + rr < pp && c4 + q < kb, xik[q], zero);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int i = t + 256 * q, c = i >> 5, k = i & 31;
@@ -720,112 +718,95 @@ __device__ __forceinline__ void nd_update_tile(const NdFront& f, const NdSys& y,
         vv[q] = csel_parts(k < kb && col < fp, vv[q], zero);
     }
     __syncthreads();
-    {
-        v4d wre[2], wim[2];
+    {   // W: one 16 x 16 block per wavefront
+        v4d wre, wim, q1, q2, q3;
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            v4d q1, q2, q3;
+        for (int e = 0; e < 4; ++e) { q1[e] = 0; q2[e] = 0; q3[e] = 0; }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { q1[e] = 0; q2[e] = 0; q3[e] = 0; }
-#pragma unroll
-            for (int s8 = 0; s8 < 8; ++s8) {
-                const int k = 4 * s8 + lg;
-                const double2 av = sW[16 * w + lr][k], bv = sT[k][cb * 16 + lr];
-                cmfma3<double, v4d>(q1, q2, q3, av.x, av.y, bv.x, bv.y);
-            }
-            cacc_final<true, v4d>(q1, q2, q3, wre[cb], wim[cb]);
+        for (int s8 = 0; s8 < 8; ++s8) {
+            const int k = 4 * s8 + lg;
+            const double2 av = sW[16 * wr + lr][k], bv = sT[k][16 * wc + lr];
+            cmfma3<double, v4d>(q1, q2, q3, av.x, av.y, bv.x, bv.y);
         }
-        double2 tk[2][4];   // rows of K: T - I, read before the buffers are rewritten
+        cacc_final<true, v4d>(q1, q2, q3, wre, wim);
+        double2 tk[4];   // rows of K: T - I, read before the buffers are rewritten
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = I0 + 16 * w + acc_row<double>(lg, e), c = cb * 16 + lr;
-                const bool in = row >= k0 && row < k0 + kb;
-                tk[cb][e] = csel_parts(in, sT[in ? row - k0 : 0][c], zero);
-            }
+        for (int e = 0; e < 4; ++e) {
+            const int row = R + acc_row<double>(lg, e), c = 16 * wc + lr;
+            const bool in = row >= k0 && row < k0 + kb;
+            tk[e] = csel_parts(in, sT[in ? row - k0 : 0][c], zero);
+        }
         __syncthreads();
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int rl = 16 * w + acc_row<double>(lg, e), row = I0 + rl, c = cb * 16 + lr;
-                const bool in = row >= k0 && row < k0 + kb;
-                double2 v = csel_parts(in, tk[cb][e], make_double2(-wre[cb][e], -wim[cb][e]));
-                if (in && row - k0 == c) v.x -= 1.0;
-                sW[rl][c] = v;
-            }
+        for (int e = 0; e < 4; ++e) {
+            const int rl = 16 * wr + acc_row<double>(lg, e), row = I0 + rl, c = 16 * wc + lr;
+            const bool in = row >= k0 && row < k0 + kb;
+            double2 v = csel_parts(in, tk[e], make_double2(-wre[e], -wim[e]));
+            if (in && row - k0 == c) v.x -= 1.0;
+            sW[rl][c] = v;
+        }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int i = t + 256 * q, k = i >> 6, cc = i & 63;
             sV[cc][k] = vv[q];
         }
     }
-    v4d a1[2][2], a2[2][2], a3[2][2];
+    v4d a1[2], a2[2], a3[2];
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int bj = 0; bj < 2; ++bj) {
+        const int col = Cc[bj] + lr;
+        const bool inK = col >= k0 && col < k0 + kb;
+        v4d re, im;
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            const int col = Cc[bj] + lr;
-            const bool inK = col >= k0 && col < k0 + kb;
-            v4d re, im;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = R[bi] + acc_row<double>(lg, e);
-                double2 v = csel_parts(inK, make_double2(row == col ? 1.0 : 0.0, 0.0), xt[bi][bj][e]);
-                v = csel_parts(vr[bi] && vc[bj], v, zero);
-                re[e] = v.x;
-                im[e] = v.y;
-            }
-            cacc_seed<true, v4d>(a1[bi][bj], a2[bi][bj], a3[bi][bj], re, im);
+        for (int e = 0; e < 4; ++e) {
+            const int row = R + acc_row<double>(lg, e);
+            double2 v = csel_parts(inK, make_double2(row == col ? 1.0 : 0.0, 0.0), xt[bj][e]);
+            v = csel_parts(vr && vc[bj], v, zero);
+            re[e] = v.x;
+            im[e] = v.y;
         }
+        cacc_seed<true, v4d>(a1[bj], a2[bj], a3[bj], re, im);
+    }
     __syncthreads();
     for (int kk = 0; kk < kb; kk += 16) {
-        double2 av[2][4], bv[2][4];
+        double2 av[4], bv[2][4];
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
+        for (int s = 0; s < 4; ++s) {
+            av[s] = sW[16 * wr + lr][kk + 4 * lg + s];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                av[q][s] = sW[32 * wr + 16 * q + lr][kk + 4 * lg + s];
-                bv[q][s] = sV[32 * wc + 16 * q + lr][kk + 4 * lg + s];
-            }
+            for (int q = 0; q < 2; ++q) bv[q][s] = sV[32 * wc + 16 * q + lr][kk + 4 * lg + s];
+        }
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                for (int bj = 0; bj < 2; ++bj)
-                    if (vr[bi] && vc[bj])
-                        cmfma3<double, v4d>(a1[bi][bj], a2[bi][bj], a3[bi][bj], av[bi][s].x, av[bi][s].y, bv[bj][s].x,
-                                            bv[bj][s].y);
+            for (int bj = 0; bj < 2; ++bj)
+                if (vr && vc[bj]) cmfma3<double, v4d>(a1[bj], a2[bj], a3[bj], av[s].x, av[s].y, bv[bj][s].x, bv[bj][s].y);
     }
     const bool last = step + 1 == f.npan;
     double2* fac = y.fac + f.fac;
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int bj = 0; bj < 2; ++bj) {
+        if (!(vr && vc[bj])) continue;
+        const int col = Cc[bj] + lr;
+        v4d re, im;
+        cacc_final<true, v4d>(a1[bj], a2[bj], a3[bj], re, im);
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            if (!(vr[bi] && vc[bj])) continue;
-            const int col = Cc[bj] + lr;
-            v4d re, im;
-            cacc_final<true, v4d>(a1[bi][bj], a2[bi][bj], a3[bi][bj], re, im);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = R[bi] + acc_row<double>(lg, e);
-                const double2 g = make_double2(re[e], im[e]);
-                if (!last) {
-                    yst(Y + (int64_t)row * fp + col, g);
-                } else if (row < f.p) {
-                    const int c = col < pp ? (col < f.p ? col : -1) : (col - pp < f.b ? f.p + col - pp : -1);
-                    if (c >= 0) gst(fac + (int64_t)c * f.p + row, g);
-                }
+        for (int e = 0; e < 4; ++e) {
+            const int row = R + acc_row<double>(lg, e);
+            const double2 g = make_double2(re[e], im[e]);
+            if (!last) {
+                yst(Y + (int64_t)row * fp + col, g);
+            } else if (row < f.p) {
+                const int c = col < pp ? (col < f.p ? col : -1) : (col - pp < f.b ? f.p + col - pp : -1);
+                if (c >= 0) gst(fac + (int64_t)c * f.p + row, g);
             }
         }
+    }
 }
 
-__global__ __launch_bounds__(256, 2) void k_nd_step(NdTabs t, int first, int count, int tile0, int parity, int step,
+__global__ __launch_bounds__(256, 3) void k_nd_step(NdTabs t, int first, int count, int tile0, int parity, int step,
                                                     const NdSysTab* __restrict__ stab) {
-    __shared__ __attribute__((aligned(16))) char smem[4 * 32 * 33 * 16 + sizeof(NdScratch)];
+    __shared__ __attribute__((aligned(16))) char smem[3 * 32 * 33 * 16 + sizeof(RowScratch<double>)];
     const NdSys y = nd_record(stab->s, blockIdx.y);
     const int b = blockIdx.x;
     const bool lead = b < count;

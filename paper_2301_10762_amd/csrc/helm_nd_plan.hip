@@ -436,7 +436,7 @@ bool nd_build(int nx, int nz, NdPlan* plan) {
         if (!L.leaf && !L.small)
             for (int q = 0; q < L.count; ++q) {
                 const NdFront& F = P.fronts[L.first + q];
-                for (int i = 0; i < (F.pp + TILE - 1) / TILE; ++i)
+                for (int i = 0; i < (F.pp + KB - 1) / KB; ++i)
                     for (int j = 0; j < (F.fp + TILE - 1) / TILE; ++j) P.tiles.push_back({q, (short)i, (short)j});
             }
         L.tiles = (int)P.tiles.size() - L.tile0;
