@@ -604,31 +604,35 @@ __device__ __forceinline__ void nd_next_tile(const NdFront& f, const NdSys& y, i
         sA[hi][lo] = csel_parts(hi < kbn, xa[i], cz);
         sB[hi][lo] = csel_parts(lo < kbn, xb[i], cz);
     }
-    v4d zr, zi, pr, pim;
+    v4d zr, zi, pr, pim, p1, p2, p3;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int rr = 16 * wr + acc_row<double>(lg, e), cc = 16 * wc + lr;
         const double2 v = csel_parts(rr < kbn && cc < kbn, xz[e], cz);
         zr[e] = v.x;
         zi[e] = v.y;
-        pr[e] = 0.0;
-        pim[e] = 0.0;
+        p1[e] = 0.0;
+        p2[e] = 0.0;
+        p3[e] = 0.0;
     }
     __syncthreads();
 #pragma unroll
     for (int s8 = 0; s8 < 8; ++s8) {
         const double2 x = sA[16 * wr + lr][4 * s8 + lg], v = sT[4 * s8 + lg][16 * wc + lr];
-        cmfma<double, v4d>(pr, pim, x.x, x.y, v.x, v.y);
+        cmfma3<double, v4d>(p1, p2, p3, x.x, x.y, v.x, v.y);
     }
+    cacc_final<true, v4d>(p1, p2, p3, pr, pim);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 4; ++e) sP[16 * wr + acc_row<double>(lg, e)][16 * wc + lr] = make_double2(-pr[e], -pim[e]);
     __syncthreads();
+    cacc_seed<true, v4d>(p1, p2, p3, zr, zi);
 #pragma unroll
     for (int s8 = 0; s8 < 8; ++s8) {
         const double2 x = sP[16 * wr + lr][4 * s8 + lg], v = sB[4 * s8 + lg][16 * wc + lr];
-        cmfma<double, v4d>(zr, zi, x.x, x.y, v.x, v.y);
+        cmfma3<double, v4d>(p1, p2, p3, x.x, x.y, v.x, v.y);
     }
+    cacc_final<true, v4d>(p1, p2, p3, zr, zi);
     double2* L2 = &sT[0][0];   // with the X_KK' buffer behind it, once that is read
     float m2 = 0.0f;
     __syncthreads();

@@ -323,11 +323,14 @@ __device__ __forceinline__ void mm16(const typename CT<T>::c (&a)[4], const type
                                      const typename CT<T>::c (&c0)[4], T sign, typename CT<T>::c (&d)[4]) {
     using C = typename CT<T>::c;
     using V = typename CT<T>::v4;
-    V re, im;
+    constexpr bool GAUSS = sizeof(T) == 8;   // three real products per complex one in complex128
+    V re, im, a1, a2, a3;
 #pragma unroll
     for (int e = 0; e < 4; ++e) { re[e] = c0[e].x; im[e] = c0[e].y; }
+    cacc_seed<GAUSS, V>(a1, a2, a3, re, im);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) cmfma<T, V>(re, im, sign * a[e].x, sign * a[e].y, b[e].x, b[e].y);
+    for (int e = 0; e < 4; ++e) cacc<GAUSS, T, V>(a1, a2, a3, sign * a[e].x, sign * a[e].y, b[e].x, b[e].y);
+    cacc_final<GAUSS, V>(a1, a2, a3, re, im);
 #pragma unroll
     for (int e = 0; e < 4; ++e) d[e] = mk<C>(re[e], im[e]);
 }
