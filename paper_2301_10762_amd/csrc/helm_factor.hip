@@ -10,7 +10,7 @@
 // is D_j^{-1}; the same launch also writes D_{j+1} for the next block.
 //
 // One launch per panel step serves every chain of the batch.  Its
-// workgroups are the 64 x 64 output tiles of Y (each forms its rows of W
+// workgroups are the 32 x 64 output tiles of Y (each forms its rows of W
 // from X and T itself, so X and Y live in different buffers and no copy of
 // V is needed) plus one workgroup per chain that builds the diagonal tile
 // the NEXT step needs,
@@ -31,14 +31,13 @@ namespace helm {
 template <typename T>
 constexpr size_t sm_bytes() {
     using C = typename CT<T>::c;
-    constexpr size_t upd = 2 * 64 * 33 * sizeof(C), nxt = 4 * 32 * 33 * sizeof(C) + sizeof(GJScratch<T>);
+    constexpr size_t upd = (32 + 64) * 33 * sizeof(C), nxt = 4 * 32 * 33 * sizeof(C) + sizeof(GJScratch<T>);
     return upd > nxt ? upd : nxt;
 }
 
 __host__ __device__ int init_blocks(int np) { return (int)(((int64_t)np * np + 255) / 256) + 1; }
 __host__ __device__ int step_blocks(int np) {
-    const int tx = (np + TILE - 1) / TILE;
-    return tx * tx + 1;
+    return ((np + KB - 1) / KB) * ((np + TILE - 1) / TILE) + 1;
 }
 int factor_init_blocks(int np) { return init_blocks(np); }
 int factor_step_blocks(int np) { return step_blocks(np); }
@@ -295,32 +294,31 @@ __device__ __forceinline__ void next_tile(const ChainInfo& d, const PanelStep& p
 // Accumulators of the update tile's product seeded with its tile of X'
 // (identity on the panel columns K, zero outside the block)
 template <bool GAUSS, typename T, typename V, typename C>
-__device__ __forceinline__ void seed_y(V (&a1)[2][2], V (&a2)[2][2], V (&a3)[2][2], const C (&xt)[2][2][4],
-                                       const int (&R)[2], const int (&Cc)[2], const bool (&vr)[2], const bool (&vc)[2],
-                                       int k0, int kb, int lr, int lg) {
+__device__ __forceinline__ void seed_y(V (&a1)[2], V (&a2)[2], V (&a3)[2], const C (&xt)[2][4], int R,
+                                       const int (&Cc)[2], bool vr, const bool (&vc)[2], int k0, int kb, int lr,
+                                       int lg) {
     const C zero = mk<C>(0.0, 0.0);
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int bj = 0; bj < 2; ++bj) {
+        const int col = Cc[bj] + lr;
+        const bool inK = col >= k0 && col < k0 + kb;
+        V sre, sim;
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            const int col = Cc[bj] + lr;
-            const bool inK = col >= k0 && col < k0 + kb;
-            V sre, sim;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = R[bi] + acc_row<T>(lg, e);
-                C v = HELM_CSEL(inK, mk<C>(row == col ? 1.0 : 0.0, 0.0), xt[bi][bj][e]);
-                // complex128 selects part by part; complex64 keeps the branch
-                if constexpr (sizeof(T) == 8) v = HELM_CSEL(vr[bi] && vc[bj], v, zero);
-                else if (!(vr[bi] && vc[bj])) v = zero;
-                sre[e] = v.x;
-                sim[e] = v.y;
-            }
-            cacc_seed<GAUSS, V>(a1[bi][bj], a2[bi][bj], a3[bi][bj], sre, sim);
+        for (int e = 0; e < 4; ++e) {
+            const int row = R + acc_row<T>(lg, e);
+            C v = HELM_CSEL(inK, mk<C>(row == col ? 1.0 : 0.0, 0.0), xt[bj][e]);
+            // complex128 selects part by part; complex64 keeps the branch
+            if constexpr (sizeof(T) == 8) v = HELM_CSEL(vr && vc[bj], v, zero);
+            else if (!(vr && vc[bj])) v = zero;
+            sre[e] = v.x;
+            sim[e] = v.y;
         }
+        cacc_seed<GAUSS, V>(a1[bj], a2[bj], a3[bj], sre, sim);
+    }
 }
 
-// update of one 64 x 64 tile of Y
+// update of one 32 x 64 tile of Y (a 64 x 64 one takes 23 k cycles at np = 48,
+// longer than the next tile's workgroup beside it)
 template <typename T>
 __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep& ps, int ti, const typename CT<T>::c* X,
                             typename CT<T>::c* Y, const typename CT<T>::c* Tcur, char* smem) {
@@ -333,20 +331,20 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
     constexpr bool GAUSS = sizeof(T) == 8;
     const int np = d.np, kb = ps.kb, k0 = ps.k0;
     const int tiles_x = (np + TILE - 1) / TILE;
-    const int I0 = (ti / tiles_x) * TILE, J0 = (ti % tiles_x) * TILE;
+    const int I0 = (ti / tiles_x) * KB, J0 = (ti % tiles_x) * TILE;
     const int t = threadIdx.x, w = t >> 6, l = t & 63;
     const int lr = l & 15, lg = l >> 4;
     const int wr = w >> 1, wc = w & 1;
-    C (*sW)[33] = (C(*)[33])smem;                      // W rows I0..I0+63, k < kb
-    C (*sV)[33] = (C(*)[33])(smem + 64 * 33 * sizeof(C));  // V^T: sV[c][k], c = J0..J0+63
+    C (*sW)[33] = (C(*)[33])smem;                      // W rows I0..I0+31, k < kb
+    C (*sV)[33] = (C(*)[33])(smem + 32 * 33 * sizeof(C));  // V^T: sV[c][k], c = J0..J0+63
 
-    int R[2], Cc[2];
-    bool vr[2], vc[2];
+    const int R = I0 + 16 * wr;
+    const bool vr = R < np;
+    int Cc[2];
+    bool vc[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        R[q] = I0 + 32 * wr + 16 * q;
         Cc[q] = J0 + 32 * wc + 16 * q;
-        vr[q] = R[q] < np;
         vc[q] = Cc[q] < np;
     }
     const int row_b = d.row0 + d.dir * ps.j, rn = row_b + d.dir;
@@ -366,13 +364,13 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
     C (*sT)[33] = sV;   // T shares the V buffer until W is formed
     // every load is issued at a clamped (in-range) address; out-of-range and
     // identity entries are substituted afterwards
-    C xik[8], tv[4], vv[8], xt[2][2][4];
+    C xik[4], tv[4], vv[8], xt[2][4];
     const int rm = min(max(rn, 0), d.cf.nz - 1);
     const double mk2[2] = {m_at(d.cf, min(Cc[0] + lr, d.cf.nx - 1), rm), m_at(d.cf, min(Cc[1] + lr, d.cf.nx - 1), rm)};
     {
-        const int rr = t >> 2, c8 = 8 * (t & 3), row = min(I0 + rr, np - 1);
+        const int rr = t >> 3, c4 = 4 * (t & 7), row = min(I0 + rr, np - 1);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) xik[q] = gld(X + (size_t)row * np + k0 + min(c8 + q, kb - 1));
+        for (int q = 0; q < 4; ++q) xik[q] = gld(X + (size_t)row * np + k0 + min(c4 + q, kb - 1));
 #pragma unroll
         for (int q = 0; q < 4; ++q) tv[q] = gld(Tcur + t + 256 * q);   // Tt[c][k], idx = 32 c + k
 #pragma unroll
@@ -381,13 +379,10 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
             vv[q] = gld(X + (size_t)(k0 + min(k, kb - 1)) * np + min(J0 + cc, np - 1));
         }
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+        for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    xt[bi][bj][e] = gld(X + (size_t)min(R[bi] + acc_row<T>(lg, e), np - 1) * np +
-                                        min(Cc[bj] + lr, np - 1));
+            for (int e = 0; e < 4; ++e)
+                xt[bj][e] = gld(X + (size_t)min(R + acc_row<T>(lg, e), np - 1) * np + min(Cc[bj] + lr, np - 1));
     }
     __builtin_amdgcn_sched_barrier(0);   // keep every load ahead of the first wait
     NextBlock<2> nb{};
@@ -405,17 +400,16 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
         }
     }
     // Y = X' + W V, accumulated from X'.  complex128 seeds its three
-    // accumulators after the W product: across it the tile of X' (64
-    // registers) is live instead of them (96), which keeps the kernel from
-    // spilling
-    V a1[2][2], a2[2][2], a3[2][2];
+    // accumulators after the W product: the tile of X' is live across it
+    // instead of them
+    V a1[2], a2[2], a3[2];
     if constexpr (!GAUSS) seed_y<GAUSS, T>(a1, a2, a3, xt, R, Cc, vr, vc, k0, kb, lr, lg);
     // 2. X_{I,K} and T into LDS
     {
-        const int rr = t >> 2, c8 = 8 * (t & 3);
+        const int rr = t >> 3, c4 = 4 * (t & 7);
         const bool rok = I0 + rr < np;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) sW[rr][c8 + q] = HELM_CSEL(rok && c8 + q < kb, xik[q], zero);
+        for (int q = 0; q < 4; ++q) sW[rr][c4 + q] = HELM_CSEL(rok && c4 + q < kb, xik[q], zero);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int i = t + 256 * q, c = i >> 5, k = i & 31;
@@ -423,45 +417,37 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
         }
     }
     __syncthreads();
-    // 3. W_I = -X_{I,K} T (matrix cores; wave w makes rows I0+16w .. +15), T - I on rows of K
+    // 3. W_I = -X_{I,K} T (matrix cores, one 16 x 16 block per wavefront), T - I on rows of K
     {
-        V wre[2], wim[2];
+        V wre, wim, q1, q2, q3;
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            V q1, q2, q3;
+        for (int e = 0; e < 4; ++e) { q1[e] = 0; q2[e] = 0; q3[e] = 0; }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { q1[e] = 0; q2[e] = 0; q3[e] = 0; }
-#pragma unroll
-            for (int s8 = 0; s8 < 8; ++s8) {
-                const int k = 4 * s8 + lg;
-                const C av = sW[16 * w + lr][k], bv = sT[k][cb * 16 + lr];
-                cacc<true, T, V>(q1, q2, q3, av.x, av.y, bv.x, bv.y);
-            }
-            cacc_final<true, V>(q1, q2, q3, wre[cb], wim[cb]);
+        for (int s8 = 0; s8 < 8; ++s8) {
+            const int k = 4 * s8 + lg;
+            const C av = sW[16 * wr + lr][k], bv = sT[k][16 * wc + lr];
+            cacc<true, T, V>(q1, q2, q3, av.x, av.y, bv.x, bv.y);
         }
-        C tk[2][4];   // rows of K: T - I, read before the buffers are rewritten
+        cacc_final<true, V>(q1, q2, q3, wre, wim);
+        C tk[4];   // rows of K: T - I, read before the buffers are rewritten
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = I0 + 16 * w + acc_row<T>(lg, e), c = cb * 16 + lr;
-                tk[cb][e] = HELM_CSEL(row >= k0 && row < k0 + kb, sT[row - k0][c], mk<C>(0.0, 0.0));
-            }
+        for (int e = 0; e < 4; ++e) {
+            const int row = R + acc_row<T>(lg, e), c = 16 * wc + lr;
+            const bool in = row >= k0 && row < k0 + kb;
+            tk[e] = HELM_CSEL(in, sT[in ? row - k0 : 0][c], mk<C>(0.0, 0.0));
+        }
         __syncthreads();   // every wave has read X_{I,K} and T
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int rl = 16 * w + acc_row<T>(lg, e), row = I0 + rl, c = cb * 16 + lr;
-                C v;
-                if (row >= k0 && row < k0 + kb) {
-                    v = tk[cb][e];
-                    if (row - k0 == c) v.x -= (T)1;
-                } else {
-                    v = mk<C>(-wre[cb][e], -wim[cb][e]);
-                }
-                sW[rl][c] = v;
+        for (int e = 0; e < 4; ++e) {
+            const int rl = 16 * wr + acc_row<T>(lg, e), row = I0 + rl, c = 16 * wc + lr;
+            C v;
+            if (row >= k0 && row < k0 + kb) {
+                v = tk[e];
+                if (row - k0 == c) v.x -= (T)1;
+            } else {
+                v = mk<C>(-wre[e], -wim[e]);
             }
+            sW[rl][c] = v;
         }
         // V_J into LDS, transposed (V_KK = I)
 #pragma unroll
@@ -474,55 +460,48 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
     __syncthreads();
     // 4. Y_IJ = X'_IJ + W_I V_J
     for (int kk = 0; kk < kb; kk += 16) {
-        C av[2][4], bv[2][4];
+        C av[4], bv[2][4];
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
+        for (int s = 0; s < 4; ++s) {
+            av[s] = sW[16 * wr + lr][kk + 4 * lg + s];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                av[q][s] = sW[32 * wr + 16 * q + lr][kk + 4 * lg + s];
-                bv[q][s] = sV[32 * wc + 16 * q + lr][kk + 4 * lg + s];
-            }
+            for (int q = 0; q < 2; ++q) bv[q][s] = sV[32 * wc + 16 * q + lr][kk + 4 * lg + s];
+        }
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                for (int bj = 0; bj < 2; ++bj)
-                    if (vr[bi] && vc[bj])
-                        cacc<GAUSS, T, V>(a1[bi][bj], a2[bi][bj], a3[bi][bj], av[bi][s].x, av[bi][s].y, bv[bj][s].x,
-                                          bv[bj][s].y);
+            for (int bj = 0; bj < 2; ++bj)
+                if (vr && vc[bj]) cacc<GAUSS, T, V>(a1[bj], a2[bj], a3[bj], av[s].x, av[s].y, bv[bj][s].x, bv[bj][s].y);
     }
     // 5. store; after the last panel also D_next = A_next - E Y E, into the
     //    front's next block, or into the merge block after a bottom front's
     //    last block
     auto store = [&](auto mode) {   // 0: Y alone, 1: and D_next from A's entries, 2: and from the merge block
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+        for (int bj = 0; bj < 2; ++bj) {
+            if (!(vr && vc[bj])) continue;
+            const int col = Cc[bj] + lr;
+            V gre, gim;
+            cacc_final<GAUSS, V>(a1[bj], a2[bj], a3[bj], gre, gim);
+            C am[4];
+            if (mode == 2) {
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj) {
-                if (!(vr[bi] && vc[bj])) continue;
-                const int col = Cc[bj] + lr;
-                V gre, gim;
-                cacc_final<GAUSS, V>(a1[bi][bj], a2[bi][bj], a3[bi][bj], gre, gim);
-                C am[4];
-                if (mode == 2) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) am[e] = gld(Asrc + (size_t)(R[bi] + acc_row<T>(lg, e)) * np + col);
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int row = R[bi] + acc_row<T>(lg, e);
-                    const C g = mk<C>(gre[e], gim[e]);
-                    // the finished inverse goes to the sweeps' operand layout
-                    yst(Y + (ps.last_panel ? (sizeof(T) == 4 ? a_tiled4(row, col, np) : a_tiled(row, col, np))
-                                           : (size_t)row * np + col),
-                        g);
-                    if (mode > 0)
-                        yst(An + (size_t)row * np + col,
-                            next_schur<C>(d.cf, nb.ez, mode == 2 ? make_double2(am[e].x, am[e].y)
-                                                                 : next_entry(d.cf, nb, bj, row, col), row, col, g));
-                }
+                for (int e = 0; e < 4; ++e) am[e] = gld(Asrc + (size_t)(R + acc_row<T>(lg, e)) * np + col);
             }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = R + acc_row<T>(lg, e);
+                const C g = mk<C>(gre[e], gim[e]);
+                // the finished inverse goes to the sweeps' operand layout
+                yst(Y + (ps.last_panel ? (sizeof(T) == 4 ? a_tiled4(row, col, np) : a_tiled(row, col, np))
+                                       : (size_t)row * np + col),
+                    g);
+                if (mode > 0)
+                    yst(An + (size_t)row * np + col,
+                        next_schur<C>(d.cf, nb.ez, mode == 2 ? make_double2(am[e].x, am[e].y)
+                                                             : next_entry(d.cf, nb, bj, row, col), row, col, g));
+            }
+        }
     };
     if (!An) store(std::integral_constant<int, 0>{});
     else if (!Asrc) store(std::integral_constant<int, 1>{});
@@ -531,7 +510,7 @@ __device__ __forceinline__ void update_tile(const ChainInfo& d, const PanelStep&
 
 // Workgroups 0 .. n-1 of a step launch prepare the next diagonal tile of
 // chains 0 .. n-1 (the critical path of the step, so they are dispatched
-// first); the rest update the 64 x 64 tiles, chain by chain (ftile0).
+// first); the rest update the 32 x 64 tiles, chain by chain (ftile0).
 // uni > 0: every chain has uni - 1 update workgroups, laid out by XCD
 // (xcd_tile); otherwise in launch order.
 // Update tile served by workgroup b (>= n) when consecutive tiles (front by

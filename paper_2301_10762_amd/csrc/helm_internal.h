@@ -8,7 +8,7 @@
 namespace helm {
 
 constexpr int MAXB = 16;   // chains (independent systems) per batched launch
-constexpr int TILE = 64;   // output tile of the rank-kb update (64 x 64)
+constexpr int TILE = 64;   // columns of an output tile of a panel step (KB rows), sides of a Schur tile
 constexpr int KB = 32;     // panel width (columns eliminated per Gauss-Jordan step)
 
 // Everything needed to assemble A(m, w) on the fly (App. A.1).
