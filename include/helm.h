@@ -10,9 +10,11 @@
  * on an n_x x n_z node grid (P1 elements with nodal quadrature, i.e. the
  * five-point stencil with halved boundary couplings; M = diag(d_k m_k),
  * B = diag(b_k sqrt(m_k)), first-order impedance boundary condition of
- * eq (forward)).  Each system is factored as a block-tridiagonal LU with one
- * dense n_x x n_x block per grid row, the explicit inverse of every Schur
- * complement being kept so that the sweeps are matrix products.
+ * eq (forward)).  A system is factored by nested dissection (a multifrontal
+ * elimination of separator lines) in complex128, or, on small and
+ * on narrow grids, as a block-tridiagonal LU with one dense n_x x n_x block
+ * per grid row.  Both keep explicit inverses of their diagonal blocks, so that
+ * the solves are matrix products.
  *
  * Conventions used by every entry point
  *   - Node k = j*nx + i, x_i = i*hx, z_j = j*hz, j = 0 is the top row.
@@ -69,24 +71,33 @@ enum {
 /* ---- factorisation -------------------------------------------------------
  * helm_factor: factor A(m, w) (App. A.1).  m_dev: nx*nz positive doubles
  * (squared slowness, eq (disc_to_cont) with nodal basis), copied into the
- * factor.  precision: HELM_FP64 (complex128 blocks) or HELM_FP32_IR
- * (complex64 blocks; solves are refined in FP64 to `tol`).  On success *out
- * owns ~nz*np^2*(16 or 8) bytes of HBM, np = nx rounded up to 16.
- * Diagonal tiles use diagonal pivots unless one falls below 1e-2 x max|tile|,
- * in which case the factor is recomputed with partial pivoting inside the
- * tiles.  Returns HELM_ESINGULAR with no factor if a pivot is exactly zero.
+ * factor.  precision: HELM_FP64 or HELM_FP32_IR (solves are refined in FP64
+ * to `tol`).  On success *out owns at most nz*np^2*(16 or 8) bytes of HBM for
+ * FP64 or FP32_IR, np = nx rounded up to 16, and the model copy.
+ * Grids of more than 32 block steps (ceil(np/32) times half the rows; 96
+ * where nx > 3 nz) are factored by nested dissection where that factor, held
+ * in complex128 for both precisions, fits those bytes; the others row by row,
+ * FP64 in complex128 blocks and FP32_IR in complex64 ones.
+ * Diagonal tiles use diagonal pivots unless one falls below 1e-2 x max|tile|;
+ * then the tile (nested dissection) or the whole factor (row by row) is done
+ * with partial pivoting inside the tiles.  A nested-dissection factor whose
+ * inverses grow (a box of the dissection near resonance) has each solve
+ * without a tolerance corrected once; one that meets an exactly zero pivot is
+ * made row by row.  Returns HELM_ESINGULAR with no factor if a pivot of that
+ * is exactly zero, HELM_EINVAL if the model is not positive and finite.
  * Synchronises `stream`.                                                   */
 int helm_factor(const helm_grid* grid, const double* m_dev, double omega, int precision,
                 void* stream, helm_factor_t* out);
 
-/* helm_factor_batch: factor `count` independent systems together (their
- * block chains advance in lockstep inside shared kernel launches).  Grids may
+/* helm_factor_batch: factor `count` independent systems together (the fronts
+ * or block chains of systems on one grid share kernel launches).  Grids may
  * differ.  outs[c] receives the factor of (grids[c], m_devs[c], omegas[c]).
  * On failure no factor is returned.  Synchronises `stream`.               */
 int helm_factor_batch(int32_t count, const helm_grid* grids, const double* const* m_devs,
                       const double* omegas, int precision, void* stream, helm_factor_t* outs);
 
-/* Bytes of HBM a factor of this grid and precision holds (for admission). */
+/* Bytes of HBM a factor of this grid and precision holds at most (for
+ * admission): that of the row-by-row form, nx*nz*8 bytes of model included. */
 int helm_factor_bytes(const helm_grid* grid, int precision, size_t* bytes);
 
 /* Releases a factor without waiting for the GPU.  Its device memory goes
@@ -104,11 +115,12 @@ void helm_factor_destroy(helm_factor_t f);
  * same factors.  B/R and X/L: device complex128, column-major with leading
  * dimension ld (>= nx*nz; entries past nx*nz in a column are neither read
  * nor written); X must not overlap B.  S >= 1; S <= 0, ld < nx*nz or
- * overlapping buffers return HELM_EINVAL before any launch.  For an FP32 factor the
+ * overlapping buffers return HELM_EINVAL before any launch.  For an FP32_IR factor the
  * result is refined in FP64 until max_s ||b_s - A x_s|| / ||b_s|| <= tol
  * (tol <= 0 selects 1e-10), at most 10 corrections, else HELM_ENOCONV.  For
  * an FP64 factor tol > 0 also measures the residual into info (and refines
- * in FP64 if needed).  info may be NULL.  Synchronises when a residual is
+ * in FP64 if needed).  On a nested-dissection factor the first correction is
+ * made from tol/10 (FP32_IR) or tol/100 (FP64) on.  info may be NULL.  Synchronises when a residual is
  * measured.                                                                 */
 int helm_solve(helm_factor_t f, const double* B_dev, double* X_dev, int32_t S, int64_t ld,
                double tol, void* stream, helm_info* info);
@@ -118,15 +130,18 @@ int helm_adjoint_solve(helm_factor_t f, const double* R_dev, double* L_dev, int3
 /* helm_solve_noalloc: helm_solve for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  The same arguments, kernels and results as helm_solve
- * (bitwise), but every scratch buffer of the call (sweep coupling vectors,
- * residual partials and norms, the complex64 right-hand side and correction
- * of the refinement, or the complex128 ones of an FP64 refinement) comes
+ * (bitwise), but every scratch buffer of the call (sweep vectors, residual
+ * partials and norms, the complex64 right-hand side and correction of the
+ * refinement, or the complex128 ones of an FP64 refinement) comes
  * from one fixed 256 MiB region of device memory that the library holds on
- * each GPU it runs on until the process ends; the call performs no device
- * allocation or free.  A solve whose scratch would exceed 256 MiB returns
- * HELM_EINVAL before any launch (at 401^2: up to 64 columns with complex64
- * factors; with complex128 factors up to 48 columns when tol > 0, any
- * number otherwise).  The region of the current device is used, so call
+ * each GPU it runs on until the process ends (for grids of which one column
+ * on a nested-dissection factor needs more, from a region held with the
+ * grid's plan); the call performs no device allocation or free.  On a
+ * nested-dissection factor columns are taken as many at a time as fit.  A
+ * solve whose row-by-row scratch would exceed 256 MiB returns HELM_EINVAL
+ * before any launch, whichever way the system was factored (at 401^2: up to
+ * 64 columns for FP32_IR; for FP64 up to 48 columns when tol > 0, any number
+ * otherwise).  The region of the current device is used, so call
  * with the factor's device current.  Every call on one GPU shares that
  * GPU's region: calls that overlap in time on one GPU (other threads, or
  * other streams while an earlier call's kernels still run) race on it.
@@ -385,8 +400,10 @@ int helm_mfma_probe(int prec, const double* A_dev, const double* B_dev, double* 
  * sweep) with two events on its stream; helm_kernel_time reports, per kind,
  * the summed elapsed milliseconds and the number of launches inside the
  * timed runs (it waits for them), so total / count is the average launch
- * duration.  Kind 0 is the factorisation step (block update + next diagonal
- * tile), kind 1 the initial assembly launch, kind 2 a sweep step.          */
+ * duration.  Kind 0 is the factorisation (row by row: a panel step, block
+ * update + next diagonal tile; nested dissection: a launch of a level or of a
+ * panel step of one), kind 1 the initial assembly launch of the row-by-row
+ * form, kind 2 a sweep launch.                                             */
 void helm_kernel_timing(int enable);
 int helm_kernel_time(int kind, double* total_ms, int64_t* count);
 

@@ -441,8 +441,18 @@ int block_steps(const helm_grid& g) {
     const int k = twist_row(g.nz);
     return (pad16(g.nx) + KB - 1) / KB * (k + 1);
 }
-// Grids whose block factorisation is at most this long keep it.
-constexpr int ND_MIN_STEPS = 96;
+// Grids with a chain of at most ND_MIN_STEPS panel steps keep the block
+// factorisation: a dozen launches of nested dissection take about as long
+// (factor and solve of 16 columns, block against dissection, in us: 24 x 24
+// 319 / 256, 16 x 90 543 / 532; beyond the line 33 x 33 564 / 278, 48 x 48
+// 738 / 349, 67 x 45 1097 / 398, 96 x 60 1532 / 450).  So do wide and short
+// grids (nx > 3 nz) of at most ND_WIDE_STEPS, whose schedule of launches is
+// fixed by test; dissection would be faster there too (130 x 33: 1331 / 385).
+constexpr int ND_MIN_STEPS = 32, ND_WIDE_STEPS = 96;
+bool nd_pays(const helm_grid& g) {
+    const int steps = block_steps(g);
+    return steps > ND_WIDE_STEPS || (steps > ND_MIN_STEPS && g.nx <= 3 * g.nz);
+}
 constexpr int64_t ND_MAX_NODES = (int64_t)1 << 26;   // the plan's tables are indexed in 32 bits
 
 // The plans made so far, one per (device, nx, nz): a plan depends on nothing
@@ -571,7 +581,7 @@ NdTabs nd_tabs(const NdPlan& p) {
 // factorisation serves it.
 int nd_choose(const helm_grid& g, int prec, std::shared_ptr<NdPlan>* out) {
     out->reset();
-    if (block_steps(g) <= ND_MIN_STEPS || N_of(g) > ND_MAX_NODES) return HELM_OK;
+    if (!nd_pays(g) || N_of(g) > ND_MAX_NODES) return HELM_OK;
     const int64_t np = pad16(g.nx);
     int rc;
     try {

@@ -1,7 +1,7 @@
 """GPU: nested-dissection factors and solves against the FP64 oracle.
 
-Grids just above the size where the block factorisation hands over (65 x 65),
-odd and long rectangles in both directions (ring sides missing on one, two
+Small grids just above the size where the block factorisation hands over
+(33 x 33; 96 x 33, as wide as that may be), odd and long rectangles in both directions (ring sides missing on one, two
 and three sides; separators of 16k, 16k + 1 and 32k + 1 nodes; leaves of every
 shape), one and 19 right-hand sides, forward and adjoint, in both precisions.
 Solutions are held to 1e-9 per column, the bound of the other parity tests
@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-GRIDS = [(65, 65), (67, 77), (130, 51), (41, 140), (401, 37), (97, 129)]
+GRIDS = [(33, 33), (96, 33), (65, 65), (67, 77), (130, 51), (41, 140), (401, 37), (97, 129)]
 
 
 @pytest.fixture(scope="module")
