@@ -553,6 +553,7 @@ __global__ __launch_bounds__(256, 2) void k_factor_step(int n, int tstep, int un
     const C* Tcur = (const C*)d.Tb + (size_t)(tstep & 1) * KB * KB;
     C* Tnext = (C*)d.Tb + (size_t)((tstep + 1) & 1) * KB * KB;
     if (nxt) {
+        __builtin_amdgcn_s_setprio(3);   // ahead of the update tiles that share its compute unit
         next_tile<T>(d, ps, X, Tcur, Tnext, smem);
     } else {
         update_tile<T>(d, ps, u - d.ftile0, X, Y, Tcur, smem);

@@ -204,8 +204,11 @@ __device__ __noinline__ int nd_pivoted(double2* S, double2* D, int ld, int n) {
 //     W_I = -C_I T,  M_IJ += s_J W_I C_J^T,  M_IK = W_I,  M_KJ = -s_J W_J^T,
 //     M_KK = T.
 // Panels may be taken in any order: a tile that is nearly singular by itself
-// waits until the others are eliminated.  Bound by the chain of tile
-// inverses (about 2.5 us each); six wavefronts per CU hide it.
+// waits until the others are eliminated.  A single leaf is a chain of three
+// tile inverses (6 k of its 33 k cycles each, 27 us a launch at 101^2); many
+// are bound by vector instructions, two wavefronts to a SIMD: 20480 leaves of
+// 36 nodes take 420 us, whose factor is 425 MB to write (94 us at the rate of
+// a copy).
 constexpr int LT = 3;
 __global__ __launch_bounds__(64, 2) void k_nd_leaf(NdTabs t, int first, const NdSysTab* __restrict__ stab) {
     constexpr int NTT = LT * (LT + 1) / 2;
@@ -400,13 +403,18 @@ __device__ __forceinline__ void nd_invert(double2 (&a)[4], int kb, const NdSys& 
 
 // ------------------------------------------------------------- narrow fronts --
 // A front of at most 32 pivots in one workgroup.  The pivot block is inverted
-// whole (G), the couplings F^T (one row per ring node) are gathered beside it and stay in LDS; each
-// wavefront then takes rows of ring tiles by itself: R_I = G F_I, whose
-// accumulators are also the A operand of the next product (the FP64 result
-// holds rows g + 4 e of column r in lane 16 g + r), so for the tiles J >= I
-// the children's part minus R_I^T F_J goes straight to the Schur complement.
-// No tile is held across a barrier, so registers and latency stay low.
-// A tile's children's parts are loaded while the one before is multiplied.
+// whole (G); beside it the couplings F^T (one row per ring node) are gathered
+// into LDS.  Each wavefront then takes rows of ring tiles by itself:
+// R_I = G F_I, whose accumulators are also the A operand of the next product
+// (the FP64 result holds rows g + 4 e of column r in lane 16 g + r), so for
+// half of the tiles J of the symmetric complement the children's part minus
+// R_I^T F_J goes straight there.  No tile is held across a barrier, so
+// registers and latency stay low; a tile's children's parts are loaded while
+// the one before is multiplied.
+// One front is bound by that chain: 90 k cycles at p = 25 when the couplings
+// were gathered first and wavefront I took all J >= I, 70 k now (101^2: two
+// launches 91 us, now 70).  401^2, 5 systems: two 32-wide levels 459 us, now
+// 405; three 16-wide ones 641, now 500, with four workgroups to a compute unit.
 template <int KP>
 __global__ __launch_bounds__(KP == 16 ? 256 : 512, KP == 16 ? 4 : 2) void k_nd_front(NdTabs t, int first, int parity, int fmax,
                                                                    const NdSysTab* __restrict__ stab) {
@@ -525,6 +533,12 @@ __global__ __launch_bounds__(KP == 16 ? 256 : 512, KP == 16 ? 4 : 2) void k_nd_f
 // once.  (Eliminating the whole front panel by panel rewrote it p / 32
 // times: 118 us a panel at 80 fronts with p = 100, b = 400, 3.7 TB/s.)
 // Working memory: the gathered rows, kept for F, then two buffers in turn.
+// A launch takes the next diagonal tile's inverse in a workgroup of its own
+// beside the update tiles.  That chain (26 k cycles: loads, two products, the
+// inverse) bounds the levels near the root, 12.5 us a panel at 401^2; with
+// many fronts the update tiles do, in 32 x 64 so that three share a compute
+// unit (5 systems of 401^2, 39 steps: 1314 us in 64 x 64 tiles of four real
+// products, 1132 now).
 __device__ __forceinline__ double2* nd_rows(const NdFront& f, double2* work, int step) {
     const int64_t n = (int64_t)f.pp * f.fp;
     return work + f.work + (step == 0 ? 0 : n * (1 + (step & 1)));
@@ -821,6 +835,8 @@ __global__ __launch_bounds__(256, 3) void k_nd_step(NdTabs t, int first, int cou
     const double2* X = nd_rows(f, work, step);
     const double2* Tcur = nd_tslot(f, work, step);
     if (lead) {
+        // ahead of the update tiles that share its compute unit
+        __builtin_amdgcn_s_setprio(3);
         if (step + 1 < f.npan) nd_next_tile(f, y, first + b, step, X, Tcur, nd_tslot(f, work, step + 1), smem);
     } else {
         nd_update_tile(f, y, step, tl.ti, tl.tj, X, nd_rows(f, work, step + 1), Tcur, smem);
@@ -829,7 +845,9 @@ __global__ __launch_bounds__(256, 3) void k_nd_step(NdTabs t, int first, int cou
 
 // Schur complement S = C - F^T R of wide fronts, one 64 x 64 tile (ti <= tj)
 // of the ring per workgroup, depth p in chunks of 32 through LDS; the next
-// chunk is loaded while this one is multiplied.
+// chunk is loaded while this one is multiplied.  401^2, 5 systems: six levels
+// 678 us, about a third of the matrix cores' rate: the gather of the
+// children's part, and two workgroups to a compute unit (240 registers).
 __global__ __launch_bounds__(256, 2) void k_nd_schur(NdTabs t, int first, int tile0, int parity,
                                                      const NdSysTab* __restrict__ stab) {
     __shared__ double2 sA[64][33], sB[64][33];   // F^T and R^T: [ring][k]
@@ -1314,6 +1332,8 @@ __global__ __launch_bounds__(SUB_T, 4) void k_nd_sub_backward(NdTabs t, int nsub
 }
 
 // -------------------------------------------------- levels above the subtrees --
+// Forward (401^2, 5 systems, 64 columns: 26 to 130 us a level, latency of the
+// gathers; one level of one system 6 us).
 // A workgroup takes RT 16-row tiles of a front's product for 16 columns; its
 // 4 / RT wavefronts per tile share the contraction and are summed in order.
 // The operand vectors, gathered from several places, are staged through LDS
@@ -1593,6 +1613,9 @@ void launch_nd_forward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs
 }
 void launch_nd_backward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st) {
     const int nct = (smax + 15) / 16;
+    // four wavefronts to a row tile where the contraction is long enough: in
+    // us, split against not, fronts above 96 rows 17 .. 69 / 30 .. 70 (401^2, 5
+    // systems), 5 / 8 .. 12 (101^2); below 57 / 47 and 5 / 7
     if (lv.fmax > 96)
         hipLaunchKernelGGL(k_nd_backward<true>, dim3(8 * ((lv.brows + 7) / 8) * nct, n), dim3(256), 0, st, t, lv.first,
                            lv.brow0, lv.brows, nct, djobs);

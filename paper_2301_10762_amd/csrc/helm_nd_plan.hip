@@ -451,7 +451,11 @@ bool nd_build(int nx, int nz, NdPlan* plan) {
         if (d < D) {
             P.upper = std::min(P.upper, (int)v);
             // few fronts: one row tile per workgroup, its wavefronts sharing
-            // the contraction (latency); many: a tile per wavefront
+            // the contraction (latency); many: a tile per wavefront, so that
+            // the gathered vectors are staged once for four.  In us, 1 row tile
+            // against 4: 16 to 256 fronts of 401^2, 5 systems, 82 .. 243 /
+            // 53 .. 127; 4 fronts of 201^2, 4 systems of 32 columns, 13 / 15;
+            // of 101^2 6 / 8
             L.frt = L.count >= 16 ? 4 : 1;
             L.frow0 = (int)P.tiles.size();
             for (int q = 0; q < L.count; ++q) {
