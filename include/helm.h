@@ -119,9 +119,10 @@ void helm_factor_destroy(helm_factor_t f);
  * result is refined in FP64 until max_s ||b_s - A x_s|| / ||b_s|| <= tol
  * (tol <= 0 selects 1e-10), at most 10 corrections, else HELM_ENOCONV.  For
  * an FP64 factor tol > 0 also measures the residual into info (and refines
- * in FP64 if needed).  On a nested-dissection factor the first correction is
- * made from tol/10 (FP32_IR) or tol/100 (FP64) on.  info may be NULL.  Synchronises when a residual is
- * measured.                                                                 */
+ * in FP64 if needed).  On a nested-dissection factor a solution is also
+ * corrected, whatever tol, until its residual is no larger than a complex128
+ * row-by-row factor would leave.  info may be NULL.  Synchronises when a
+ * residual is measured.                                                     */
 int helm_solve(helm_factor_t f, const double* B_dev, double* X_dev, int32_t S, int64_t ld,
                double tol, void* stream, helm_info* info);
 int helm_adjoint_solve(helm_factor_t f, const double* R_dev, double* L_dev, int32_t S, int64_t ld,

@@ -1045,7 +1045,12 @@ struct SolveJob {
 // Residual norms of several (factor, B, X) at once, max over columns of
 // ||B - A X|| / ||B||, maxrel[c] per request.  The norms are written straight
 // into pinned host memory (a copy per request held up the next launch: 30 us
-// of idle GPU each).
+// of idle GPU each).  excess[c] (or null): how far the residual is above what
+// the block factorisation leaves in complex128, the largest column's
+// ||r|| / (eps max(N^(1/4), 8) (c ||X|| + ||B|| / 4)), c the larger of hx/hz
+// and hz/hx.  Block factors leave eps N^(1/4) times 1.0 to 1.2 of ||X|| at 33^2
+// to 401^2, for point sources, dense right-hand sides and smooth ones (6 eps at
+// 33^2, 21 eps at 401^2), dissection without boxes near resonance 5 to 8 eps.
 struct ResidualReq {
     const helm_factor_s* f;
     const double* B;
@@ -1056,15 +1061,16 @@ struct ResidualReq {
     float* R32;     // conjugated-if-adjoint complex64 copy of r, or NULL
     int S;
 };
-int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStream_t st, double* maxrel) {
-    const int n = (int)rq.size();
+int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStream_t st, double* maxrel,
+                         double* excess = nullptr) {
+    const int n = (int)rq.size(), nn = excess ? 3 : 2;
     if (n == 0) return HELM_OK;
     Scratch sc(st);
     HostBlock hb(st);
     double *h, *norms;
     std::vector<double> copy;
     size_t tot = 0;
-    for (auto& r : rq) tot += 2 * (size_t)r.S;
+    for (auto& r : rq) tot += nn * (size_t)r.S;
     int rc;
     if (g_arena) {   // nothing may be allocated, pinned memory neither
         copy.resize(tot);
@@ -1083,9 +1089,9 @@ int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStr
             const ResidualReq& r = rq[c0 + c];
             const int64_t N = N_of(r.f->g);
             double* partial;
-            if ((rc = sc.get(&partial, sizeof(double) * 2 * (size_t)residual_blocks(N) * r.S))) return rc;
-            tab.j[c] = {coef_of(r.f), r.B, r.X, r.R, r.R32, partial, norms + off, r.ldb, r.ldx, N, r.S, 0, 0, 0};
-            off += 2 * (size_t)r.S;
+            if ((rc = sc.get(&partial, sizeof(double) * nn * (size_t)residual_blocks(N) * r.S))) return rc;
+            tab.j[c] = {coef_of(r.f), r.B, r.X, r.R, r.R32, partial, norms + off, r.ldb, r.ldx, N, r.S, nn, 0, 0};
+            off += nn * (size_t)r.S;
         }
         launch_residual(tab, k, adjoint, st);
         launch_norms_finish(tab, k, st);
@@ -1096,14 +1102,20 @@ int residual_norms_batch(const std::vector<ResidualReq>& rq, int adjoint, hipStr
     if ((rc = hb.wait())) return rc;
     off = 0;
     for (int c = 0; c < n; ++c) {
-        double mx = 0.0;
+        const helm_grid& g = rq[c].f->g;
+        const double unit = 0x1p-52 * std::max(8.0, std::sqrt(std::sqrt((double)N_of(g))));
+        const double cpl = std::max(g.hx / g.hz, g.hz / g.hx);
+        double mx = 0.0, ex = 0.0;
         for (int s = 0; s < rq[c].S; ++s) {
-            double rr = std::sqrt(h[off + 2 * s]), bb = std::sqrt(h[off + 2 * s + 1]);
-            double rel = bb > 0.0 ? rr / bb : (rr > 0.0 ? INFINITY : 0.0);
+            const double* q = h + off + nn * (size_t)s;
+            const double rr = std::sqrt(q[0]), bb = std::sqrt(q[1]);
+            const double rel = bb > 0.0 ? rr / bb : (rr > 0.0 ? INFINITY : 0.0);
             if (!(rel <= mx)) mx = rel;   // NaN propagates
+            if (excess && rr > 0.0) ex = std::max(ex, rr / (unit * (cpl * std::sqrt(q[2]) + 0.25 * bb)));
         }
         maxrel[c] = mx;
-        off += 2 * (size_t)rq[c].S;
+        if (excess) excess[c] = ex;
+        off += nn * (size_t)rq[c].S;
     }
     return HELM_OK;
 }
@@ -1187,7 +1199,7 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
             wide = std::max(wide, d.S);
             if (correct && d.S > 0) {
                 rt.j[nres++] = {d.cf, (const double*)d.B, (const double*)d.X, R[c], nullptr, part[c], nullptr,
-                                js[c]->ld, js[c]->ld, N, d.S, 0, 0, 0};
+                                js[c]->ld, js[c]->ld, N, d.S, 2, 0, 0};
                 d.B = (const double2*)R[c];
             }
         }
@@ -1208,6 +1220,14 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
     HIPCHECK(hipGetLastError());
     return HELM_OK;
 }
+
+// A nested-dissection solve with a tolerance is corrected, whatever the
+// tolerance, where its residual is above ND_EXCESS (residual_norms_batch) and
+// ND_SMALL_RES of the right-hand side: boxes of the dissection near resonance
+// cost digits, up to eight of them at 401^2, and one correction then leaves a
+// tenth of what block factors do.  (Corrections from tol/10 or tol/100 on left
+// errors of up to 2.6e-11 at 401^2, where block factors leave 2e-13.)
+constexpr double ND_EXCESS = 1.25, ND_SMALL_RES = 2e-14;
 
 // Solve jobs whose factors are nested-dissection ones (complex128 in either
 // precision), to tol where one is given or the precision implies one.
@@ -1232,7 +1252,7 @@ int nd_solve_jobs(std::vector<SolveJob*>& jobs, bool adjoint, double tol, hipStr
     std::vector<int> act(n), iters(n, 0);
     for (int c = 0; c < n; ++c) act[c] = c;
     if (int rc = sweep(act, false)) return rc;
-    std::vector<double> rels(n, -1.0);
+    std::vector<double> rels(n, -1.0), over(n, 0.0);
     int worst = HELM_OK;
     if (!(tol > 0.0)) {
         // no residual is measured: where the factor says digits were lost,
@@ -1248,17 +1268,17 @@ int nd_solve_jobs(std::vector<SolveJob*>& jobs, bool adjoint, double tol, hipStr
             std::vector<ResidualReq> rq;
             for (int c : act)
                 rq.push_back({jobs[c]->f, jobs[c]->B, jobs[c]->ld, jobs[c]->X, jobs[c]->ld, nullptr, nullptr, jobs[c]->S});
-            std::vector<double> rel(act.size());
-            if (int rc = residual_norms_batch(rq, adjoint ? 1 : 0, st, rel.data())) return rc;
+            std::vector<double> rel(act.size()), ex(act.size());
+            if (int rc = residual_norms_batch(rq, adjoint ? 1 : 0, st, rel.data(), ex.data())) return rc;
             std::vector<int> next;
             for (size_t q = 0; q < act.size(); ++q) {
                 const int c = act[q];
+                // a correction too where digits were lost, unless the last one
+                // did not halve the residual
+                const bool lost = ex[q] > ND_EXCESS && rel[q] > ND_SMALL_RES && !(iters[c] && ex[q] > 0.5 * over[c]);
+                over[c] = ex[q];
                 rels[c] = rel[q];
-                // a correction too where a box near resonance cost digits (a
-                // plain solve is otherwise far below any tolerance used); a
-                // refined solve, whose tolerance is its accuracy, keeps one
-                // digit in reserve, one in FP64 two
-                const bool more = !(rel[q] <= tol) || (iters[c] == 0 && rel[q] > (refined ? 0.1 : 0.01) * tol);
+                const bool more = !(rel[q] <= tol) || lost;
                 if (more && iters[c] < MAX_IR) next.push_back(c);
             }
             act = next;
@@ -2594,7 +2614,7 @@ int helm_residual(const helm_grid* grid, const double* m_dev, double omega, int 
     Coef cf{m_dev, omega, grid->hx, grid->hz, grid->nx, grid->nz};
     // r is written with leading dimension ld when requested
     ResTab tab{};
-    tab.j[0] = {cf, B_dev, X_dev, r_dev, nullptr, partial, norms_dev, ld, ld, ld, S, 0, 0, 0};
+    tab.j[0] = {cf, B_dev, X_dev, r_dev, nullptr, partial, norms_dev, ld, ld, ld, S, 2, 0, 0};
     launch_residual(tab, 1, adjoint, st);
     launch_norms_finish(tab, 1, st);
     g_launches += 2;

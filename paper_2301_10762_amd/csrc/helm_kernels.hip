@@ -49,7 +49,7 @@ __global__ void k_zero(uint32_t* p, size_t n32) {
     if (i < n32) p[i] = 0u;
 }
 
-// r = B - A X (or A^*), FP64; per-block partial sums of |r|^2 and |B|^2
+// r = B - A X (or A^*), FP64; per-block partial sums of |r|^2, |B|^2 and |X|^2
 //
 // A workgroup takes one block of 256 nodes and a group of RES_CS columns:
 // each thread forms its node's stencil (the diagonal entry from m, the two
@@ -73,7 +73,7 @@ __global__ void k_zero(uint32_t* p, size_t n32) {
 constexpr int RES_CS = 2;
 
 __global__ __launch_bounds__(256) void k_residual(const ResTab tab, int adjoint) {
-    __shared__ double sr[RES_CS][4], sb[RES_CS][4];
+    __shared__ double sums[RES_CS][3][4];
     const ResJob d = tab.j[blockIdx.y];
     const Coef cf = d.cf;
     const double2* __restrict__ B = (const double2*)d.B;
@@ -112,11 +112,12 @@ __global__ __launch_bounds__(256) void k_residual(const ResTab tab, int adjoint)
     double2 dg = diag_entry(cf, i, j);
     if (adjoint) dg.y = -dg.y;
     const double cx = x_coupling(cf, j), cz = z_coupling(cf, i);
-    double rr[RES_CS], bb[RES_CS];
+    double rr[RES_CS], bb[RES_CS], xx[RES_CS];
 #pragma unroll
     for (int c = 0; c < RES_CS; ++c) {
         rr[c] = 0.0;
         bb[c] = 0.0;
+        xx[c] = 0.0;
         if (in && c < ns) {
             const int s = s0 + c;
             double ar = dg.x * xc[c].x - dg.y * xc[c].y, ai = dg.x * xc[c].y + dg.y * xc[c].x;
@@ -130,56 +131,65 @@ __global__ __launch_bounds__(256) void k_residual(const ResTab tab, int adjoint)
             if (R32) R32[(size_t)s * ldr + k] = make_float2((float)r.x, (float)(adjoint ? -r.y : r.y));
             rr[c] = r.x * r.x + r.y * r.y;
             bb[c] = bk.x * bk.x + bk.y * bk.y;
+            xx[c] = xc[c].x * xc[c].x + xc[c].y * xc[c].y;
         }
     }
     const int w = threadIdx.x >> 6;
 #pragma unroll
     for (int c = 0; c < RES_CS; ++c) {
-        double a = rr[c], e = bb[c];
+        double a = rr[c], e = bb[c], x = xx[c];
         for (int o = 32; o > 0; o >>= 1) {
             a += __shfl_down(a, o, 64);
             e += __shfl_down(e, o, 64);
+            x += __shfl_down(x, o, 64);
         }
         if ((threadIdx.x & 63) == 0) {
-            sr[c][w] = a;
-            sb[c][w] = e;
+            sums[c][0][w] = a;
+            sums[c][1][w] = e;
+            sums[c][2][w] = x;
         }
     }
     __syncthreads();
-    if ((int)threadIdx.x < ns) {
-        const int c = threadIdx.x;
-        partial[((size_t)(s0 + c) * nblk + kb) * 2 + 0] = (sr[c][0] + sr[c][1]) + (sr[c][2] + sr[c][3]);
-        partial[((size_t)(s0 + c) * nblk + kb) * 2 + 1] = (sb[c][0] + sb[c][1]) + (sb[c][2] + sb[c][3]);
+    if ((int)threadIdx.x < 4 * ns) {
+        const int c = threadIdx.x >> 2, q = threadIdx.x & 3;
+        if (q < d.nn)
+            partial[((size_t)(s0 + c) * nblk + kb) * d.nn + q] =
+                (sums[c][q][0] + sums[c][q][1]) + (sums[c][q][2] + sums[c][q][3]);
     }
 }
 
 // per column s: the sums of the per-block partials, one workgroup per
 // column, strided partial sums then a fixed-order tree in LDS
 __global__ __launch_bounds__(256) void k_norms_finish(const ResTab tab) {
-    __shared__ double sa[256], sc[256];
+    __shared__ double sa[256], sc[256], sx[256];
     const ResJob d = tab.j[blockIdx.y];
     const double* partial = d.partial;
     double* norms = d.norms;
-    const int s = blockIdx.x, t = threadIdx.x, nblk = d.nblk;
+    const int s = blockIdx.x, t = threadIdx.x, nblk = d.nblk, nn = d.nn;
     if (s >= d.S) return;
-    double a = 0.0, c = 0.0;
+    double a = 0.0, c = 0.0, x = 0.0;
     for (int q = t; q < nblk; q += 256) {
-        a += partial[((size_t)s * nblk + q) * 2];
-        c += partial[((size_t)s * nblk + q) * 2 + 1];
+        const double* p = partial + ((size_t)s * nblk + q) * nn;
+        a += p[0];
+        c += p[1];
+        if (nn == 3) x += p[2];
     }
     sa[t] = a;
     sc[t] = c;
+    sx[t] = x;
     __syncthreads();
     for (int h = 128; h > 0; h >>= 1) {
         if (t < h) {
             sa[t] += sa[t + h];
             sc[t] += sc[t + h];
+            sx[t] += sx[t + h];
         }
         __syncthreads();
     }
     if (t == 0) {
-        norms[2 * s] = sa[0];
-        norms[2 * s + 1] = sc[0];
+        norms[nn * s] = sa[0];
+        norms[nn * s + 1] = sc[0];
+        if (nn == 3) norms[nn * s + 2] = sx[0];
     }
 }
 

@@ -37,7 +37,7 @@ void launch_check_model(const double* m, int64_t n, int* flag, hipStream_t st);
 // Residuals r = B - A X of up to RES_MAX jobs in one launch: R and R32 (or
 // null) take r and its complex64 copy (conjugated if adjoint), partial the
 // sums of squares of residual_blocks() blocks per column; then norms, per
-// column the squares' sums of r and B.
+// column the squares' sums of r and B, and of X where nn is 3.
 constexpr int RES_MAX = 16;
 struct ResJob {
     Coef cf;
@@ -46,7 +46,7 @@ struct ResJob {
     float* R32;
     double *partial, *norms;
     int64_t ldb, ldx, ldr;
-    int S, nblk, per_xcd, pad_;   // nblk, per_xcd: set by the launchers
+    int S, nn, nblk, per_xcd;   // nn: sums per column (2 or 3); nblk, per_xcd: set by the launchers
 };
 struct ResTab {
     ResJob j[RES_MAX];

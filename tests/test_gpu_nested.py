@@ -85,3 +85,37 @@ def test_nested_forced_tile_pivoting(helm, nx, nz):
     F.close()
     assert info.max_relres <= 1e-10
     assert_cols(X.cpu().numpy(), Xo, 1e-9, what="forced pivoting")
+
+
+def _excess(helm, G, m, w, B, X, adjoint=False):
+    """Largest column's ||b - A x|| over eps max(N^(1/4), 8) (||x|| + ||b|| / 4)."""
+    n = helm.residual(G, m, w, B, X, adjoint=adjoint)[1].cpu().numpy()
+    x = torch.linalg.vector_norm(X, dim=1).cpu().numpy()
+    return float((np.sqrt(n[:, 0]) / (2.0 ** -52 * max(G.N ** 0.25, 8.0) * (x + 0.25 * np.sqrt(n[:, 1])))).max())
+
+
+# Layered models at 8 to 20 points per wavelength, where boxes of the
+# dissection come near resonance.  Block factors leave an excess of 0.8 to 1.2
+# in complex128; solves to a tolerance may leave 1.25 or a residual of 2e-14, in
+# either precision and direction, for sources and for smooth right-hand sides.
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("nx,nz", [(41, 77), (101, 101), (151, 97), (201, 201), (401, 37)])
+def test_nested_as_accurate_as_blocks(helm, nx, nz, precision):
+    from paper_2301_10762_amd import inputs as I
+    G = helm.Grid(nx, nz, I.H_KM, I.H_KM)
+    for seed in range(3):
+        mh = (1.0 / I.layered_velocity(nx, nz, seed, I.H_KM) ** 2).reshape(-1)
+        m = torch.as_tensor(mh, device="cuda")
+        for ppw in (8.0, 9.5, 12.0, 20.0):
+            w = I.omega_from_ppw(ppw, I.C_MIN, I.H_KM)
+            F = helm.factor(G, m, w, precision)
+            B = torch.zeros(3, G.N, dtype=torch.complex128, device="cuda")
+            B[0, 2 * nx + nx // 3] = B[1, (nz // 2) * nx + nx // 2] = 1.0
+            B[2] = F.solve(B[:1], tol=1e-10)[0][0] * m
+            for adjoint in (False, True):
+                X, info = (F.adjoint_solve if adjoint else F.solve)(B, tol=1e-10)
+                ex = _excess(helm, G, m, w, B, X, adjoint)
+                print(f"{nx}x{nz} {precision} seed {seed} ppw {ppw}: excess {ex:.2f}, {info.ir_iters} corrections",
+                      flush=True)
+                assert ex <= 1.25 or info.max_relres <= 2e-14
+            F.close()
