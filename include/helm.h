@@ -100,6 +100,12 @@ int helm_factor_batch(int32_t count, const helm_grid* grids, const double* const
  * admission): that of the row-by-row form, nx*nz*8 bytes of model included. */
 int helm_factor_bytes(const helm_grid* grid, int precision, size_t* bytes);
 
+/* Bytes of LDS per workgroup (static and dynamic) that the kernels of this
+ * grid's nested dissection ask for: [0], [1] fronts of at most 16 and 32
+ * pivots, [2], [3] subtree sweeps forward and backward; zeros where the grid
+ * has no such launch.  Needs no GPU (for tests: a compute unit has 163840).  */
+int helm_plan_lds(const helm_grid* grid, size_t bytes[4]);
+
 /* Releases a factor without waiting for the GPU.  Its device memory goes
  * back to the library's cache in the order of the stream the factor was made
  * on, after the factor's last use by a solve call on any other stream (the

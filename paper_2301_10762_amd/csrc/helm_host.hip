@@ -626,7 +626,7 @@ int nd_factor_group(helm_factor_s* const* fs, int n, int pivot, hipStream_t st, 
     KernelTimer::Pair pu;
     const bool tu = g_timer.begin(0, st, &pu);
     int64_t launches = 0;
-    for (auto& lv : P.levels) launches += launch_nd_level(t, lv, dtab, n, st);
+    for (auto& lv : P.levels) HIPCHECK(launch_nd_level(t, lv, dtab, n, st, &launches));
     if (tu) g_timer.end(pu, launches, st);
     g_launches += 2 + launches;
     HIPCHECK(hipGetLastError());
@@ -1005,7 +1005,7 @@ int sweep_group(helm_factor_s* const* fs, int n, const void* const* Ys, const in
         for (int c = 0; c < nf; ++c) np_max = std::max(np_max, tab[c].np);
         KernelTimer::Pair p;
         const bool tm = g_timer.begin(2, st, &p);
-        launch_sweep_chain(dtab, nf, st_max, np_max, fp32, conj_b, st);
+        HIPCHECK(launch_sweep_chain(dtab, nf, st_max, np_max, fp32, conj_b, st));
         if (tm) g_timer.end(p, 2, st);
         g_launches += 3;
         HIPCHECK(hipGetLastError());
@@ -1210,10 +1210,10 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
         launch_nd_put_jobs(tab, dtab, st);
         KernelTimer::Pair p;
         const bool tm = g_timer.begin(2, st, &p);
-        launch_nd_sub_forward(t, P, dtab, n, wide, adjoint, st);
+        HIPCHECK(launch_nd_sub_forward(t, P, dtab, n, wide, adjoint, st));
         for (int q = P.upper; q < L; ++q) launch_nd_forward(t, P.levels[q], dtab, n, wide, st);
         for (int q = L - 1; q >= P.upper; --q) launch_nd_backward(t, P.levels[q], dtab, n, wide, st);
-        launch_nd_sub_backward(t, P, dtab, n, wide, correct, adjoint, st);
+        HIPCHECK(launch_nd_sub_backward(t, P, dtab, n, wide, correct, adjoint, st));
         if (tm) g_timer.end(p, 2 + 2 * (L - P.upper), st);
         g_launches += 3 + 2 * (L - P.upper);
     }
@@ -2531,6 +2531,23 @@ int helm_factor_bytes(const helm_grid* grid, int precision, size_t* bytes) {
     if (!bytes) return fail(HELM_EINVAL, "bytes is NULL");
     if (precision != HELM_FP64 && precision != HELM_FP32_IR) return fail(HELM_EINVAL, "unknown precision");
     *bytes = factor_bytes_of(*grid, precision);
+    return HELM_OK;
+}
+
+int helm_plan_lds(const helm_grid* grid, size_t* bytes) {
+    int rc = check_grid(grid);
+    if (rc) return rc;
+    if (!bytes) return fail(HELM_EINVAL, "bytes is NULL");
+    std::fill(bytes, bytes + 4, (size_t)0);
+    NdPlan p;
+    if (N_of(*grid) > ND_MAX_NODES || !nd_build(grid->nx, grid->nz, &p)) return HELM_OK;
+    for (auto& lv : p.levels)
+        if (lv.small) {
+            const int kp = lv.pmax <= 16 ? 16 : 32;
+            bytes[kp == 32] = std::max(bytes[kp == 32], nd_front_lds(kp, lv.fmax));
+        }
+    bytes[2] = nd_sub_forward_lds(p);
+    bytes[3] = nd_sub_backward_lds(p);
     return HELM_OK;
 }
 

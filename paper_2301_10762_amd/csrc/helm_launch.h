@@ -30,7 +30,7 @@ void launch_sweep(const SweepTab* dtab, int n, int t, int uni, int unroll, int g
                   bool forward, bool conj_b, hipStream_t st_);
 // both sweeps of narrow fronts, in two launches; np: padded nodes a row
 inline bool sweep_narrow(int np, bool fp32) { return np <= (fp32 ? 96 : 64); }
-void launch_sweep_chain(const SweepTab* dtab, int nf, int nct, int np_max, bool fp32, bool conj_b, hipStream_t st);
+hipError_t launch_sweep_chain(const SweepTab* dtab, int nf, int nct, int np_max, bool fp32, bool conj_b, hipStream_t st);
 int sweep_row_tiles(int np);
 int sweep_col_tiles(int S);
 void launch_check_model(const double* m, int64_t n, int* flag, hipStream_t st);

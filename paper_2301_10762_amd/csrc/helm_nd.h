@@ -143,7 +143,7 @@ struct NdPlan {
 };
 
 // host description only (no device memory); false: the grid does not divide
-// into subtrees of the size the sweeps take
+// into subtrees of the size the sweeps take, or whose vectors fit the LDS
 bool nd_build(int nx, int nz, NdPlan* plan);
 // complex128 values a factor of this grid stores
 int64_t nd_factor_elems(int nx, int nz);
@@ -188,18 +188,25 @@ static_assert(sizeof(NdSysTab) <= 4000 && sizeof(NdJobTab) <= 4000, "tables pass
 
 void launch_nd_put_sys(const NdSysTab& tab, NdSysTab* dst, hipStream_t st);
 void launch_nd_put_jobs(const NdJobTab& tab, NdJobTab* dst, hipStream_t st);
-// LDS a workgroup of k_nd_front may take, and whether a level's fronts fit it
+// LDS a workgroup may take, all of it dynamic: a compute unit's 160 KB with a
+// little left for the launch; what a level's narrow fronts (kp: 16 or 32
+// pivots) and the subtree sweeps take; whether a level's fronts are narrow
+// (those that do not fit go the wide fronts' way)
 constexpr size_t ND_LDS = 160 * 1024 - 512;
+size_t nd_front_lds(int kp, int fmax);
+size_t nd_sub_forward_lds(const NdPlan& p);
+size_t nd_sub_backward_lds(const NdPlan& p);
 bool nd_narrow(int pmax, int fmax);
-// factorisation of one level; returns the number of launches
-int launch_nd_level(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, int n, hipStream_t st);
-// right-hand sides of the rows above the subtrees (conjugated when conj), and their solutions back: X = a, or X += a
+// factorisation of one level; adds its launches to *launches
+hipError_t launch_nd_level(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, int n, hipStream_t st,
+                           int64_t* launches);
+// one level's forward and backward sweep, above the subtrees
 void launch_nd_forward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st);
 void launch_nd_backward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st);
 // the subtrees' sweeps: from B to ring contributions, and from the rings' solutions to X
-void launch_nd_sub_forward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool conj,
-                           hipStream_t st);
-void launch_nd_sub_backward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool add,
-                            bool conj, hipStream_t st);
+hipError_t launch_nd_sub_forward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool conj,
+                                 hipStream_t st);
+hipError_t launch_nd_sub_backward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool add,
+                                  bool conj, hipStream_t st);
 
 }  // namespace helm

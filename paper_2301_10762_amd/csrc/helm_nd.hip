@@ -418,12 +418,13 @@ __device__ __forceinline__ void nd_invert(double2 (&a)[4], int kb, const NdSys& 
 template <int KP>
 __global__ __launch_bounds__(KP == 16 ? 256 : 512, KP == 16 ? 4 : 2) void k_nd_front(NdTabs t, int first, int parity, int fmax,
                                                                    const NdSysTab* __restrict__ stab) {
+    // all of its LDS (nd_front_lds, which decides whether a level comes here)
     extern __shared__ __attribute__((aligned(16))) char nd_smem[];
     constexpr int LD = KP + 1, NTH = KP == 16 ? 256 : 512, NW = NTH / 64;
     double2* L2 = (double2*)nd_smem;                            // G, and for KP = 32 inversion scratch behind it
     double2* sF = L2 + (KP == 16 ? 16 * 33 : 2 * 32 * 33);      // [ring][LD]
     NdIndex* sidx = (NdIndex*)(sF + (size_t)(fmax - 16) * LD);  // fmax entries
-    __shared__ NdScratch sh;
+    NdScratch& sh = *(NdScratch*)(sidx + fmax);
     const NdSys y = nd_record(stab->s, blockIdx.y);
     const NdFront f = nd_record(t.fronts, first + (int)blockIdx.x);
     const NdKids kids = nd_kids(t, f, y, parity);
@@ -1548,59 +1549,71 @@ void launch_nd_put_jobs(const NdJobTab& tab, NdJobTab* dst, hipStream_t st) {
 }
 
 // LDS of k_nd_front<KP> for a level's widest front
-static size_t nd_front_lds(int kp, int fmax) {
+size_t nd_front_lds(int kp, int fmax) {
     return sizeof(double2) * ((size_t)(kp == 16 ? 16 : 64) * 33 + (size_t)(fmax - 16) * (kp + 1)) +
-           sizeof(NdIndex) * (size_t)fmax;
+           sizeof(NdIndex) * (size_t)fmax + sizeof(NdScratch);
 }
 bool nd_narrow(int pmax, int fmax) { return pmax <= 32 && nd_front_lds(pmax <= 16 ? 16 : 32, fmax) <= ND_LDS; }
 
-template <int KP>
-static void launch_nd_front(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, int n, hipStream_t st) {
-    const size_t lds = nd_front_lds(KP, lv.fmax);
-    if (lds > 65536)
-        (void)hipFuncSetAttribute((const void*)k_nd_front<KP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_nd_front<KP>, dim3(lv.count, n), dim3(KP == 16 ? 256 : 512), lds, st, t, lv.first, lv.parity,
-                       lv.fmax, dsys);
+// More than 64 KB of LDS is asked for by the kernel's attribute, always for
+// the most that any launch takes, so that no thread lowers it under another's
+// launch.
+static hipError_t nd_allow_lds(const void* kernel, size_t lds) {
+    if (lds > ND_LDS) return hipErrorInvalidValue;
+    return lds > 65536 ? hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ND_LDS) : hipSuccess;
 }
 
-int launch_nd_level(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, int n, hipStream_t st) {
+template <int KP>
+static hipError_t launch_nd_front(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, int n, hipStream_t st) {
+    const size_t lds = nd_front_lds(KP, lv.fmax);
+    const hipError_t e = nd_allow_lds((const void*)k_nd_front<KP>, lds);
+    if (e == hipSuccess)
+        hipLaunchKernelGGL(k_nd_front<KP>, dim3(lv.count, n), dim3(KP == 16 ? 256 : 512), lds, st, t, lv.first,
+                           lv.parity, lv.fmax, dsys);
+    return e;
+}
+
+hipError_t launch_nd_level(const NdTabs& t, const NdLevel& lv, const NdSysTab* dsys, int n, hipStream_t st, int64_t* launches) {
+    *launches += 1;
     if (lv.leaf) {
         hipLaunchKernelGGL(k_nd_leaf, dim3(lv.count, n), dim3(64), 0, st, t, lv.first, dsys);
-        return 1;
+        return hipSuccess;
     }
-    if (lv.small) {
-        if (lv.pmax <= 16) launch_nd_front<16>(t, lv, dsys, n, st);
-        else launch_nd_front<32>(t, lv, dsys, n, st);
-        return 1;
-    }
+    if (lv.small) return lv.pmax <= 16 ? launch_nd_front<16>(t, lv, dsys, n, st) : launch_nd_front<32>(t, lv, dsys, n, st);
     const dim3 grid(lv.count + lv.tiles, n);
     hipLaunchKernelGGL(k_nd_gather, grid, dim3(256), 0, st, t, lv.first, lv.count, lv.tile0, lv.parity, dsys);
     for (int s = 0; s < lv.npan; ++s)
         hipLaunchKernelGGL(k_nd_step, grid, dim3(256), 0, st, t, lv.first, lv.count, lv.tile0, lv.parity, s, dsys);
     if (lv.stiles)
         hipLaunchKernelGGL(k_nd_schur, dim3(lv.stiles, n), dim3(256), 0, st, t, lv.first, lv.stile0, lv.parity, dsys);
-    return 1 + lv.npan + (lv.stiles ? 1 : 0);
+    *launches += lv.npan + (lv.stiles ? 1 : 0);
+    return hipSuccess;
 }
 
-template <typename K>
-static dim3 nd_sub_grid(K kernel, const NdPlan& p, int nct, int n, size_t lds) {
-    if (lds > 65536)
-        (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    return dim3(8 * ((p.nsub + 7) / 8) * nct, n);
+size_t nd_sub_forward_lds(const NdPlan& p) { return (size_t)p.sub_rows * SUB_RS * 16 + 4 * (size_t)p.sub_tab; }
+size_t nd_sub_backward_lds(const NdPlan& p) {
+    return (size_t)p.sub_brows * SUB_RS * 16 + SUB_W / 2 * 4096 + 4 * (size_t)p.sub_tab;
 }
-void launch_nd_sub_forward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool conj,
+static dim3 nd_sub_grid(const NdPlan& p, int nct, int n) { return dim3(8 * ((p.nsub + 7) / 8) * nct, n); }
+hipError_t launch_nd_sub_forward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool conj,
                            hipStream_t st) {
     const int nct = (smax + 15) / 16;
-    const size_t lds = (size_t)p.sub_rows * SUB_RS * 16 + 4 * (size_t)p.sub_tab;
-    hipLaunchKernelGGL(k_nd_sub_forward, nd_sub_grid(k_nd_sub_forward, p, nct, n, lds), dim3(SUB_T), lds, st, t,
-                       p.nsub, nct, p.sub_rows, p.sub_parity, conj ? 1 : 0, djobs);
+    const size_t lds = nd_sub_forward_lds(p);
+    const hipError_t e = nd_allow_lds((const void*)k_nd_sub_forward, lds);
+    if (e == hipSuccess)
+        hipLaunchKernelGGL(k_nd_sub_forward, nd_sub_grid(p, nct, n), dim3(SUB_T), lds, st, t, p.nsub, nct, p.sub_rows,
+                           p.sub_parity, conj ? 1 : 0, djobs);
+    return e;
 }
-void launch_nd_sub_backward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool add,
+hipError_t launch_nd_sub_backward(const NdTabs& t, const NdPlan& p, const NdJobTab* djobs, int n, int smax, bool add,
                             bool conj, hipStream_t st) {
     const int nct = (smax + 15) / 16;
-    const size_t lds = (size_t)p.sub_brows * SUB_RS * 16 + SUB_W / 2 * 4096 + 4 * (size_t)p.sub_tab;
-    hipLaunchKernelGGL(k_nd_sub_backward, nd_sub_grid(k_nd_sub_backward, p, nct, n, lds), dim3(SUB_T), lds, st, t,
-                       p.nsub, nct, p.sub_brows, conj ? 1 : 0, add ? 1 : 0, djobs);
+    const size_t lds = nd_sub_backward_lds(p);
+    const hipError_t e = nd_allow_lds((const void*)k_nd_sub_backward, lds);
+    if (e == hipSuccess)
+        hipLaunchKernelGGL(k_nd_sub_backward, nd_sub_grid(p, nct, n), dim3(SUB_T), lds, st, t, p.nsub, nct, p.sub_brows,
+                           conj ? 1 : 0, add ? 1 : 0, djobs);
+    return e;
 }
 
 void launch_nd_forward(const NdTabs& t, const NdLevel& lv, const NdJobTab* djobs, int n, int smax, hipStream_t st) {

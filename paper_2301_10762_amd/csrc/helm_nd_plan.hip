@@ -488,7 +488,7 @@ bool nd_build(int nx, int nz, NdPlan* plan) {
         P.urows[P.levels[v].parity] = std::max(P.urows[P.levels[v].parity], (int64_t)P.levels[v].urows);
     for (auto& F : P.fronts)
         for (int c = 0; c < 2; ++c) F.curow[c] = F.child[c] < 0 ? 0 : P.fronts[F.child[c]].urow;
-    return true;
+    return nd_sub_forward_lds(P) <= ND_LDS && nd_sub_backward_lds(P) <= ND_LDS;
 }
 
 }  // namespace helm

@@ -450,27 +450,29 @@ __global__ __launch_bounds__(SWC_T) void k_sweep_chain(const SweepTab* __restric
 }
 
 template <typename T, int CN>
-static void launch_sweep_chain_t(const SweepTab* dtab, int nf, int nct, int np_max, bool conj_b, hipStream_t st) {
+static hipError_t launch_sweep_chain_t(const SweepTab* dtab, int nf, int nct, int np_max, bool conj_b, hipStream_t st) {
     using C = typename CT<T>::c;
+    // the attribute is set to the most that this kernel takes, so that no
+    // thread lowers it under another's launch
+    constexpr size_t most = sizeof(C) * 17 * (16 * SWC_W + (sizeof(T) == 4 ? 96 : 64));
     const size_t lds = sizeof(C) * 17 * (16 * SWC_W + (size_t)np_max);
     const dim3 grid(nct, nf), block(SWC_T);
-    auto go = [&](auto kernel) {
-        if (lds > 65536)
-            (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    auto go = [&](auto kernel) -> hipError_t {
+        if (lds > 65536) {
+            const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+            if (e != hipSuccess) return e;
+        }
         hipLaunchKernelGGL(kernel, grid, block, lds, st, dtab);
+        return hipSuccess;
     };
-    if (conj_b) {
-        go(k_sweep_chain<T, true, true, CN>);
-        go(k_sweep_chain<T, false, true, CN>);
-    } else {
-        go(k_sweep_chain<T, true, false, CN>);
-        go(k_sweep_chain<T, false, false, CN>);
-    }
+    const hipError_t e = conj_b ? go(k_sweep_chain<T, true, true, CN>) : go(k_sweep_chain<T, true, false, CN>);
+    if (e != hipSuccess) return e;
+    return conj_b ? go(k_sweep_chain<T, false, true, CN>) : go(k_sweep_chain<T, false, false, CN>);
 }
-void launch_sweep_chain(const SweepTab* dtab, int nf, int nct, int np_max, bool fp32, bool conj_b, hipStream_t st) {
-    if (!fp32) launch_sweep_chain_t<double, 1>(dtab, nf, nct, np_max, conj_b, st);
-    else if (np_max <= 64) launch_sweep_chain_t<float, 1>(dtab, nf, nct, np_max, conj_b, st);
-    else launch_sweep_chain_t<float, 3>(dtab, nf, nct, np_max, conj_b, st);
+hipError_t launch_sweep_chain(const SweepTab* dtab, int nf, int nct, int np_max, bool fp32, bool conj_b, hipStream_t st) {
+    if (!fp32) return launch_sweep_chain_t<double, 1>(dtab, nf, nct, np_max, conj_b, st);
+    if (np_max <= 64) return launch_sweep_chain_t<float, 1>(dtab, nf, nct, np_max, conj_b, st);
+    return launch_sweep_chain_t<float, 3>(dtab, nf, nct, np_max, conj_b, st);
 }
 
 void launch_sweep_init(const SweepTab* dtab, int n, int total, bool fp32, bool conj_b, hipStream_t st) {

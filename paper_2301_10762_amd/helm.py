@@ -98,6 +98,7 @@ def lib():
     L.helm_factor_batch.argtypes = [i32, G, ctypes.POINTER(_vp), ctypes.POINTER(f64), ctypes.c_int, _vp,
                                     ctypes.POINTER(_vp)]
     L.helm_factor_bytes.argtypes = [G, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)]
+    L.helm_plan_lds.argtypes = [G, ctypes.POINTER(ctypes.c_size_t)]
     L.helm_factor_destroy.argtypes = [_vp]
     L.helm_factor_destroy.restype = None
     L.helm_solve.argtypes = [_vp, _vp, _vp, i32, i64, f64, _vp, I]
@@ -142,7 +143,7 @@ def lib():
     L.helm_counter.argtypes = [ctypes.c_int]
     L.helm_counter.restype = ctypes.c_int64
     L.helm_last_error.restype = ctypes.c_char_p
-    for name in ("helm_factor", "helm_factor_batch", "helm_factor_bytes", "helm_solve", "helm_adjoint_solve",
+    for name in ("helm_factor", "helm_factor_batch", "helm_factor_bytes", "helm_plan_lds", "helm_solve", "helm_adjoint_solve",
                  "helm_solve_batch", "helm_misfit_grad", "helm_gn_hvp", "helm_residual", "helm_tile_inverse",
                  "helm_mfma_probe", "helm_hess_create", "helm_hess_apply", "helm_hess_pcg", "helm_gamma_solve",
                  "helm_hess_create_at", "helm_upper_grad", "helm_restrict", "helm_fwi",

@@ -119,3 +119,22 @@ def test_nested_as_accurate_as_blocks(helm, nx, nz, precision):
                       flush=True)
                 assert ex <= 1.25 or info.max_relres <= 2e-14
             F.close()
+
+
+# The widest narrow fronts: boxes of 60 to 65 nodes a side with a ring on every
+# side (tests/test_plan_host.py holds what their levels ask of a compute unit).
+@pytest.mark.parametrize("nx,nz,precision", [(256, 256, "fp64"), (243, 251, "fp32_ir"), (122, 239, "fp64")])
+def test_nested_widest_narrow_fronts(helm, nx, nz, precision):
+    print(f"{nx}x{nz}, {precision}", flush=True)
+    m, w, B, h = _system(nx, nz, 3)
+    G, Bd = helm.Grid(nx, nz, h, h), torch.as_tensor(B, device="cuda")
+    Fo = oracle.Factor(oracle.Grid(nx, nz, h, h), m, w)
+    Xo, Lo = Fo.solve(B), Fo.adjoint_solve(B)
+    Fo.close()
+    F = helm.factor(G, m, w, precision)
+    X, info = F.solve(Bd, tol=1e-10)
+    L, ainfo = F.adjoint_solve(Bd, tol=1e-10)
+    F.close()
+    assert info.max_relres <= 1e-10 and ainfo.max_relres <= 1e-10
+    assert_cols(X.cpu().numpy(), Xo, 1e-9, what="forward")
+    assert_cols(L.cpu().numpy(), Lo, 1e-9, what="adjoint")
