@@ -81,9 +81,9 @@ enum {
  * Diagonal tiles use diagonal pivots unless one falls below 1e-2 x max|tile|;
  * then the tile (nested dissection) or the whole factor (row by row) is done
  * with partial pivoting inside the tiles.  A nested-dissection factor whose
- * inverses grow (a box of the dissection near resonance) has each solve
- * without a tolerance corrected once; one that meets an exactly zero pivot is
- * made row by row.  Returns HELM_ESINGULAR with no factor if a pivot of that
+ * inverses grow (boxes of the dissection near resonance) has each solve
+ * without a tolerance corrected once to three times; a system with a box at
+ * resonance (a zero pivot, inverses above 1e6) is made row by row.  Returns HELM_ESINGULAR with no factor if a pivot of that
  * is exactly zero, HELM_EINVAL if the model is not positive and finite.
  * Synchronises `stream`.                                                   */
 int helm_factor(const helm_grid* grid, const double* m_dev, double omega, int precision,

@@ -28,7 +28,7 @@ struct helm_factor_s {
     double* m;     // device copy of the model
     size_t gbytes;    // size of G
     std::shared_ptr<NdPlan> nd;   // nested-dissection factor: G holds its fronts (complex128); else null
-    bool grown = false;           // of which a tile inverse grew: plain solves are corrected once
+    int fixes = 0;                // of which tile inverses grew: corrections of a solve without a tolerance
     hipStream_t st;   // the stream it was made on (its memory is released there)
     // last use on every other stream a solve ran it on (an event each); at
     // release the factor's own stream waits for them, so the memory is not
@@ -596,9 +596,10 @@ int nd_choose(const helm_grid& g, int prec, std::shared_ptr<NdPlan>* out) {
     return rc;
 }
 
-// Factor at most ND_MAXS systems of one plan together.  zero[c] is set where
-// system c met an exactly zero pivot.
-int nd_factor_group(helm_factor_s* const* fs, int n, int pivot, hipStream_t st, int* zero) {
+// Factor at most ND_MAXS systems of one plan together.  lost[c] is set where
+// system c met an exactly zero pivot, or one so small that no solve would
+// recover its digits.
+int nd_factor_group(helm_factor_s* const* fs, int n, int pivot, hipStream_t st, int* lost) {
     const NdPlan& P = *fs[0]->nd;
     Scratch sc(st);
     double2 *w0, *w1;
@@ -637,8 +638,9 @@ int nd_factor_group(helm_factor_s* const* fs, int n, int pivot, hipStream_t st, 
     g_launches += 1;
     if ((rc = hb.wait())) return rc;
     for (int c = 0; c < n; ++c) {
-        zero[c] = hs[4 * c];
-        fs[c]->grown = hs[4 * c + 3] != 0;
+        const int grown = hs[4 * c + 3];
+        lost[c] = hs[4 * c] != 0 || (grown & 8);
+        fs[c]->fixes = (grown & 1) + (grown >> 1 & 1) + (grown >> 2 & 1);
     }
     return HELM_OK;
 }
@@ -771,7 +773,7 @@ void destroy(helm_factor_s* f) {
 constexpr size_t ND_WORK_BYTES = (size_t)8 << 30;
 
 int factor_checked(int count, const helm_grid* grids, const double* const* m_devs, const double* omegas, int prec,
-                   hipStream_t st, helm_factor_t* outs);
+                   hipStream_t st, const int* bad, helm_factor_t* outs);
 
 int factor_many(int count, const helm_grid* grids, const double* const* m_devs, const double* omegas, int prec,
                 hipStream_t st, helm_factor_t* outs) {
@@ -792,7 +794,7 @@ int factor_many(int count, const helm_grid* grids, const double* const* m_devs, 
     int* flag;
     int rc = check_models(count, m_devs, ns.data(), hb, &flag);
     if (rc) return rc;
-    rc = factor_checked(count, grids, m_devs, omegas, prec, st, outs);
+    rc = factor_checked(count, grids, m_devs, omegas, prec, st, flag, outs);
     if (int rw = hb.wait()) rc = rc ? rc : rw;
     else if (*flag) {
         if (rc == HELM_OK)
@@ -805,8 +807,9 @@ int factor_many(int count, const helm_grid* grids, const double* const* m_devs, 
     return rc;
 }
 
+// *bad: nonzero, after a wait for the stream, where a model is not positive and finite
 int factor_checked(int count, const helm_grid* grids, const double* const* m_devs, const double* omegas, int prec,
-                   hipStream_t st, helm_factor_t* outs) {
+                   hipStream_t st, const int* bad, helm_factor_t* outs) {
     keep_pool_memory();
     std::vector<helm_factor_s*> fs(count, nullptr);
     auto cleanup = [&]() {
@@ -858,15 +861,15 @@ int factor_checked(int count, const helm_grid* grids, const double* const* m_dev
                 grp.push_back(fs[d]);
                 done[d] = 1;
             }
-        std::vector<int> zero(grp.size(), 0);
-        int rc = nd_factor_group(grp.data(), (int)grp.size(), g_force_pivot, st, zero.data());
-        // a zero pivot inside a box, or no room to work in: the block
-        // factorisation, whose blocks reach the absorbing boundary, takes the
-        // system
+        std::vector<int> lost(grp.size(), 0);
+        int rc = nd_factor_group(grp.data(), (int)grp.size(), g_force_pivot, st, lost.data());
+        if (rc == HELM_OK && *bad) rc = bad_model();   // known since that wait
+        // a box at resonance, or no room to work in: the block factorisation,
+        // whose blocks reach the absorbing boundary, takes the system
         const bool room_left = rc != HELM_ENOMEM;
         if (!room_left) rc = HELM_OK;
         for (size_t q = 0; q < grp.size() && rc == HELM_OK; ++q)
-            if (zero[q] || !room_left) {
+            if (lost[q] || !room_left) {
                 g_cache.put(grp[q]->G, grp[q]->gbytes, st);
                 grp[q]->nd.reset();
                 rc = store(grp[q], block_bytes(grp[q]));
@@ -1255,14 +1258,16 @@ int nd_solve_jobs(std::vector<SolveJob*>& jobs, bool adjoint, double tol, hipStr
     std::vector<double> rels(n, -1.0), over(n, 0.0);
     int worst = HELM_OK;
     if (!(tol > 0.0)) {
-        // no residual is measured: where the factor says digits were lost,
-        // one correction, queued without a wait
-        std::vector<int> grown;
-        for (int c = 0; c < n; ++c)
-            if (jobs[c]->f->grown) grown.push_back(c);
-        if (!grown.empty())
-            if (int rc = sweep(grown, true)) return rc;
-        for (int c : grown) iters[c] = 1;
+        // no residual is measured: as many corrections as the factor says the
+        // lost digits take, queued without a wait
+        for (;;) {
+            std::vector<int> fix;
+            for (int c = 0; c < n; ++c)
+                if (iters[c] < jobs[c]->f->fixes) fix.push_back(c);
+            if (fix.empty()) break;
+            if (int rc = sweep(fix, true)) return rc;
+            for (int c : fix) ++iters[c];
+        }
     } else {
         for (;;) {
             std::vector<ResidualReq> rq;

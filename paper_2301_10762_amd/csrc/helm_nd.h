@@ -159,11 +159,19 @@ struct NdTabs {
 
 constexpr int ND_MAXS = 16;   // systems per launch
 
+// Steps of the largest |T_ij|^2 (tile inverses, in couplings) that count: above
+// 3, 10^4 and 10^5 couplings a solve without a tolerance takes one, two and
+// three corrections (residuals before any: below 3 couplings what block
+// factors leave, 33^2 to 401^2; 2e-8 at 10^4, growing with its square; each
+// correction multiplies by as much again), above 10^6 the system is factored
+// row by row.
+constexpr float ND_GROWN[4] = {9.0f, 1e8f, 1e10f, 1e12f};
+
 struct NdSys {        // one system being factored
     Coef cf;
     double2* fac;
     double2* work[2];   // working memory of even and odd levels
-    int* status;        // [0] zero-pivot flag, [1] front, [2] row, [3] grown inverses
+    int* status;        // [0] zero-pivot flag, [1] front, [2] row, [3] steps of ND_GROWN passed (bits)
     int pivot;          // 1: partial pivoting in every tile
     int pad_;
 };

@@ -40,7 +40,6 @@ __device__ __forceinline__ R nd_record(const R* tab, int i) {
     return r;
 }
 
-constexpr float ND_GROWN2 = 2500.0f;   // |T_ij| above 50 couplings
 
 // What a front gathers from: its children's Schur complements, or a leaf
 // child's inverse G (its Schur complement is -c_r c_c G at the leaf nodes the
@@ -140,12 +139,16 @@ __device__ __forceinline__ double2 nd_entry(const NdKids& k, bool kids, const Nd
     return o;
 }
 
-// Flags a system whose tile inverses grow (m2: this lane's largest |T_ij|^2
-// over the couplings' scale): a box near resonance, whose plain solves lose
-// digits and are corrected once (residuals measured about 1e-15 max |T|^2).
+// Notes how far a system's tile inverses grow (m2: this lane's largest
+// |T_ij|^2 over the couplings' scale), one bit per step of ND_GROWN: a box near
+// resonance, behind which solves lose digits (1e-17 to 2e-16 max |T|^2).
 __device__ __forceinline__ void nd_grown(const NdSys& y, float m2, bool valid) {
-    const float sc = (float)fmax(y.cf.hz / y.cf.hx, y.cf.hx / y.cf.hz);
-    if (__any(valid && !(m2 * sc * sc <= ND_GROWN2)) && (threadIdx.x & 63) == 0) atomicOr(&y.status[3], 1);
+    const float sc = (float)fmax(y.cf.hz / y.cf.hx, y.cf.hx / y.cf.hz), v = m2 * sc * sc;
+    int bits = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (__any(valid && !(v <= ND_GROWN[k]))) bits |= 1 << k;
+    if (bits && (threadIdx.x & 63) == 0 && (bits & ~y.status[3])) atomicOr(&y.status[3], bits);
 }
 __device__ __forceinline__ float nd_max2(const double2 (&a)[4]) {
     float m2 = 0.0f;

@@ -121,6 +121,29 @@ def test_nested_as_accurate_as_blocks(helm, nx, nz, precision):
             F.close()
 
 
+# The same without a tolerance in complex128, where the factor decides on
+# corrections: twice what block factors leave.
+@pytest.mark.parametrize("nx,nz", [(41, 77), (101, 101), (151, 97), (201, 201), (401, 37)])
+def test_nested_plain_as_accurate_as_blocks(helm, nx, nz):
+    from paper_2301_10762_amd import inputs as I
+    G = helm.Grid(nx, nz, I.H_KM, I.H_KM)
+    for seed in range(3):
+        mh = (1.0 / I.layered_velocity(nx, nz, seed, I.H_KM) ** 2).reshape(-1)
+        m = torch.as_tensor(mh, device="cuda")
+        for ppw in (8.0, 9.5, 12.0, 20.0):
+            w = I.omega_from_ppw(ppw, I.C_MIN, I.H_KM)
+            F = helm.factor(G, m, w)
+            B = torch.zeros(3, G.N, dtype=torch.complex128, device="cuda")
+            B[0, 2 * nx + nx // 3] = B[1, (nz // 2) * nx + nx // 2] = 1.0
+            B[2] = F.solve(B[:1])[0][0] * m
+            for adjoint in (False, True):
+                X, info = (F.adjoint_solve if adjoint else F.solve)(B)
+                ex = _excess(helm, G, m, w, B, X, adjoint)
+                print(f"{nx}x{nz} plain seed {seed} ppw {ppw}: excess {ex:.2f}, {info.ir_iters} corrections", flush=True)
+                assert ex <= 2.0
+            F.close()
+
+
 # The widest narrow fronts: boxes of 60 to 65 nodes a side with a ring on every
 # side (tests/test_plan_host.py holds what their levels ask of a compute unit).
 @pytest.mark.parametrize("nx,nz,precision", [(256, 256, "fp64"), (243, 251, "fp32_ir"), (122, 239, "fp64")])
