@@ -397,6 +397,10 @@ void helm_set_tile_pivoting(int always);
  * the library. */
 size_t helm_set_cache_limit(size_t bytes);
 
+/* For tests of what happens when memory is short: of the calling thread's
+ * next allocations of factors and scratch, skip some and let `count` fail.   */
+void helm_fail_allocations(int32_t skip, int32_t count);
+
 /* Lane-layout check of the matrix-core instruction used by the kernels:
  * D = A(16x4) * B(4x16) in FP64 (prec 0) or FP32 (prec 1) on one wavefront. */
 int helm_mfma_probe(int prec, const double* A_dev, const double* B_dev, double* D_dev, void* stream);

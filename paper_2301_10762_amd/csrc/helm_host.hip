@@ -143,6 +143,19 @@ void keep_pool_memory() {
 // large blocks).
 // Blocks beyond the cache limit are released to the device's stream-ordered
 // pool, oldest first, once their last use has finished.
+//
+// helm_fail_allocations: of this thread's next allocations (blocks of the
+// cache, or pieces of a fixed region) skip some, then fail some.
+thread_local int g_fail_skip = 0, g_fail_count = 0;
+bool fail_allocation() {
+    if (g_fail_count <= 0) return false;
+    if (g_fail_skip > 0) {
+        --g_fail_skip;
+        return false;
+    }
+    --g_fail_count;
+    return true;
+}
 struct DevCache {
     struct Blk {
         void* p;
@@ -174,6 +187,7 @@ struct DevCache {
     hipError_t get(void** out, size_t bytes, hipStream_t st) {
         const size_t rb = rounded(bytes);
         int dev = 0;
+        if (fail_allocation()) return hipErrorOutOfMemory;
         (void)hipGetDevice(&dev);
         {
             // Candidates, best first: last used on this stream (already in
@@ -278,7 +292,7 @@ struct Scratch {
     int get(T** out, size_t bytes) {
         if (arena) {
             const size_t off = al256(arena->used);
-            if (off + bytes > arena->cap) return fail(HELM_ENOMEM, "scratch beyond the fixed region");
+            if (off + bytes > arena->cap || fail_allocation()) return fail(HELM_ENOMEM, "scratch beyond the fixed region");
             arena->used = off + bytes;
             *out = (T*)(arena->base + off);
             return HELM_OK;
@@ -849,23 +863,34 @@ int factor_checked(int count, const helm_grid* grids, const double* const* m_dev
             return fail(HELM_EDEVICE, "model copy failed");
         }
     }
-    // nested-dissection systems, those of one plan together
+    // nested-dissection systems, those of one plan together; where the
+    // working memory is refused fewer at a time (which changes no bit)
     std::vector<char> done(count, 0);
-    for (int c = 0; c < count; ++c) {
-        if (!fs[c]->nd || done[c]) continue;
+    int most = ND_MAXS;
+    for (int c = 0; c < count;) {
+        if (!fs[c]->nd || done[c]) {
+            ++c;
+            continue;
+        }
         const size_t work = sizeof(double2) * (size_t)(fs[c]->nd->work_elems[0] + fs[c]->nd->work_elems[1]);
-        const int room = (int)std::max<size_t>(1, std::min<size_t>(ND_MAXS, ND_WORK_BYTES / std::max<size_t>(work, 1)));
+        const int room = (int)std::max<size_t>(1, std::min<size_t>(most, ND_WORK_BYTES / std::max<size_t>(work, 1)));
         std::vector<helm_factor_s*> grp;
+        std::vector<int> of;
         for (int d = c; d < count && (int)grp.size() < room; ++d)
             if (!done[d] && fs[d]->nd == fs[c]->nd) {
                 grp.push_back(fs[d]);
-                done[d] = 1;
+                of.push_back(d);
             }
         std::vector<int> lost(grp.size(), 0);
         int rc = nd_factor_group(grp.data(), (int)grp.size(), g_force_pivot, st, lost.data());
         if (rc == HELM_OK && *bad) rc = bad_model();   // known since that wait
-        // a box at resonance, or no room to work in: the block factorisation,
-        // whose blocks reach the absorbing boundary, takes the system
+        if (rc == HELM_ENOMEM && grp.size() > 1) {
+            most = (int)grp.size() / 2;
+            continue;
+        }
+        for (int d : of) done[d] = 1;
+        // a box at resonance, or no room to work on one system: the block
+        // factorisation, whose blocks reach the absorbing boundary, takes it
         const bool room_left = rc != HELM_ENOMEM;
         if (!room_left) rc = HELM_OK;
         for (size_t q = 0; q < grp.size() && rc == HELM_OK; ++q)
@@ -2510,6 +2535,11 @@ int64_t helm_counter(int which) {
 void helm_set_tile_pivoting(int always) { g_force_pivot = always ? 1 : 0; }
 
 size_t helm_set_cache_limit(size_t bytes) { return g_cache.set_limit(bytes); }
+
+void helm_fail_allocations(int32_t skip, int32_t count) {
+    g_fail_skip = skip;
+    g_fail_count = count;
+}
 
 void helm_kernel_timing(int enable) {
     g_timer.drain();

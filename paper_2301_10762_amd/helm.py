@@ -135,6 +135,8 @@ def lib():
     L.helm_set_tile_pivoting.restype = None
     L.helm_set_cache_limit.argtypes = [ctypes.c_size_t]
     L.helm_set_cache_limit.restype = ctypes.c_size_t
+    L.helm_fail_allocations.argtypes = [i32, i32]
+    L.helm_fail_allocations.restype = None
     L.helm_mfma_probe.argtypes = [ctypes.c_int, _vp, _vp, _vp, _vp]
     L.helm_kernel_timing.argtypes = [ctypes.c_int]
     L.helm_kernel_timing.restype = None
