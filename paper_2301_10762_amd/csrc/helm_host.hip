@@ -1170,7 +1170,11 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
         smax = std::max(smax, jb->S);
         stot += jb->S;
     }
-    const size_t room = g_arena ? g_arena->cap - al256(g_arena->used) - ND_SLACK / 2 : ND_SOLVE_BYTES;
+    size_t room = ND_SOLVE_BYTES;
+    if (g_arena) {
+        const size_t taken = al256(g_arena->used) + ND_SLACK / 2;
+        room = g_arena->cap > taken ? g_arena->cap - taken : 0;
+    }
     int cols = smax;
     if (P.col_bytes() * (size_t)stot > room) {
         cols = (int)std::min<size_t>(smax, std::max<size_t>(1, room / (P.col_bytes() * n)));
@@ -1200,6 +1204,7 @@ int nd_sweep(const std::vector<SolveJob*>& js, bool correct, bool adjoint, hipSt
         return HELM_OK;
     };
     for (;;) {   // fewer columns at a time where memory is short
+        sc.reset();   // before the next one notes where the fixed region stands
         sc = std::make_unique<Scratch>(st);
         const int rc = take();
         if (rc == HELM_OK) break;

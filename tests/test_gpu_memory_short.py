@@ -48,3 +48,24 @@ def test_factor_in_smaller_groups(helm, skip, count, precision):
     for F, a, b in zip(Fs, got, want):
         assert torch.equal(a, b)
         F.close()
+
+
+# A solve of 64 columns at 201 x 201 takes the fixed region (or the cache) in
+# several pieces; refusing the fourth, and with it the first attempt, leaves
+# fewer columns at a time.
+@pytest.mark.parametrize("tol", [0.0, 1e-10])
+@pytest.mark.parametrize("noalloc", [True, False])
+def test_solve_in_fewer_columns(helm, noalloc, tol):
+    G = helm.Grid(201, 201, 0.025, 0.025)
+    ms, ws, B = _systems(1, 201, 201, 64)
+    F = helm.factor(G, ms[0], ws[0])
+    want, winfo = F.solve(B, tol=tol)
+    X = torch.full_like(B, complex(np.nan, np.nan))
+    helm.lib().helm_fail_allocations(4, 1)
+    if noalloc:
+        info = helm.solve_noalloc(F, B, X, tol=tol)
+    else:
+        X, info = F.solve(B, tol=tol)
+    helm.lib().helm_fail_allocations(0, 0)
+    assert torch.equal(X, want) and info.ir_iters == winfo.ir_iters
+    F.close()
