@@ -449,6 +449,13 @@ int check_model(const double* m, int64_t n, hipStream_t st) {
     return rc ? rc : *flag ? bad_model() : HELM_OK;
 }
 
+// host -> device copy of caller-owned host data, complete on return
+int upload_sync(void* dev, const void* src, size_t bytes, hipStream_t st) {
+    HIPCHECK(hipMemcpyAsync(dev, src, bytes, hipMemcpyHostToDevice, st));
+    HIPCHECK(hipStreamSynchronize(st));
+    return HELM_OK;
+}
+
 // ------------------------------------------------ nested-dissection plans --
 // Panel-step launches of the block factorisation of one system.
 int block_steps(const helm_grid& g) {
@@ -471,52 +478,120 @@ constexpr int64_t ND_MAX_NODES = (int64_t)1 << 26;   // the plan's tables are in
 
 // The plans made so far, one per (device, nx, nz): a plan depends on nothing
 // else, is read-only once made, and is shared by the factors of that grid on
-// every thread and stream.  Plans no factor uses are kept for the next one,
-// up to PLAN_KEEP of them; the oldest of the others is given back when a new
-// plan is made (hipFree waits for work that may still read its tables).
+// every thread and stream.  Plans no factor uses are kept for the next one, up
+// to PLAN_KEEP of them and PLAN_KEEP_BYTES of device memory (a plan takes 0.3 MB
+// at 101^2, 4.2 MB at 401^2; building one 0.4 and 6 ms of host time); the oldest
+// beyond go to the block cache, once no kernel reads them.  Only the list is
+// under one mutex: a plan is built under its own, so that other grids' factors
+// do not wait for it.
 struct PlanCache {
-    static constexpr size_t PLAN_KEEP = 16;
-    struct Entry {
+    static constexpr size_t PLAN_KEEP = 256, PLAN_KEEP_BYTES = (size_t)1 << 30;
+    struct Slot {
         int dev, nx, nz;
-        int64_t elems;
-        std::shared_ptr<NdPlan> plan;   // null: described only
+        std::mutex mu;
+        int64_t elems = -1;             // -1: not counted yet
+        std::shared_ptr<NdPlan> plan;   // null: not built
     };
     std::mutex mu;
-    std::vector<Entry> entries;   // oldest use first
+    std::vector<std::shared_ptr<Slot>> slots;   // oldest use first
 
-    Entry& find_locked(int dev, int nx, int nz) {
-        for (size_t q = 0; q < entries.size(); ++q)
-            if (entries[q].dev == dev && entries[q].nx == nx && entries[q].nz == nz) {
-                std::rotate(entries.begin() + q, entries.begin() + q + 1, entries.end());
-                return entries.back();
+    std::shared_ptr<Slot> find(int dev, int nx, int nz) {
+        std::lock_guard<std::mutex> lk(mu);
+        for (size_t q = 0; q < slots.size(); ++q)
+            if (slots[q]->dev == dev && slots[q]->nx == nx && slots[q]->nz == nz) {
+                std::rotate(slots.begin() + q, slots.begin() + q + 1, slots.end());
+                return slots.back();
             }
-        size_t idle = 0;
-        for (auto& e : entries) idle += e.plan.use_count() <= 1;
-        for (size_t q = 0; q < entries.size() && idle >= PLAN_KEEP; ++q)
-            if (entries[q].plan.use_count() <= 1) {
-                if (entries[q].plan) {
-                    (void)hipFree(entries[q].plan->mem);
-                    (void)hipFree(entries[q].plan->reserve);
-                }
-                entries.erase(entries.begin() + q);
-                break;
-            }
-        entries.push_back({dev, nx, nz, nd_factor_elems(nx, nz), nullptr});
-        return entries.back();
+        auto s = std::make_shared<Slot>();
+        s->dev = dev;
+        s->nx = nx;
+        s->nz = nz;
+        slots.push_back(s);
+        return s;
     }
-    int get(int nx, int nz, int64_t max_elems, std::shared_ptr<NdPlan>* out);
+    void trim(int dev, hipStream_t st);
+    int get(int nx, int nz, int64_t max_elems, hipStream_t st, std::shared_ptr<NdPlan>* out);
 };
 PlanCache g_plans;
 constexpr size_t NOALLOC_BYTES = (size_t)256 << 20;   // fixed region of helm_solve_noalloc
 constexpr size_t ND_SLACK = (size_t)1 << 20;          // of it, for tables and alignment
 
-// The plan of a grid, or null where its factor would exceed max_elems.
-int PlanCache::get(int nx, int nz, int64_t max_elems, std::shared_ptr<NdPlan>* out) {
+// a factor of this plan is being released; st is in order after every use of it
+void note_release(NdPlan* p, hipStream_t st) {
+    std::lock_guard<std::mutex> lk(p->mu);
+    for (auto& e : p->last)
+        if (e.first == st) {
+            (void)hipEventRecord(e.second, st);
+            return;
+        }
+    hipEvent_t ev;
+    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipStreamSynchronize(st);
+        return;
+    }
+    (void)hipEventRecord(ev, st);
+    p->last.push_back({st, ev});
+}
+
+// Gives the oldest idle plans of device dev (the current one) beyond the
+// limits back; one that may still be read is left for a later call.
+void PlanCache::trim(int dev, hipStream_t st) {
+    std::vector<std::shared_ptr<Slot>> out;
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        // the list's reference alone is left, so no call can take the plan now
+        auto idle = [&](const std::shared_ptr<Slot>& s) {
+            return s->dev == dev && s.use_count() == 1 && s->plan.use_count() <= 1;
+        };
+        auto bytes = [](const Slot& s) { return s.plan ? s.plan->mem_bytes + s.plan->reserve_bytes : 0; };
+        size_t n = 0, held = 0;
+        for (auto& s : slots)
+            if (idle(s)) {
+                ++n;
+                held += bytes(*s);
+            }
+        for (size_t q = 0; q < slots.size() && (n > PLAN_KEEP || held > PLAN_KEEP_BYTES);) {
+            bool free = idle(slots[q]);
+            if (free && slots[q]->plan) {
+                std::lock_guard<std::mutex> lp(slots[q]->plan->mu);
+                for (auto& e : slots[q]->plan->last)
+                    if (free && hipEventQuery(e.second) != hipSuccess) {
+                        (void)hipGetLastError();
+                        free = false;
+                    }
+            }
+            if (!free) {
+                ++q;
+                continue;
+            }
+            --n;
+            held -= bytes(*slots[q]);
+            out.push_back(std::move(slots[q]));
+            slots.erase(slots.begin() + q);
+        }
+    }
+    for (auto& s : out)
+        if (NdPlan* p = s->plan.get()) {
+            for (auto& e : p->last) (void)hipEventDestroy(e.second);
+            g_cache.put(p->mem, p->mem_bytes, st);
+            g_cache.put(p->reserve, p->reserve_bytes, st);
+        }
+}
+
+// The plan of a grid, or null where its factor would exceed max_elems.  A new
+// one is uploaded on st, which is waited for.
+int PlanCache::get(int nx, int nz, int64_t max_elems, hipStream_t st, std::shared_ptr<NdPlan>* out) {
     out->reset();
     int dev = 0;
     HIPCHECK(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lk(mu);
-    Entry& e = find_locked(dev, nx, nz);
+    auto slot = find(dev, nx, nz);
+    std::lock_guard<std::mutex> lk(slot->mu);
+    Slot& e = *slot;
+    if (e.elems < 0) {   // new in the list
+        trim(dev, st);
+        e.elems = nd_factor_elems(nx, nz);
+    }
     if (e.elems > max_elems) return HELM_OK;
     if (!e.plan) {
         auto p = std::make_shared<NdPlan>();
@@ -546,22 +621,22 @@ int PlanCache::get(int nx, int nz, int64_t max_elems, std::shared_ptr<NdPlan>* o
         std::vector<char> host(need);
         for (auto& q : parts)
             if (q.bytes) std::memcpy(host.data() + q.at, q.src, q.bytes);
-        if (hipMalloc(&p->mem, need) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(HELM_ENOMEM, "plan allocation of " + std::to_string(need) + " bytes failed");
-        }
-        if (p->col_bytes() + ND_SLACK > NOALLOC_BYTES) {
-            p->reserve_bytes = p->col_bytes() + ND_SLACK;
-            if (hipMalloc(&p->reserve, p->reserve_bytes) != hipSuccess) {
-                (void)hipGetLastError();
-                (void)hipFree(p->mem);
-                return fail(HELM_ENOMEM, "plan allocation of " + std::to_string(p->reserve_bytes) + " bytes failed");
+        int rc = HELM_OK;
+        auto room = [&](void** m, size_t* have, size_t bytes) {
+            if (rc == HELM_OK && g_cache.get(m, bytes, st) != hipSuccess) {
+                *m = nullptr;
+                rc = fail(HELM_ENOMEM, "plan allocation of " + std::to_string(bytes) + " bytes failed");
+            } else if (rc == HELM_OK) {
+                *have = bytes;
             }
-        }
-        if (hipMemcpy(p->mem, host.data(), need, hipMemcpyHostToDevice) != hipSuccess) {
-            (void)hipFree(p->mem);
-            (void)hipFree(p->reserve);
-            return fail(HELM_EDEVICE, "plan upload failed");
+        };
+        room(&p->mem, &p->mem_bytes, need);
+        if (p->col_bytes() + ND_SLACK > NOALLOC_BYTES) room(&p->reserve, &p->reserve_bytes, p->col_bytes() + ND_SLACK);
+        if (rc == HELM_OK) rc = upload_sync(p->mem, host.data(), need, st);
+        if (rc) {
+            g_cache.put(p->mem, p->mem_bytes, st);
+            g_cache.put(p->reserve, p->reserve_bytes, st);
+            return rc;
         }
         char* m = (char*)p->mem;
         p->d_fronts = (const NdFront*)(m + parts[0].at);
@@ -593,13 +668,13 @@ NdTabs nd_tabs(const NdPlan& p) {
 
 // The plan for a system of this grid and precision, or null where the block
 // factorisation serves it.
-int nd_choose(const helm_grid& g, int prec, std::shared_ptr<NdPlan>* out) {
+int nd_choose(const helm_grid& g, int prec, hipStream_t st, std::shared_ptr<NdPlan>* out) {
     out->reset();
     if (!nd_pays(g) || N_of(g) > ND_MAX_NODES) return HELM_OK;
     const int64_t np = pad16(g.nx);
     int rc;
     try {
-        rc = g_plans.get(g.nx, g.nz, np * np * g.nz * (int64_t)elem_bytes(prec) / 16, out);
+        rc = g_plans.get(g.nx, g.nz, np * np * g.nz * (int64_t)elem_bytes(prec) / 16, st, out);
     } catch (const std::bad_alloc&) {
         rc = HELM_ENOMEM;
     }
@@ -778,6 +853,7 @@ void destroy(helm_factor_s* f) {
         }
         f->uses.clear();
     }
+    if (f->nd) note_release(f->nd.get(), f->st);
     if (f->G) g_cache.put(f->G, f->gbytes, f->st);
     if (f->m) g_cache.put(f->m, sizeof(double) * N_of(f->g), f->st);
     delete f;
@@ -846,7 +922,7 @@ int factor_checked(int count, const helm_grid* grids, const double* const* m_dev
         f->prec = prec;
         f->omega = omegas[c];
         f->st = st;
-        int rc = nd_choose(grids[c], prec, &f->nd);
+        int rc = nd_choose(grids[c], prec, st, &f->nd);
         if (rc == HELM_OK) rc = store(f, f->nd ? sizeof(double2) * (size_t)f->nd->fac_elems : block_bytes(f));
         if (rc) {
             cleanup();
@@ -896,6 +972,7 @@ int factor_checked(int count, const helm_grid* grids, const double* const* m_dev
         for (size_t q = 0; q < grp.size() && rc == HELM_OK; ++q)
             if (lost[q] || !room_left) {
                 g_cache.put(grp[q]->G, grp[q]->gbytes, st);
+                note_release(grp[q]->nd.get(), st);
                 grp[q]->nd.reset();
                 rc = store(grp[q], block_bytes(grp[q]));
             }
@@ -1520,13 +1597,6 @@ int block_solve_jobs(std::vector<SolveJob>& jobs, bool adjoint, double tol, hipS
                                                               std::to_string(rels[c]) + " > " + std::to_string(tol));
     }
     return worst;
-}
-
-// host -> device copy of caller-owned host data, complete on return
-int upload_sync(void* dev, const void* src, size_t bytes, hipStream_t st) {
-    HIPCHECK(hipMemcpyAsync(dev, src, bytes, hipMemcpyHostToDevice, st));
-    HIPCHECK(hipStreamSynchronize(st));
-    return HELM_OK;
 }
 
 int check_solve_args(const helm_factor_s* f, const double* B, double* X, int S, int64_t ld) {

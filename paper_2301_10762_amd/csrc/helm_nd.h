@@ -2,6 +2,8 @@
 // and the tables the kernels read.  Host and device.
 #pragma once
 #include <memory>
+#include <mutex>
+#include <utility>
 #include <vector>
 
 #include "helm_internal.h"
@@ -130,6 +132,11 @@ struct NdPlan {
     int64_t work_elems[2] = {0, 0};  // working memory of even and odd levels, per system
     int64_t urows[2] = {0, 0};       // ring-contribution rows of even and odd levels
     void* mem = nullptr;             // device tables
+    size_t mem_bytes = 0;
+    // where each stream stood when a factor of this plan was last released on
+    // it: once these have passed no kernel reads the tables
+    std::mutex mu;
+    std::vector<std::pair<hipStream_t, hipEvent_t>> last;
     void* reserve = nullptr;         // scratch of one column's solve (grids beyond the fixed region only)
     size_t reserve_bytes = 0;
     const NdFront* d_fronts = nullptr;
