@@ -685,51 +685,176 @@ int nd_choose(const helm_grid& g, int prec, hipStream_t st, std::shared_ptr<NdPl
     return rc;
 }
 
-// Factor at most ND_MAXS systems of one plan together.  lost[c] is set where
+// Side streams for the groups of a call whose grids differ: their launches are
+// chains too short to fill the GPU, and independent.  The call's own stream
+// takes a share of the groups; the side streams start after the work queued on
+// it and it waits for them at the end, so that for the caller everything is
+// still on that one stream.  (Eight grids of 33 to 60 nodes a side: one group
+// after the other, with a wait for each factorisation, 1430 us to factor and
+// 850 to solve, on four streams 710 and 520.)
+// Streams are kept for reuse, at most FORK_KEEP of a device; work left on one
+// is in order before its next user's.
+struct Fork {
+    static constexpr size_t SIDE = 3, FORK_KEEP = 16;
+    struct Side {
+        int dev;
+        hipStream_t st;
+        hipEvent_t ev;
+    };
+    static std::mutex mu;
+    static std::vector<Side> kept;
+    hipStream_t st;
+    std::vector<Side> sides;
+    bool joined = true;
+
+    // want: independent groups; nothing is forked for one, in an allocation-free
+    // call or under stream capture
+    Fork(hipStream_t s, size_t want) : st(s) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (want < 2 || g_arena) return;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return;
+        }
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        while (sides.size() < std::min(SIDE, want - 1)) {
+            Side x{dev, nullptr, nullptr};
+            {
+                std::lock_guard<std::mutex> lk(mu);
+                for (size_t q = 0; q < kept.size() && !x.st; ++q)
+                    if (kept[q].dev == dev) {
+                        x = kept[q];
+                        kept.erase(kept.begin() + q);
+                    }
+            }
+            if (!x.st && (hipStreamCreateWithFlags(&x.st, hipStreamNonBlocking) != hipSuccess ||
+                          hipEventCreateWithFlags(&x.ev, hipEventDisableTiming) != hipSuccess)) {
+                (void)hipGetLastError();
+                if (x.st) (void)hipStreamDestroy(x.st);
+                break;
+            }
+            sides.push_back(x);
+        }
+    }
+    Fork(const Fork&) = delete;
+    Fork& operator=(const Fork&) = delete;
+    ~Fork() {
+        (void)join();
+        size_t n = 0;
+        std::lock_guard<std::mutex> lk(mu);
+        for (auto& x : sides) {
+            for (auto& k : kept) n += k.dev == x.dev;
+            if (n < FORK_KEEP) {
+                kept.push_back(x);
+            } else {
+                (void)hipEventDestroy(x.ev);
+                (void)hipStreamDestroy(x.st);
+            }
+            n = 0;
+        }
+    }
+    // from here on stream(g) is where group g goes
+    int start() {
+        if (sides.empty()) return HELM_OK;
+        HIPCHECK(hipEventRecord(sides[0].ev, st));
+        joined = false;
+        for (auto& x : sides) HIPCHECK(hipStreamWaitEvent(x.st, sides[0].ev, 0));
+        return HELM_OK;
+    }
+    hipStream_t stream(size_t g) const {
+        const size_t k = g % (sides.size() + 1);
+        return k ? sides[k - 1].st : st;
+    }
+    int join() {
+        if (joined) return HELM_OK;
+        joined = true;
+        hipError_t e = hipSuccess;
+        for (auto& x : sides) {
+            hipError_t a = hipEventRecord(x.ev, x.st);
+            if (a == hipSuccess) a = hipStreamWaitEvent(st, x.ev, 0);
+            if (a != hipSuccess) e = a;
+        }
+        HIPCHECK(e);
+        return HELM_OK;
+    }
+};
+std::mutex Fork::mu;
+std::vector<Fork::Side> Fork::kept;
+
+// At most ND_MAXS systems of one plan, factored together.  lost[c] is set where
 // system c met an exactly zero pivot, or one so small that no solve would
 // recover its digits.
-int nd_factor_group(helm_factor_s* const* fs, int n, int pivot, hipStream_t st, int* lost) {
-    const NdPlan& P = *fs[0]->nd;
-    Scratch sc(st);
-    double2 *w0, *w1;
-    int* status;
-    NdSysTab* dtab;
-    int rc;
-    if ((rc = sc.get(&w0, sizeof(double2) * (size_t)P.work_elems[0] * n))) return rc;
-    if ((rc = sc.get(&w1, sizeof(double2) * (size_t)P.work_elems[1] * n))) return rc;
-    if ((rc = sc.get(&status, sizeof(int) * 4 * n))) return rc;
-    if ((rc = sc.get(&dtab, sizeof(NdSysTab)))) return rc;
-    launch_zero(status, sizeof(int) * 4 * n, st);
-    NdSysTab tab;
-    std::memset(&tab, 0, sizeof(tab));
-    for (int c = 0; c < n; ++c) {
-        NdSys& s = tab.s[c];
-        s.cf = coef_of(fs[c]);
-        s.fac = (double2*)fs[c]->G;
-        s.work[0] = w0 + (size_t)P.work_elems[0] * c;
-        s.work[1] = w1 + (size_t)P.work_elems[1] * c;
-        s.status = status + 4 * c;
-        s.pivot = pivot;
+struct NdGroup {
+    std::vector<helm_factor_s*> fs;
+    std::vector<int> of, lost;   // their places in the call
+    const NdPlan& plan() const { return *fs[0]->nd; }
+    size_t work() const {
+        return sizeof(double2) * (size_t)(plan().work_elems[0] + plan().work_elems[1]) * fs.size();
     }
-    launch_nd_put_sys(tab, dtab, st);
-    const NdTabs t = nd_tabs(P);
-    KernelTimer::Pair pu;
-    const bool tu = g_timer.begin(0, st, &pu);
-    int64_t launches = 0;
-    for (auto& lv : P.levels) HIPCHECK(launch_nd_level(t, lv, dtab, n, st, &launches));
-    if (tu) g_timer.end(pu, launches, st);
-    g_launches += 2 + launches;
-    HIPCHECK(hipGetLastError());
+};
+
+// Factor several groups, with one wait for all.  HELM_ENOMEM: nothing was launched.
+int nd_factor_groups(std::vector<NdGroup>& gs, int pivot, hipStream_t st) {
+    struct Mem {
+        double2 *w0, *w1;
+        NdSysTab* dtab;
+    };
+    Scratch sc(st);
+    std::vector<Mem> mem(gs.size());
+    int rc, *status, *hs, total = 0;
+    for (size_t g = 0; g < gs.size(); ++g) {
+        const NdPlan& P = gs[g].plan();
+        const size_t n = gs[g].fs.size();
+        if ((rc = sc.get(&mem[g].w0, sizeof(double2) * (size_t)P.work_elems[0] * n))) return rc;
+        if ((rc = sc.get(&mem[g].w1, sizeof(double2) * (size_t)P.work_elems[1] * n))) return rc;
+        if ((rc = sc.get(&mem[g].dtab, sizeof(NdSysTab)))) return rc;
+        total += (int)n;
+    }
+    if ((rc = sc.get(&status, sizeof(int) * 4 * total))) return rc;
     HostBlock hb(st);
-    int* hs;
-    if ((rc = hb.get(&hs, sizeof(int) * 4 * n))) return rc;
-    launch_copy_words(status, hs, 4 * n, st);
+    if ((rc = hb.get(&hs, sizeof(int) * 4 * total))) return rc;
+    launch_zero(status, sizeof(int) * 4 * total, st);
+    g_launches += 1;
+    Fork fork(st, gs.size());
+    if ((rc = fork.start())) return rc;
+    int at = 0;
+    for (size_t g = 0; g < gs.size(); ++g) {
+        const NdPlan& P = gs[g].plan();
+        const int n = (int)gs[g].fs.size();
+        const hipStream_t sg = fork.stream(g);
+        NdSysTab tab;
+        std::memset(&tab, 0, sizeof(tab));
+        for (int c = 0; c < n; ++c, ++at) {
+            NdSys& s = tab.s[c];
+            s.cf = coef_of(gs[g].fs[c]);
+            s.fac = (double2*)gs[g].fs[c]->G;
+            s.work[0] = mem[g].w0 + (size_t)P.work_elems[0] * c;
+            s.work[1] = mem[g].w1 + (size_t)P.work_elems[1] * c;
+            s.status = status + 4 * at;
+            s.pivot = pivot;
+        }
+        launch_nd_put_sys(tab, mem[g].dtab, sg);
+        const NdTabs t = nd_tabs(P);
+        KernelTimer::Pair pu;
+        const bool tu = g_timer.begin(0, sg, &pu);
+        int64_t launches = 0;
+        for (auto& lv : P.levels) HIPCHECK(launch_nd_level(t, lv, mem[g].dtab, n, sg, &launches));
+        if (tu) g_timer.end(pu, launches, sg);
+        g_launches += 1 + launches;
+    }
+    if ((rc = fork.join())) return rc;
+    HIPCHECK(hipGetLastError());
+    launch_copy_words(status, hs, 4 * total, st);
     g_launches += 1;
     if ((rc = hb.wait())) return rc;
-    for (int c = 0; c < n; ++c) {
-        const int grown = hs[4 * c + 3];
-        lost[c] = hs[4 * c] != 0 || (grown & 8);
-        fs[c]->fixes = (grown & 1) + (grown >> 1 & 1) + (grown >> 2 & 1);
+    for (auto& g : gs) {
+        g.lost.assign(g.fs.size(), 0);
+        for (size_t c = 0; c < g.fs.size(); ++c, hs += 4) {
+            const int grown = hs[3];
+            g.lost[c] = hs[0] != 0 || (grown & 8);
+            g.fs[c]->fixes = (grown & 1) + (grown >> 1 & 1) + (grown >> 2 & 1);
+        }
     }
     return HELM_OK;
 }
@@ -939,42 +1064,49 @@ int factor_checked(int count, const helm_grid* grids, const double* const* m_dev
             return fail(HELM_EDEVICE, "model copy failed");
         }
     }
-    // nested-dissection systems, those of one plan together; where the
-    // working memory is refused fewer at a time (which changes no bit)
+    // nested-dissection systems, those of one plan together, as many groups at
+    // a time as their working memory allows; where it is refused fewer (which
+    // changes no bit)
     std::vector<char> done(count, 0);
-    int most = ND_MAXS;
-    for (int c = 0; c < count;) {
-        if (!fs[c]->nd || done[c]) {
-            ++c;
-            continue;
+    size_t most = ND_MAXS, groups = count;
+    for (;;) {
+        std::vector<NdGroup> wave;
+        std::vector<char> taken(done);
+        size_t held = 0;
+        for (int c = 0; c < count && wave.size() < groups; ++c) {
+            if (!fs[c]->nd || taken[c]) continue;
+            const size_t one = sizeof(double2) * (size_t)(fs[c]->nd->work_elems[0] + fs[c]->nd->work_elems[1]);
+            const size_t room = std::max<size_t>(1, std::min(most, ND_WORK_BYTES / std::max<size_t>(one, 1)));
+            NdGroup g;
+            for (int d = c; d < count && g.fs.size() < room; ++d)
+                if (!taken[d] && fs[d]->nd == fs[c]->nd) {
+                    g.fs.push_back(fs[d]);
+                    g.of.push_back(d);
+                    taken[d] = 1;
+                }
+            if (!wave.empty() && held + g.work() > ND_WORK_BYTES) break;
+            held += g.work();
+            wave.push_back(std::move(g));
         }
-        const size_t work = sizeof(double2) * (size_t)(fs[c]->nd->work_elems[0] + fs[c]->nd->work_elems[1]);
-        const int room = (int)std::max<size_t>(1, std::min<size_t>(most, ND_WORK_BYTES / std::max<size_t>(work, 1)));
-        std::vector<helm_factor_s*> grp;
-        std::vector<int> of;
-        for (int d = c; d < count && (int)grp.size() < room; ++d)
-            if (!done[d] && fs[d]->nd == fs[c]->nd) {
-                grp.push_back(fs[d]);
-                of.push_back(d);
-            }
-        std::vector<int> lost(grp.size(), 0);
-        int rc = nd_factor_group(grp.data(), (int)grp.size(), g_force_pivot, st, lost.data());
+        if (wave.empty()) break;
+        int rc = nd_factor_groups(wave, g_force_pivot, st);
         if (rc == HELM_OK && *bad) rc = bad_model();   // known since that wait
-        if (rc == HELM_ENOMEM && grp.size() > 1) {
-            most = (int)grp.size() / 2;
+        if (rc == HELM_ENOMEM && (wave.size() > 1 || wave[0].fs.size() > 1)) {
+            (wave.size() > 1 ? groups : most) = std::max<size_t>(1, (wave.size() > 1 ? wave.size() : wave[0].fs.size()) / 2);
             continue;
         }
-        for (int d : of) done[d] = 1;
         // a box at resonance, or no room to work on one system: the block
         // factorisation, whose blocks reach the absorbing boundary, takes it
         const bool room_left = rc != HELM_ENOMEM;
         if (!room_left) rc = HELM_OK;
-        for (size_t q = 0; q < grp.size() && rc == HELM_OK; ++q)
-            if (lost[q] || !room_left) {
-                g_cache.put(grp[q]->G, grp[q]->gbytes, st);
-                note_release(grp[q]->nd.get(), st);
-                grp[q]->nd.reset();
-                rc = store(grp[q], block_bytes(grp[q]));
+        for (auto& g : wave)
+            for (size_t q = 0; q < g.fs.size() && rc == HELM_OK; ++q) {
+                done[g.of[q]] = 1;
+                if (room_left && !g.lost[q]) continue;
+                g_cache.put(g.fs[q]->G, g.fs[q]->gbytes, st);
+                note_release(g.fs[q]->nd.get(), st);
+                g.fs[q]->nd.reset();
+                rc = store(g.fs[q], block_bytes(g.fs[q]));
             }
         if (rc) {
             cleanup();
@@ -1347,17 +1479,24 @@ int nd_solve_jobs(std::vector<SolveJob*>& jobs, bool adjoint, double tol, hipStr
     if (refined && tol <= 0.0) tol = 1e-10;
     auto sweep = [&](const std::vector<int>& idx, bool correct) -> int {
         std::vector<char> done(n, 0);
+        std::vector<std::vector<SolveJob*>> grps;
+        size_t bytes = 0;
         for (int c : idx) {
             if (done[c]) continue;
-            std::vector<SolveJob*> grp;
+            grps.emplace_back();
             for (int d : idx)
-                if (!done[d] && jobs[d]->f->nd == jobs[c]->f->nd && (int)grp.size() < ND_MAXS) {
-                    grp.push_back(jobs[d]);
+                if (!done[d] && jobs[d]->f->nd == jobs[c]->f->nd && (int)grps.back().size() < ND_MAXS) {
+                    grps.back().push_back(jobs[d]);
+                    bytes += jobs[d]->f->nd->col_bytes() * (size_t)jobs[d]->S;
                     done[d] = 1;
                 }
-            if (int rc = nd_sweep(grp, correct, adjoint, st)) return rc;
         }
-        return HELM_OK;
+        // side by side while all of their scratch fits
+        Fork fork(st, bytes <= ND_SOLVE_BYTES ? grps.size() : 1);
+        if (int rc = fork.start()) return rc;
+        for (size_t g = 0; g < grps.size(); ++g)
+            if (int rc = nd_sweep(grps[g], correct, adjoint, fork.stream(g))) return rc;
+        return fork.join();
     };
     std::vector<int> act(n), iters(n, 0);
     for (int c = 0; c < n; ++c) act[c] = c;
