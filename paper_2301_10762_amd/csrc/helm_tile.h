@@ -297,7 +297,9 @@ __device__ __forceinline__ void gj16_wave(typename CT<T>::c (&a)[4], float thr, 
 }
 
 // One wavefront's part of a 16 x 16 complex product on the matrix cores:
-// d = c0 + sign A B, with A read by rows from LDS (stride 33) or from
+// d = c0 + sign A B (the product by itself, then one addition: accumulated onto
+// c0 every step rounds at its size, and complex64 solutions of 30 x 60 grids
+// were 1.7 times as far off), with A read by rows from LDS (stride 33) or from
 // registers (a[e] = A[lr][acc_row(lg, e)]), B from LDS or from registers
 // (b[e] = B[acc_row(lg, e)][lr]); results as b is.
 template <typename T>
@@ -326,13 +328,12 @@ __device__ __forceinline__ void mm16(const typename CT<T>::c (&a)[4], const type
     constexpr bool GAUSS = sizeof(T) == 8;   // three real products per complex one in complex128
     V re, im, a1, a2, a3;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { re[e] = c0[e].x; im[e] = c0[e].y; }
-    cacc_seed<GAUSS, V>(a1, a2, a3, re, im);
+    for (int e = 0; e < 4; ++e) { a1[e] = 0; a2[e] = 0; a3[e] = 0; }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) cacc<GAUSS, T, V>(a1, a2, a3, sign * a[e].x, sign * a[e].y, b[e].x, b[e].y);
+    for (int e = 0; e < 4; ++e) cacc<GAUSS, T, V>(a1, a2, a3, a[e].x, a[e].y, b[e].x, b[e].y);
     cacc_final<GAUSS, V>(a1, a2, a3, re, im);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) d[e] = mk<C>(re[e], im[e]);
+    for (int e = 0; e < 4; ++e) d[e] = mk<C>(c0[e].x + sign * re[e], c0[e].y + sign * im[e]);
 }
 
 // The unpivoted inverse of the kb x kb tile in a[] (256-thread layout of the
