@@ -5,10 +5,10 @@ Workload (one "step"): the 401 x 401 layered-model configuration with five
 frequencies (1.5, 2.25, 3, 4.5, 6 Hz at 25 m spacing), 64 point sources per
 frequency: factor the five systems A(m, w) (nested dissection, the five
 systems' fronts in shared launches) and solve all 5 x 64 right-hand sides to a
-relative residual <= 1e-10.  The headline form is the refined one (its factors
-are held in complex128 at this size, and a system is corrected when its
-residual is above a tenth of the tolerance); the plain FP64 form, which keeps
-two digits in reserve, is timed beside it.
+relative residual <= 1e-10.  The headline form is the refined one; its factors
+are held in complex128 at this size, as those of the plain FP64 form timed
+beside it, and in both a system is corrected where boxes of the dissection near
+resonance left more than a complex128 factorisation row by row would.
 
 Metric: right-hand-side solves per second (5 x 64 per step / step time),
 with p50/p99 step latency.  Inputs are seeded synthetic layered models

@@ -26,7 +26,7 @@
 namespace helm {
 
 // ----------------------------------------------------------------- launches --
-// LDS of a step workgroup: update tiles use sW, sV (64 x 33 each); the
+// LDS of a step workgroup: update tiles use sW (32 x 33) and sV (64 x 33); the
 // next-tile workgroup four 32 x 33 blocks and the pivoting scratch
 template <typename T>
 constexpr size_t sm_bytes() {

@@ -10,9 +10,18 @@
 
 namespace helm {
 
-// Nodes of a subtree that one workgroup sweeps: with 16 columns its vectors
-// take about 57 KB of LDS, so that two workgroups share a CU.
+// Nodes of a leaf box.  A leaf keeps its whole inverse, so the factor's size
+// and the solves' work grow with this, and the number of levels falls: 36
+// (6 x 6) is taken where the factor then still fits the room of the complex64
+// block factor it replaces, 16 elsewhere (narrow grids).
+constexpr int ND_LEAF_MAX = 36, ND_LEAF_MIN = 16;
+
+// Nodes of a subtree that one workgroup sweeps.  With 16 columns its vectors
+// and tables take 63 to 75 KB of LDS forward and 73 to 84 KB backward (12 x 12
+// boxes at 401^2, 13 x 13 at 55^2), so that two workgroups share a compute unit,
+// backward all but the largest.
 constexpr int ND_SUB = 170;
+static_assert(17 * 17 > ND_SUB, "the subtree kernels take separators of at most 16 nodes");
 constexpr int ND_SUB_LEAVES = 16;   // 16-row tiles of its leaves, at most
 constexpr int ND_SUB_EXT = 224;     // nodes with the separators right of it and below it, at most
 

@@ -200,7 +200,7 @@ __device__ __noinline__ int nd_pivoted(double2* S, double2* D, int ld, int n) {
 }
 
 // ------------------------------------------------------------------- leaves --
-// G = A^{-1} of a leaf box (at most 48 nodes), one wavefront per leaf: the
+// G = A^{-1} of a leaf box (at most ND_LEAF_MAX nodes), one wavefront per leaf: the
 // upper 16 x 16 tiles in accumulator registers, panels of 16 pivots through
 // LDS.  Per panel K, with C_I = M_IK (from the stored upper tiles; M_KI =
 // s_I M_IK^T, s_I = -1 where I is eliminated) and T the inverse of tile KK:
@@ -213,6 +213,7 @@ __device__ __noinline__ int nd_pivoted(double2* S, double2* D, int ld, int n) {
 // 36 nodes take 420 us, whose factor is 425 MB to write (94 us at the rate of
 // a copy).
 constexpr int LT = 3;
+static_assert(16 * LT >= ND_LEAF_MAX, "a leaf's tiles");
 __global__ __launch_bounds__(64, 2) void k_nd_leaf(NdTabs t, int first, const NdSysTab* __restrict__ stab) {
     constexpr int NTT = LT * (LT + 1) / 2;
     __shared__ double2 sC[LT * 16][17];   // C; rows of the panel itself hold its diagonal tile
@@ -542,7 +543,7 @@ __global__ __launch_bounds__(KP == 16 ? 256 : 512, KP == 16 ? 4 : 2) void k_nd_f
 // inverse) bounds the levels near the root, 12.5 us a panel at 401^2; with
 // many fronts the update tiles do, in 32 x 64 so that three share a compute
 // unit (5 systems of 401^2, 39 steps: 1314 us in 64 x 64 tiles of four real
-// products, 1132 now).
+// products, 1132 in these, 1082 with the next tile's workgroup ahead).
 __device__ __forceinline__ double2* nd_rows(const NdFront& f, double2* work, int step) {
     const int64_t n = (int64_t)f.pp * f.fp;
     return work + f.work + (step == 0 ? 0 : n * (1 + (step & 1)));
@@ -983,7 +984,8 @@ constexpr int SUB_RS = 17;                                  // LDS row: 16 colum
 constexpr int SUB_LD = (ND_SUB * 16 + SUB_T - 1) / SUB_T;   // (node, column) pairs per thread
 constexpr int SUB_LDX = (ND_SUB_EXT * 16 + SUB_T - 1) / SUB_T;
 constexpr int SUB_LJ = ND_SUB_LEAVES / SUB_W;               // leaf row tiles per wavefront
-constexpr int SUB_K = 9;                                    // MFMA steps (of 4) of a leaf's 36 nodes
+constexpr int SUB_K = ND_LEAF_MAX / 4;                      // MFMA steps (of 4) of a leaf's nodes
+static_assert(4 * SUB_K == ND_LEAF_MAX, "a leaf's nodes in whole steps");
 
 // record i of a shape's table (in LDS), the same in all lanes
 template <typename R>
@@ -1468,7 +1470,7 @@ __global__ __launch_bounds__(256, 4) void k_nd_forward(NdTabs t, int first, int 
     }
 }
 
-// Backward: x = G y - R^T x_ring, one 16-row tile of a front for 16 columns,
+// Backward: x = G y - R x_ring, one 16-row tile of a front for 16 columns,
 // by a wavefront (SPLIT: by four that share the contraction).  The operands
 // are read straight from L2: their rows are whole, one load each, and staging
 // them in LDS for several tiles was slower at every level (401^2, 64 columns,

@@ -13,12 +13,6 @@ namespace helm {
 
 namespace {
 
-// Nodes of a leaf box.  A leaf keeps its whole inverse, so the factor's size
-// and the solves' work grow with this, and the number of levels falls: 36
-// (6 x 6) is taken where the factor then still fits the room of the complex64
-// block factor it replaces, 16 elsewhere (narrow grids).
-constexpr int ND_LEAF_MAX = 36, ND_LEAF_MIN = 16;
-
 struct Box {
     int x0, x1, z0, z1, depth;
     int child[2];
