@@ -852,8 +852,10 @@ int nd_factor_groups(std::vector<NdGroup>& gs, int pivot, hipStream_t st) {
         g.lost.assign(g.fs.size(), 0);
         for (size_t c = 0; c < g.fs.size(); ++c, hs += 4) {
             const int grown = hs[3];
-            g.lost[c] = hs[0] != 0 || (grown & 8);
-            g.fs[c]->fixes = (grown & 1) + (grown >> 1 & 1) + (grown >> 2 & 1);
+            g.lost[c] = hs[0] != 0 || (grown >> (ND_STEPS - 1) & 1);
+            g.fs[c]->fixes = 0;
+            for (int k = 0; k < ND_STEPS - 1; ++k)
+                if (grown >> k & 1) g.fs[c]->fixes = ND_FIXES[k];
         }
     }
     return HELM_OK;

@@ -175,13 +175,15 @@ struct NdTabs {
 
 constexpr int ND_MAXS = 16;   // systems per launch
 
-// Steps of the largest |T_ij|^2 (tile inverses, in couplings) that count: above
-// 3, 10^4 and 10^5 couplings a solve without a tolerance takes one, two and
-// three corrections (residuals before any: below 3 couplings what block
-// factors leave, 33^2 to 401^2; 2e-8 at 10^4, growing with its square; each
-// correction multiplies by as much again), above 10^6 the system is factored
-// row by row.
-constexpr float ND_GROWN[4] = {9.0f, 1e8f, 1e10f, 1e12f};
+// Steps of the largest |T_ij|^2 (tile inverses, in couplings) that count.  A
+// plain solve leaves at most 5e-15 max|T|^2 (480 systems, 33^2 to 401^2; up to
+// 3 couplings what block factors leave) and each correction multiplies that by
+// as much again: above 3, 10^3, 3 10^4 and 2 10^5 couplings a solve without a
+// tolerance takes ND_FIXES corrections, above 10^6 the system is factored row
+// by row.
+constexpr int ND_STEPS = 5;
+constexpr float ND_GROWN[ND_STEPS] = {9.0f, 1e6f, 9e8f, 4e10f, 1e12f};
+constexpr int ND_FIXES[ND_STEPS - 1] = {1, 2, 3, 5};
 
 struct NdSys {        // one system being factored
     Coef cf;

@@ -141,12 +141,12 @@ __device__ __forceinline__ double2 nd_entry(const NdKids& k, bool kids, const Nd
 
 // Notes how far a system's tile inverses grow (m2: this lane's largest
 // |T_ij|^2 over the couplings' scale), one bit per step of ND_GROWN: a box near
-// resonance, behind which solves lose digits (1e-17 to 2e-16 max |T|^2).
+// resonance, behind which solves lose digits (ND_GROWN).
 __device__ __forceinline__ void nd_grown(const NdSys& y, float m2, bool valid) {
     const float sc = (float)fmax(y.cf.hz / y.cf.hx, y.cf.hx / y.cf.hz), v = m2 * sc * sc;
     int bits = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < ND_STEPS; ++k)
         if (__any(valid && !(v <= ND_GROWN[k]))) bits |= 1 << k;
     if (bits && (threadIdx.x & 63) == 0 && (bits & ~y.status[3])) atomicOr(&y.status[3], bits);
 }
