@@ -83,9 +83,10 @@ enum {
  * with partial pivoting inside the tiles.  A nested-dissection factor whose
  * inverses grow (boxes of the dissection near resonance) has each solve
  * without a tolerance corrected one to five times; a system with a box at
- * resonance (a zero pivot, inverses above 1e6) is made row by row.  Returns HELM_ESINGULAR with no factor if a pivot of that
- * is exactly zero, HELM_EINVAL if the model is not positive and finite.
- * Synchronises `stream`.                                                   */
+ * resonance (a zero pivot, inverses above 1e6) is made row by row.  Returns
+ * HELM_ESINGULAR with no factor if a pivot of that is exactly zero,
+ * HELM_EINVAL if the model is not positive and finite.  Synchronises
+ * `stream`.                                                                 */
 int helm_factor(const helm_grid* grid, const double* m_dev, double omega, int precision,
                 void* stream, helm_factor_t* out);
 
